@@ -51,11 +51,10 @@ U_F = 2.0 ** -22
 # HBM bytes per launch of the headline row amplitude kernel, from the
 # FETCH_SIZE / WRITE_SIZE counters (copy-calibrated) recorded in profiles/;
 # valid only for the kernel source they were taken on (first 16 hex digits of
-# the sha256 of psi.hip followed by device.h) and for that workload.
+# the sha256 of psi_tri.h followed by device.h) and for that workload.
 MEASURED_TRAFFIC = {
-    ("c3", "f64"): {"sha16": "a5dfbc82a9b3c72e", "bytes_per_launch": 73.490e9 + 3.728e9},
 }
-KERNEL_SOURCES = ("psi.hip", "device.h")
+KERNEL_SOURCES = ("psi_tri.h", "device.h")
 WORKLOAD_TEXT = {
     "c2": "chain K=20 10a+10b, BDG-RNN chain chi=16, 4096 distinct samples drawn from Phi^2, eps=1e-3, N_eps=64",
     "c3": "chain-like K=50 25a+25b, BDG-RNN NN+NNN chi=32 x cos-RBM N_h=100, 16384 distinct samples drawn "
@@ -69,6 +68,17 @@ def kernel_sha16():
     for f in KERNEL_SOURCES:
         h.update(open(os.path.join(ROOT, "paper_2507_19276_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
+
+
+def row_flops(st, w, prec):
+    """Flops of the row kernel: st["psi_flops"] counts four candidates per site
+    (8 chi^2 d); FP64 rows need their own candidate and the triangular factor
+    of the four (2 chi^2 d + (chi d)^2) where every site has at most three
+    parents and there is no tensor term."""
+    d = [int(b - a) for a, b in zip(w.parent_ptr[:-1], w.parent_ptr[1:])]
+    if prec != "f64" or w.tensor or max(d) > 3:
+        return st["psi_flops"]
+    return st["psi_flops"] * sum(2 * x + x * x for x in d) / sum(8 * x for x in d)
 
 
 def measured_traffic(workload, prec):
@@ -269,9 +279,9 @@ def run_eloc_bench(args):
     N = Wh["w"].n_samples
     head = results[head_prec]
     hs = head["stats"]
-    achieved = hs["psi_flops"] / (hs["ms_psi"] * 1e-3) / 1e12
-    peak = PEAKS[head_prec]
     wh = Wh["w"]
+    achieved = row_flops(hs, wh, head_prec) / (hs["ms_psi"] * 1e-3) / 1e12
+    peak = PEAKS[head_prec]
     line = {
         "metric": "local energies/sec at fixed bond dim D",
         "value": head["value"],
@@ -292,8 +302,8 @@ def run_eloc_bench(args):
         "site_rows_per_step": hs["n_site_rows"],
         "by_precision": {p: {"value": r["value"], "ms_per_step": r["ms_per_step"],
                              "row_kernel_ms": r["stats"]["ms_psi"],
-                             "row_kernel_tflops": r["stats"]["psi_flops"] / r["stats"]["ms_psi"] / 1e9,
-                             "row_kernel_frac_of_peak": r["stats"]["psi_flops"] / r["stats"]["ms_psi"] / 1e9
+                             "row_kernel_tflops": row_flops(r["stats"], wh, p) / r["stats"]["ms_psi"] / 1e9,
+                             "row_kernel_frac_of_peak": row_flops(r["stats"], wh, p) / r["stats"]["ms_psi"] / 1e9
                              / PEAKS[p],
                              "stages_ms": {k: r["stats"][k] for k in ("ms_enumerate", "ms_draw", "ms_rows",
                                                                        "ms_amplitude", "ms_reduce")},
@@ -303,8 +313,9 @@ def run_eloc_bench(args):
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak,
                      "traffic": args.traffic_bytes if args.traffic_bytes else measured_traffic(head_name, head_prec),
-                     "kernel": "k_psi_mt (row amplitude kernel: bond contractions and conditionals)",
-                     "flops_per_launch": hs["psi_flops"], "ms_per_launch": hs["ms_psi"],
+                     "kernel": "row amplitude kernel (bond contractions and conditionals): k_psi_tri in FP64, "
+                               "k_psi_mt in FP32, k_psi_b16 in BF16",
+                     "flops_per_launch": row_flops(hs, wh, head_prec), "ms_per_launch": hs["ms_psi"],
                      "kernel_sha16": kernel_sha16()},
     }
     if not args.headline_only:
@@ -313,7 +324,7 @@ def run_eloc_bench(args):
         line[other] = {"workload": WORKLOAD_TEXT[other],
                        "by_precision": {p: {"value": r["value"], "ms_per_step": r["ms_per_step"],
                                             "row_kernel_ms": r["stats"]["ms_psi"],
-                                            "row_kernel_frac_of_peak": r["stats"]["psi_flops"]
+                                            "row_kernel_frac_of_peak": row_flops(r["stats"], Wo["w"], p)
                                             / r["stats"]["ms_psi"] / 1e9 / PEAKS[p]}
                                         for p, r in ro.items()}}
         eq = {}
@@ -514,12 +525,12 @@ def run_next_bench(args):
     for prec in ("f32", "f64"):
         kw = dict(eps=w.eps, n_eps=w.n_eps, precision=prec, stream_id=0)
         dt, (o, st) = timed(lambda: nqs.eloc_complex(ctx, inst, ans, s, seed=w.seed, **kw), 3)
-        fl = st["psi_flops"] / (st["ms_psi"] * 1e-3) / 1e12
+        fl = row_flops(st, w, prec) / (st["ms_psi"] * 1e-3) / 1e12
         cx[prec] = {"local_energies_per_s": w.n_samples / dt, "ms_per_step": dt * 1e3,
                     "row_kernel_ms": st["ms_psi"], "site_rows": st["n_site_rows"], "E_im": st["E_im"],
                     "roofline": {"bound": "mfma", "achieved": fl, "peak": PEAKS[prec], "unit": "TFLOP/s",
-                                 "frac": fl / PEAKS[prec], "flops_per_launch": st["psi_flops"],
-                                 "kernel": f"k_psi_mt<{'float' if prec == 'f32' else 'double'},32,...,CPLX>"}}
+                                 "frac": fl / PEAKS[prec], "flops_per_launch": row_flops(st, w, prec),
+                                 "kernel": "k_psi_mt<float,32,...,CPLX>" if prec == "f32" else "k_psi_tri<32,...,CPLX>"}}
         print(f"# complex {prec}: {w.n_samples / dt:.0f} E_loc/s, row kernel {st['ms_psi']:.2f} ms, "
               f"{fl:.2f} TFLOP/s", file=sys.stderr, flush=True)
     p = torch.from_numpy(w.params.copy()).cuda()
@@ -607,13 +618,13 @@ def run_configs_bench(args):
             se = float(np.sqrt((wf ** 2 * (el[ok] - E) ** 2).sum()) / wf.sum())
             ess = float(wf.sum() ** 2 / (wf ** 2).sum())
             energies[prec] = (E, se)
-            fl = st["psi_flops"] / (st["ms_psi"] * 1e-3) / 1e12
+            fl = row_flops(st, w, prec) / (st["ms_psi"] * 1e-3) / 1e12
             res[prec] = {"local_energies_per_s": w.n_samples / dt, "ms_per_step": dt * 1e3, "rows": st["n_rows"],
                          "site_rows": st["n_site_rows"], "E": E, "sampling_se": se, "effective_samples": ess,
                          "stage_ms": {k: st[k] for k in ("ms_enumerate", "ms_draw", "ms_rows", "ms_amplitude",
                                                           "ms_reduce", "ms_psi")},
                          "roofline": {"bound": "mfma", "achieved": fl, "peak": PEAKS[prec], "unit": "TFLOP/s",
-                                      "frac": fl / PEAKS[prec], "flops_per_launch": st["psi_flops"],
+                                      "frac": fl / PEAKS[prec], "flops_per_launch": row_flops(st, w, prec),
                                       "kernel": "row amplitude kernel"}}
             print(f"# {name} {prec}: {w.n_samples / dt:.0f} E_loc/s, {st['n_rows']} rows, row kernel "
                   f"{st['ms_psi']:.1f} ms at {fl:.1f} TFLOP/s", file=sys.stderr, flush=True)

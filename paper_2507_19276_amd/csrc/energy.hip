@@ -593,6 +593,17 @@ __global__ void k_gather_logpsi_phase(int64_t N, const double* lphi, const int8_
   if (phase) phase[n] = sphi[n] == 0 ? 0.0 : remainder(ph + (neg_f ? pi : 0.0), 2.0 * pi);
 }
 
+// the samples' own rows (each sample's first) take the samples' values
+__global__ void k_own_rows(int64_t n0, int64_t n1, const int64_t* rowptr, int64_t row_base, const double* lphi_s,
+                           const int8_t* sphi_s, const double* phs_s, double* lphi, int8_t* sphi, double* phs) {
+  const int64_t n = n0 + int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (n >= n1) return;
+  const int64_t r = rowptr[n] - row_base;
+  lphi[r] = lphi_s[n];
+  sphi[r] = sphi_s[n];
+  if (phs) phs[r] = phs_s[n];
+}
+
 __global__ void k_gather_logpsi(int64_t N, const double* lphi, const int8_t* sphi, const double* lf,
                                 const int8_t* sf, double* logabs, int8_t* sign) {
   const int64_t n = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -721,6 +732,15 @@ hipError_t launch_gather_logpsi_phase(int64_t N, const double* lphi, const int8_
   if (N <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_gather_logpsi_phase, dim3(grid_for(N, 256)), dim3(256), 0, st, N, lphi, sphi, phs, lf, sf,
                      logabs, phase);
+  return hipGetLastError();
+}
+
+hipError_t launch_own_rows(int64_t n0, int64_t n1, const int64_t* rowptr, int64_t row_base, const double* lphi_s,
+                           const int8_t* sphi_s, const double* phs_s, double* lphi, int8_t* sphi, double* phs,
+                           hipStream_t st) {
+  if (n1 <= n0) return hipSuccess;
+  hipLaunchKernelGGL(k_own_rows, dim3(grid_for(n1 - n0, 256)), dim3(256), 0, st, n0, n1, rowptr, row_base, lphi_s,
+                     sphi_s, phs_s, lphi, sphi, phs);
   return hipGetLastError();
 }
 

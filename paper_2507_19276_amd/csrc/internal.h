@@ -252,7 +252,8 @@ struct SampleArgs {
 template <typename T> struct PsiParams;
 // PSI_NODE: SEED for the units of a node list (resumed from their samples)
 // plus the compact store of nodes.hip.
-enum { PSI_PLAIN = 0, PSI_STORE = 1, PSI_SEED = 2, PSI_NODE = 3 };
+// PSI_ROWS: PLAIN for the rows of a local energy (the kernel that SEED takes).
+enum { PSI_PLAIN = 0, PSI_STORE = 1, PSI_SEED = 2, PSI_NODE = 3, PSI_ROWS = 4 };
 // what the amplitude kernels read of a node (one 32-byte record, a single
 // cache line): log-product entries from off, carried-state slots from coff
 // for the sites marked in need, the changed site c1 and the last resume site e1
@@ -290,6 +291,74 @@ struct PsiStates {
   const NodeRec* nrec = nullptr; // [nodes]
   const int32_t* unode = nullptr;// SEED rows: [rows] node the row resumes from (-1: its sample)
 };
+// ---- operand stream of the triangular-normaliser forward (psi_tri.h) --------
+// 16x16 blocks of A operands, 256 doubles each: lane l holds row
+// 4 (m % 4) + m / 4 of the block (m = l % 16: the 16x16x4 f64 MFMA returns row
+// g + 4 v in register v of lane group g, so lane group g ends up with units
+// 4 g + v) and columns 4 (l / 16) + 0..3, its operands of the block's four
+// k-steps.  Per site the parts R, C_0 .. C_3, each padded to a multiple of the
+// kernel's window of tri_pw blocks; rows of a part in groups of tri_rp.
+__host__ __device__ constexpr int tri_pw(int CH) { return CH == 16 ? 1 : (CH == 32 ? 2 : 4); }
+__host__ __device__ constexpr int tri_rp(int CH) { return CH <= 32 ? 1 : 2; }
+__host__ __device__ constexpr int tri_pad(int n, int pw) { return (n + pw - 1) / pw * pw; }
+// blocks of the parts at a site with d parents (d >= 1; a parentless site has one zero edge)
+__host__ __device__ constexpr int tri_lr(int CH, int d) {
+  return tri_pad((d * CH / 16) * (d * CH / 16 + 1) / 2, tri_pw(CH));
+}
+__host__ __device__ constexpr int tri_lc(int CH, int d) { return tri_pad((CH / 16) * (d * CH / 16), tri_pw(CH)); }
+__host__ __device__ constexpr int tri_site_blocks(int CH, int d) { return tri_lr(CH, d) + 4 * tri_lc(CH, d); }
+// tiles of 16 rows per wavefront, by the largest in-degree.  Each operand block
+// feeds this many tiles; the LDS ring holds 2 KB per tile, unit tile and slot.
+__host__ __device__ constexpr int tri_tiles(int CH, int dm) {
+  return CH == 16 || dm <= 2 ? 2 : 1;
+}
+constexpr int kTriMaxDegree = 3;
+constexpr size_t kTriRingBytes = 64 * 1024;   // LDS ring of one wavefront at most
+
+// The triangular-normaliser forward of FP64 rows (psi_tri.h): edge tables and
+// vectors of the folded layout, and the operand stream.
+struct TriParams {
+  int K, chip, na, nb, W, dmax;  // W: ring slots; dmax: largest in-degree, 1..kTriMaxDegree
+  const int* pptr;               // forward edges, ring slots and live masks as in PsiParams
+  const int* slot;
+  const int* wsl;
+  const uint64_t* live;
+  const double* Q;               // blocks of 16x16 operands, then the sites' vectors
+  int qbytes, vofs;              // size of Q and byte offset of the vectors: per site
+                                 // (r [dmax][chip] of Z = |R x + r|^2 + rho, v [4][chip], w [chip], w2 [chip])
+  const int* qoff;               // [K] first block of each site
+  const double* rho;             // [K]
+  const double* c;               // [K]
+  const double* c2;              // complex parameters, as in PsiParams
+};
+// what the operands are made from: packed (realified) parameters on the device
+struct TriBuild {
+  int chi, chip;
+  const int* pptr;               // device [K+1] parents of each site
+  const int* pidx;
+  const double* prm;
+  const int64_t* offM;           // [edges]
+  const int64_t* offV;           // [K]
+  const int64_t* offEta;         // [K] (w follows eta)
+  const int64_t* offW2;          // [K] complex parameters, else null
+  double* G;                     // scratch: [K][gstride], gstride >= 4 chi (chi dmax + 1)
+  int64_t gstride;
+};
+hipError_t launch_tri_build(const TriBuild& B, const TriParams& P, double* Q, double* rho, hipStream_t st);
+hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                          hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+hipError_t launch_tri_16(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+hipError_t launch_tri_32(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+hipError_t launch_tri_48(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+hipError_t launch_tri_64(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+// lphi/sphi (and phs, nullable) of the pass's own rows from the samples' values
+hipError_t launch_own_rows(int64_t n0, int64_t n1, const int64_t* rowptr, int64_t row_base, const double* lphi_s,
+                           const int8_t* sphi_s, const double* phs_s, double* lphi, int8_t* sphi, double* phs,
+                           hipStream_t st);
 // node list written by nodes.hip
 struct NodeList {
   uint64_t* m;                   // [nodes][2] ONV: the sample with its rows' first (two) changes
@@ -412,6 +481,16 @@ inline int64_t order_blocks(int64_t R) { return (R + kOrderChunk - 1) / kOrderCh
 // (device); perm: [R] rows in (t0, row) order; t0s: [R] t0 of each position.
 hipError_t launch_order_t0(const uint8_t* t0, int64_t R, int K, int32_t* cnt, int64_t* tot, int32_t* perm,
                            uint8_t* t0s, hipStream_t st);
+// Rows of the samples n0 .. n1-1 by (resume site, sample, state there, next
+// changed site); cnt: [n1 - n0][K+1] int32 scratch, tot, perm, t0s as above.
+hipError_t launch_order_rows(const uint8_t* site, const uint64_t* m, const uint64_t* samples, const int64_t* rowptr,
+                             int64_t n0, int64_t n1, int64_t row_base, int64_t R, int K, int32_t* cnt, int64_t* tot,
+                             int32_t* perm, uint8_t* t0s, hipStream_t st);
+// The node units of ns samples (nbase[s] < 0: none; nn in all) in the order
+// described in order.hip; cnt: [ns] int32 scratch, tot: [1].
+hipError_t launch_order_nodes(const uint8_t* c1, const uint8_t* e1, const int64_t* nbase, const int32_t* ncnt,
+                              int64_t ns, int64_t nn, int K, int32_t* cnt, int64_t* tot, int32_t* perm, uint8_t* c1s,
+                              hipStream_t st);
 // The same in (t0, t1, row) order (t1[r] in [0, K]); tmp_perm: [2 R] int32,
 // tmp_key: [2 R] bytes of scratch.
 hipError_t launch_order_t0_t1(const uint8_t* t0, const uint8_t* t1, int64_t R, int K, int32_t* cnt, int64_t* tot,

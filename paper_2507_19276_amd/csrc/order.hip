@@ -123,6 +123,156 @@ __global__ __launch_bounds__(256) void k_t0_scatter(const uint8_t* __restrict__ 
   }
 }
 
+// Order of the FP64 rows (psi_tri.h): by resume site, then sample, then the
+// row's state at the resume site and its next changed site after it, so that the
+// rows of a wavefront agree on nearly every site they evaluate.  The rows of
+// a sample are contiguous, so one workgroup per sample counts its rows per
+// resume site (launch 1), the columns are scanned over the samples (k_t0_scan),
+// and the workgroup places its rows with LDS counters over (resume site, state,
+// next change).  Rows with equal keys take their places in any order (LDS
+// atomics): which rows share a wavefront does not change a bit of any.
+constexpr int kRowOrderThreads = 512;
+
+__global__ __launch_bounds__(kRowOrderThreads) void k_row_count(const uint8_t* __restrict__ site,
+                                                                const int64_t* __restrict__ rowptr, int64_t n0,
+                                                                int64_t row_base, int K, int32_t* __restrict__ cnt) {
+  __shared__ int h[65];
+  const int tid = threadIdx.x;
+  if (tid <= K) h[tid] = 0;
+  __syncthreads();
+  const int64_t r1 = rowptr[n0 + blockIdx.x + 1] - row_base;
+  for (int64_t r = rowptr[n0 + blockIdx.x] - row_base + tid; r < r1; r += kRowOrderThreads) atomicAdd(&h[site[r]], 1);
+  __syncthreads();
+  if (tid <= K) cnt[int64_t(blockIdx.x) * (K + 1) + tid] = h[tid];
+}
+
+// LDS bin of a row: (resume site, state there, next changed site)
+__device__ inline int row_bin(int t, uint64_t lo, uint64_t hi, uint64_t nlo, uint64_t nhi, int K) {
+  if (t >= K) return K * 4 * (K + 1);
+  const uint64_t ev = 0x5555555555555555ull;
+  uint64_t xl = lo ^ nlo, xh = hi ^ nhi;
+  xl = (xl | (xl >> 1)) & ev;
+  xh = (xh | (xh >> 1)) & ev;
+  // keep the changes above site t
+  if (t < 31) xl &= ~0ull << (2 * t + 2);
+  else {
+    xl = 0;
+    if (t > 31) xh = t < 63 ? xh & (~0ull << (2 * t - 62)) : 0;
+  }
+  const int next = xl ? __builtin_ctzll(xl) >> 1 : (xh ? 32 + (__builtin_ctzll(xh) >> 1) : K);
+  const int s = t < 32 ? int((lo >> (2 * t)) & 3ull) : int((hi >> (2 * t - 64)) & 3ull);
+  return (t * 4 + s) * (K + 1) + next;
+}
+
+__global__ __launch_bounds__(kRowOrderThreads) void k_row_place(
+    const uint8_t* __restrict__ site, const uint64_t* __restrict__ m, const uint64_t* __restrict__ samples,
+    const int64_t* __restrict__ rowptr, int64_t n0, int64_t row_base, int K, const int32_t* __restrict__ off,
+    const int64_t* __restrict__ tot, int32_t* __restrict__ perm, uint8_t* __restrict__ t0s) {
+  extern __shared__ int bins[];   // [K + 1][4][K + 1], the last site's one bin
+  __shared__ int start[65];
+  const int tid = threadIdx.x, per = 4 * (K + 1), nbin = K * per + 1;
+  const int64_t n = n0 + blockIdx.x;
+  const int64_t r0 = rowptr[n] - row_base, r1 = rowptr[n + 1] - row_base;
+  const uint64_t nlo = samples[2 * n], nhi = samples[2 * n + 1];
+  for (int k = tid; k < nbin; k += kRowOrderThreads) bins[k] = 0;
+  if (tid < 64) {
+    // first position of each site: the lower sites' totals and the lower samples' rows
+    int64_t a = tid <= K ? tot[tid] : 0;
+    const int64_t own = a;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t x = __shfl_up(a, o);
+      if (tid >= o) a += x;
+    }
+    if (tid <= K) start[tid] = int(a - own) + off[int64_t(blockIdx.x) * (K + 1) + tid];
+    if (tid == 63 && K == 64) start[64] = int(a) + off[int64_t(blockIdx.x) * 65 + 64];
+  }
+  __syncthreads();
+  for (int64_t r = r0 + tid; r < r1; r += kRowOrderThreads)
+    atomicAdd(&bins[row_bin(site[r], m[2 * r], m[2 * r + 1], nlo, nhi, K)], 1);
+  __syncthreads();
+  // exclusive scan of each site's bins from its first position, a wavefront per site
+  const int wv = tid >> 6, lane = tid & 63;
+  for (int t = wv; t <= K; t += kRowOrderThreads / 64) {
+    int run = start[t];
+    const int len = t < K ? per : 1;
+    for (int k0 = 0; k0 < len; k0 += 64) {
+      const int k = k0 + lane;
+      const int c = k < len ? bins[t * per + k] : 0;
+      int a = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(a, o);
+        if (lane >= o) a += x;
+      }
+      if (k < len) bins[t * per + k] = run + a - c;
+      run += __shfl(a, 63);
+    }
+  }
+  __syncthreads();
+  for (int64_t r = r0 + tid; r < r1; r += kRowOrderThreads) {
+    const int t = site[r];
+    const int pos = atomicAdd(&bins[row_bin(t, m[2 * r], m[2 * r + 1], nlo, nhi, K)], 1);
+    perm[pos] = int32_t(r);
+    t0s[pos] = uint8_t(t);
+  }
+}
+
+// Order of the node units of the triangular-normaliser forward.  A
+// wavefront runs from its units' lowest changed site to their last site and pays
+// for every local state that occurs among them, so its units should be of one
+// sample and end together: the units that run to the last site (about a third,
+// with two thirds of the sites at K = 50) come first, then the others, each in
+// sample order, a sample's units by changed site upwards in even samples and
+// downwards in odd ones, so that a wavefront across two samples joins
+// neighbouring sites.  (NN+NNN chain K = 50, 16384 samples: node pass 213 ms
+// in the order of the changed site alone, 129 ms here; the four-candidate
+// kernel took 114 ms.)
+__global__ __launch_bounds__(256) void k_norder_count(const uint8_t* __restrict__ e1, const int64_t* __restrict__ nbase,
+                                                      const int32_t* __restrict__ ncnt, int K,
+                                                      int32_t* __restrict__ cnt) {
+  __shared__ int c;
+  if (threadIdx.x == 0) c = 0;
+  __syncthreads();
+  const int64_t b = nbase[blockIdx.x];
+  const int n = b < 0 ? 0 : ncnt[blockIdx.x];
+  int own = 0;
+  for (int k = threadIdx.x; k < n; k += 256) own += e1[b + k] >= K;
+  if (own) atomicAdd(&c, own);
+  __syncthreads();
+  if (threadIdx.x == 0) cnt[blockIdx.x] = c;
+}
+
+__global__ __launch_bounds__(64) void k_norder_place(const uint8_t* __restrict__ c1, const uint8_t* __restrict__ e1,
+                                                     const int64_t* __restrict__ nbase,
+                                                     const int32_t* __restrict__ ncnt, int K,
+                                                     const int32_t* __restrict__ off, const int64_t* __restrict__ tot,
+                                                     int64_t ns, int64_t nn, int32_t* __restrict__ perm,
+                                                     uint8_t* __restrict__ c1s) {
+  const int64_t s = blockIdx.x, b = nbase[s];
+  if (b < 0) return;
+  const int n = ncnt[s], lane = threadIdx.x;
+  const int64_t l0 = off[s], h0 = tot[0] + b - l0;   // the sample's first place among the long and the short units
+  const int64_t lend = s + 1 < ns ? int64_t(off[s + 1]) : tot[0];
+  const int nl = int(lend - l0), nh = n - nl;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int rl = 0, rh = 0;
+  for (int k0 = 0; k0 < n; k0 += 64) {
+    const int k = k0 + lane;
+    const bool in = k < n, lg = in && e1[b + (in ? k : 0)] >= K;
+    const uint64_t ml = __ballot(lg), mh = __ballot(in && !lg);
+    if (in) {
+      const int r = lg ? rl + __popcll(ml & below) : rh + __popcll(mh & below);
+      const int len = lg ? nl : nh;
+      const int64_t pos = (lg ? l0 : h0) + ((s & 1) ? len - 1 - r : r);
+      if (pos < nn) {
+        perm[pos] = int32_t(b + k);
+        c1s[pos] = c1[b + k];
+      }
+    }
+    rl += __popcll(ml);
+    rh += __popcll(mh);
+  }
+}
+
 // dst[p] = src[perm[p]]
 __global__ __launch_bounds__(256) void k_gather_u8(const uint8_t* __restrict__ src, const int32_t* __restrict__ perm,
                                                    int64_t n, uint8_t* __restrict__ dst) {
@@ -147,6 +297,32 @@ hipError_t launch_order_t0(const uint8_t* t0, int64_t R, int K, int32_t* cnt, in
   hipLaunchKernelGGL(k_t0_count, dim3(unsigned(nb)), dim3(256), 0, st, t0, R, K, cnt);
   hipLaunchKernelGGL(k_t0_scan, dim3(unsigned(K + 1)), dim3(256), 0, st, cnt, nb, K, tot);
   hipLaunchKernelGGL(k_t0_scatter, dim3(unsigned(nb)), dim3(256), 0, st, t0, R, K, cnt, tot, perm, t0s);
+  return hipGetLastError();
+}
+
+hipError_t launch_order_rows(const uint8_t* site, const uint64_t* m, const uint64_t* samples, const int64_t* rowptr,
+                             int64_t n0, int64_t n1, int64_t row_base, int64_t R, int K, int32_t* cnt, int64_t* tot,
+                             int32_t* perm, uint8_t* t0s, hipStream_t st) {
+  if (R <= 0) return hipSuccess;
+  if (K < 1 || K > 64 || R >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  const int64_t ns = n1 - n0;
+  hipLaunchKernelGGL(k_row_count, dim3(unsigned(ns)), dim3(kRowOrderThreads), 0, st, site, rowptr, n0, row_base, K,
+                     cnt);
+  hipLaunchKernelGGL(k_t0_scan, dim3(unsigned(K + 1)), dim3(256), 0, st, cnt, ns, K, tot);
+  const size_t lds = size_t(K * 4 * (K + 1) + 1) * sizeof(int);
+  hipLaunchKernelGGL(k_row_place, dim3(unsigned(ns)), dim3(kRowOrderThreads), lds, st, site, m, samples, rowptr, n0,
+                     row_base, K, cnt, tot, perm, t0s);
+  return hipGetLastError();
+}
+
+hipError_t launch_order_nodes(const uint8_t* c1, const uint8_t* e1, const int64_t* nbase, const int32_t* ncnt,
+                              int64_t ns, int64_t nn, int K, int32_t* cnt, int64_t* tot, int32_t* perm, uint8_t* c1s,
+                              hipStream_t st) {
+  if (nn <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_norder_count, dim3(unsigned(ns)), dim3(256), 0, st, e1, nbase, ncnt, K, cnt);
+  hipLaunchKernelGGL(k_t0_scan, dim3(1), dim3(256), 0, st, cnt, ns, 0, tot);
+  hipLaunchKernelGGL(k_norder_place, dim3(unsigned(ns)), dim3(64), 0, st, c1, e1, nbase, ncnt, K, cnt, tot, ns, nn,
+                     perm, c1s);
   return hipGetLastError();
 }
 

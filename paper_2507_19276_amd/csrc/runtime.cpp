@@ -378,6 +378,14 @@ struct nqs_ansatz {
   int64_t nr_params = 0;
   std::vector<int64_t> offW2x, offC2x, cx_offM, cx_offV, cx_offEta, cx_offW, cx_offC;
   int64_t cx_offB = 0;
+  // the triangular-normaliser forward of FP64 rows (psi_tri.h): whether the
+  // graph takes it (create), whether the bound parameters do (bind), its operands
+  bool tri_graph = false, tri = false;
+  int dmax = 1;
+  int* d_qoff = nullptr;
+  double *triQ = nullptr, *tri_rho = nullptr, *tri_G = nullptr;
+  int tri_bytes = 0, tri_vofs = 0;
+  int64_t tri_gstride = 0;
   int64_t* d_cx = nullptr;  // device: rW, rC, rW2, rC2, cV, cEta, cW, cC ([K] each), then cM ([edges])
   ~nqs_ansatz() {
     L64.free_all();
@@ -389,7 +397,7 @@ struct nqs_ansatz {
                     (void*)bfAlo,
                     (void*)d_cb, (void*)d_cW, (void*)d_cW1t, (void*)d_cS, (void*)d_cS32, (void*)d_tn_edge,
                     (void*)d_tn_site, (void*)tn64, (void*)tn32, (void*)d_offM, (void*)d_offV,
-                    (void*)d_offEta, (void*)d_cx, (void*)d_tsite})
+                    (void*)d_offEta, (void*)d_cx, (void*)d_tsite, (void*)d_qoff, (void*)triQ, (void*)tri_rho, (void*)tri_G})
       if (p) (void)hipFree(p);
   }
   template <typename T>
@@ -413,6 +421,14 @@ struct nqs_ansatz {
     P.w2 = L.w2; P.c2 = L.c2;
     P.TA = tn_mfma ? L.TA : nullptr;
     P.tsite = d_tsite;
+    return P;
+  }
+  TriParams tri_params() const {
+    TriParams P;
+    P.K = K; P.chip = chip; P.na = na; P.nb = nb; P.W = ring; P.dmax = dmax;
+    P.pptr = d_fptr; P.slot = d_fslot; P.wsl = d_wsl; P.live = d_live;
+    P.Q = triQ; P.qoff = d_qoff; P.qbytes = tri_bytes; P.vofs = tri_vofs; P.rho = tri_rho;
+    P.c = F64.c; P.c2 = F64.c2;
     return P;
   }
   CxMap cxmap() const {
@@ -1100,6 +1116,30 @@ nqs_status nqs_ansatz_create(nqs_ctx* ctx, int K, int n_alpha, int n_beta, int c
   }
   a->d1 = true;
   for (int i = 0; i < K; ++i) a->d1 = a->d1 && fptr[i + 1] - fptr[i] == 1;
+  // FP64 rows take the triangular normaliser (psi_tri.h) where its operands
+  // are fewer than the four candidates' (up to three parents: n (n + 1) / 2 +
+  // chi/16 n against 4 chi/16 n blocks for n = d chi/16, 126 against 192 at
+  // chi = 64, d = 3) and the ring of one of its wavefronts, which holds more
+  // rows than psi.hip's, leaves the LDS room for at least two.
+  for (int i = 0; i < K; ++i) a->dmax = std::max(a->dmax, fptr[i + 1] - fptr[i]);
+  a->tri_graph = !a->tensor && a->dmax <= kTriMaxDegree &&
+                 size_t(a->ring) * tri_tiles(a->chip, a->dmax) * 16 * a->chip * 8 <= kTriRingBytes;
+  if (a->tri_graph) {
+    std::vector<int> qoff(K);
+    int64_t nblk = 0;
+    for (int i = 0; i < K; ++i) {
+      qoff[i] = int(nblk);
+      nblk += tri_site_blocks(a->chip, fptr[i + 1] - fptr[i]);
+    }
+    nblk += 2;   // the window's fetches past the last part
+    a->tri_gstride = int64_t(4) * chi * (int64_t(chi) * a->dmax + 1);
+    if ((st = upload(&a->d_qoff, qoff)) != NQS_OK) return st;
+    a->tri_vofs = int(nblk * 2048);
+    a->tri_bytes = a->tri_vofs + K * (a->dmax + 6) * a->chip * int(sizeof(double));
+    HIPCHK(hipMalloc((void**)&a->triQ, size_t(a->tri_bytes)));
+    HIPCHK(hipMalloc((void**)&a->tri_rho, size_t(K) * sizeof(double)));
+    HIPCHK(hipMalloc((void**)&a->tri_G, size_t(K) * a->tri_gstride * sizeof(double)));
+  }
   if ((st = upload(&a->d_fptr, fptr)) != NQS_OK) return st;
   if ((st = upload(&a->d_fslot, fslot)) != NQS_OK) return st;
   if ((st = upload(&a->d_offM, a->offM)) != NQS_OK) return st;
@@ -1259,6 +1299,29 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
     if ((st = build_layout<float>(ans, prm, ans->F32, true)) != NQS_OK) return st;
     ans->has_fold = true;
   }
+  // the triangular factors of the folded layout, made on the device (not from
+  // infinities or NaN: a factorisation would spread them over every candidate)
+  ans->tri = false;
+  bool finite = ans->tri_graph && ans->has_fold;
+  for (size_t k = 0; finite && k < prm.size(); ++k) finite = std::isfinite(prm[k]);
+  double* d_real = nullptr;   // complex parameters: the realified vector
+  struct FreeReal {
+    double** p;
+    ~FreeReal() { if (*p) (void)hipFree(*p); }
+  } free_real{&d_real};
+  if (finite) {
+    if (ans->cplx && (st = upload(&d_real, prm)) != NQS_OK) return st;
+    TriBuild B;
+    B.chi = ans->chi; B.chip = ans->chip;
+    B.pptr = ans->d_pptr; B.pidx = ans->d_pidx;
+    B.prm = ans->cplx ? d_real : params;
+    B.offM = ans->d_offM; B.offV = ans->d_offV; B.offEta = ans->d_offEta;
+    B.offW2 = ans->cplx ? ans->d_cx + 2 * ans->K : nullptr;
+    B.G = ans->tri_G; B.gstride = ans->tri_gstride;
+    HIPCHK(launch_tri_build(B, ans->tri_params(), ans->triQ, ans->tri_rho, stream));
+    HIPCHK(hipStreamSynchronize(stream));   // the caller's buffer may change after the call
+    ans->tri = true;
+  }
   if (!ans->cplx && (st = build_bf16(ans, prm, ans->has_fold)) != NQS_OK) return st;
   if (ans->tensor && (st = build_tn(ans, prm)) != NQS_OK) return st;
   if (ans->d_cb) { (void)hipFree(ans->d_cb); ans->d_cb = nullptr; }
@@ -1382,14 +1445,23 @@ size_t state_bytes(int precision) { return precision == NQS_F64 ? 8 : (precision
 size_t mantissa_bytes(int precision) { return precision == NQS_F64 ? 8 : 4; }
 
 // amplitudes of R rows into (lphi, sphi).  mode PSI_STORE (samples, with rs)
-// or PSI_SEED (rows of a pass, with rs and its order).
+// or PSI_SEED (rows of a pass, with rs and its order).  The rows of a local
+// energy (every mode but PLAIN) take the triangular normaliser in FP64 where
+// there is one; the amplitudes that PLAIN and STORE return for samples are those
+// of the four-candidate sum, as the sampler's.
 // phs: complex parameters, the phase of each row
 nqs_status run_amplitudes(const nqs_ansatz* a, int precision, const uint64_t* m, int64_t R, double* lphi,
                           int8_t* sphi, hipStream_t st, const Resume* rs = nullptr, int mode = PSI_PLAIN,
                           double* phs = nullptr) {
-  if (mode != PSI_PLAIN && !rs) return fail(NQS_EINVAL, "resume state missing");
+  if (mode != PSI_PLAIN && mode != PSI_ROWS && !rs) return fail(NQS_EINVAL, "resume state missing");
+  if (a->cplx && !phs) return fail(NQS_EINVAL, "complex amplitudes need their phases");
+  if (precision == NQS_F64 && a->tri && mode != PSI_PLAIN) {
+    HIPCHK(launch_psi_tri(a->tri_params(), m, R, lphi, sphi, st, rs ? states<double>(*rs) : PsiStates<double>(), mode,
+                          a->cplx ? phs : nullptr));
+    return NQS_OK;
+  }
+  if (mode == PSI_ROWS) mode = PSI_PLAIN;
   if (a->cplx) {
-    if (!phs) return fail(NQS_EINVAL, "complex amplitudes need their phases");
     if (precision == NQS_F64) {
       HIPCHK(launch_psi_f64(a->params(a->fwd64()), m, R, lphi, sphi, st,
                             rs ? states<double>(*rs) : PsiStates<double>(), mode, phs));
@@ -1892,6 +1964,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
   const int64_t max_pass_samples = max_samples_per_pass(passes);
   const bool tn = ans->tensor;
   const bool pair = pair_nodes(K, tn);
+  const bool tri = ans->tri && opts->precision == NQS_F64;
   const NodeCaps caps = node_caps(cap_used, K, ans->W, pair, tn, ctx->node_cap_scale.load());
   const int64_t scap = node_slots(caps, K, tn);
   NodeList nl{};
@@ -1974,6 +2047,16 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
       ms_amp += t;
     }
   }
+  if (tri && !resume) {
+    // the samples' own amplitudes (run_amplitudes), kept in outputs that the
+    // reduction writes after it has read them
+    lphi_s = f2;
+    sphi_s = reinterpret_cast<int8_t*>(et) + 7 * N;   // above what earlier passes' reductions write
+    phs_s = ans->cplx ? el : nullptr;
+    if ((s = run_amplitudes(ans, opts->precision, samples, N, lphi_s, sphi_s, stream, nullptr, PSI_PLAIN, phs_s)) !=
+        NQS_OK)
+      return s;
+  }
   for (auto& pr : passes) {
     const int64_t n0 = pr.first, n1 = pr.second;
     const int64_t Rp = P.rowptr_host[n1] - P.rowptr_host[n0];
@@ -1995,8 +2078,14 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
         HIPCHK(launch_node_assign(P.rows.t0, P.rows.sec, samples, P.rowptr, n0, n1, row_base, K, ans->W, pair, nbase,
                                   ebase, nl, row_node, row_site, stream));
         const int64_t nn = tot2[0];
-        // the rows' order first: it fixes which node states the row pass reads
-        HIPCHK(launch_order_t0(row_site, Rp, K, rs.cnt, rs.tot, rs.perm, rs.t0, stream));
+        // the rows' order first: it fixes which node states the row pass reads.
+        // Its per-sample counts live in the node states' storage, written later.
+        const size_t nhs_ints = size_t(scap) * ans->chip * (state_bytes(opts->precision) / sizeof(int32_t));
+        if (tri && size_t(ns) * (K + 1) <= nhs_ints)
+          HIPCHK(launch_order_rows(row_site, P.rows.m, samples, P.rowptr, n0, n1, row_base, Rp, K,
+                                   static_cast<int32_t*>(rs.nhs), rs.tot, rs.perm, rs.t0, stream));
+        else
+          HIPCHK(launch_order_t0(row_site, Rp, K, rs.cnt, rs.tot, rs.perm, rs.t0, stream));
         if (nn > 0) {
           HIPCHK(launch_node_need(rs.perm, rs.t0, Rp, ans->W, row_node, nl.c1, nl.need, stream));
           // node records; carried-state slots only for the sites some row
@@ -2008,7 +2097,11 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
           // site and stops after its units' last site.  At smaller chi a site
           // costs little next to a unit's start, and the changed-site order,
           // which keeps a sample's units together, measured faster.
-          if (ans->chip >= 32)
+          if (tri && size_t(ns) <= nhs_ints)
+            // its counts too where the node pass will write its states
+            HIPCHK(launch_order_nodes(nl.c1, nl.e1, nbase, ncnt, ns, nn, K, static_cast<int32_t*>(rs.nhs), ntot_s,
+                                      nperm, nt0s, stream));
+          else if (ans->chip >= 32)
             HIPCHK(launch_order_t0_t1(nl.c1, nl.e1, nn, K, ncnt_s, ntot_s, ntmp_p, ntmp_k, nperm, nt0s, stream));
           else
             HIPCHK(launch_order_t0(nl.c1, nn, K, ncnt_s, ntot_s, nperm, nt0s, stream));
@@ -2045,7 +2138,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
       }
     } else {
       if (timing) HIPCHK(hipEventRecord(kq[0], stream));
-      if ((s = run_amplitudes(ans, opts->precision, P.rows.m, Rp, lphi, sphi, stream, nullptr, PSI_PLAIN, phs)) !=
+      if ((s = run_amplitudes(ans, opts->precision, P.rows.m, Rp, lphi, sphi, stream, nullptr, PSI_ROWS, phs)) !=
           NQS_OK)
         return s;
       if (timing) HIPCHK(hipEventRecord(kq[1], stream));
@@ -2053,6 +2146,8 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
       psi_flops += double(Rp) * tail_flops[0];
     }
     if (timing) HIPCHK(hipEventRecord(pe[2], stream));
+    if (tri)
+      HIPCHK(launch_own_rows(n0, n1, P.rowptr, P.rowptr_host[n0], lphi_s, sphi_s, phs_s, lphi, sphi, phs, stream));
     if (ans->nh)
       HIPCHK(launch_corr_rows(ans->corr(), P.rows.m, P.rows.owner, samples, theta, Etab, Rp, opts->precision, lf,
                               sf, stream));
