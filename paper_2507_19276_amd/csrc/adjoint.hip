@@ -73,18 +73,26 @@ __device__ inline void counts_below(uint64_t lo, uint64_t hi, int i, int& ca, in
   cb = __popcll(lo & mlo & (ev << 1)) + __popcll(hi & mhi & (ev << 1));
 }
 
-// Kernel A: one wavefront = 16 rows of site i.
+// Kernel A: one workgroup of four wavefronts = 16 rows of site i.  The sweep over
+// the sites is serial and a batch of a few thousand rows has only a few hundred
+// tiles, so a launch lasts as long as one tile's chain of loads and MFMAs:
+// wavefront s recomputes candidate s (its states and P^s go to the others
+// through LDS), and the parents' cotangents are split over (edge, unit tile).
+// Every sum keeps one order, so a gradient's bits do not depend on the split.
+// (NN+NNN K = 50, chi = 32, FP64, 4096 rows: 46 us per site with one wavefront
+// per tile.)
 template <typename T, int CH, bool CPLX>
 __global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i, const uint64_t* m, int64_t R,
                                                   int64_t Rpad, const double* cot, const T* Hbuf,
                                                   T* dcarry, T* Dc, T* Eeta) {
   typedef typename V4<T>::type V;
   constexpr int TPC = CH / 16, NT = 4 * TPC, KS = CH / 4;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  __shared__ V xb[NT * 64];       // candidates, then dcand: [s][tile][lane]
+  __shared__ T pb[4 * 64];
+  __shared__ T zb[2 * 16];
+  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int j = lane & 15, g = lane >> 4;
-  const int64_t tile = int64_t(blockIdx.x) * 4 + wv;
-  const int64_t row0 = tile * 16;
-  if (row0 >= Rpad) return;
+  const int64_t row0 = int64_t(blockIdx.x) * 16;
   const int64_t row = row0 + j;
   const bool live = row < R;
   const int64_t rr = live ? row : (R - 1);
@@ -92,15 +100,15 @@ __global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i, const u
   const double gd = live ? cot[row] : 0.0;
   const T gg = T(gd);
   const int e0 = P.pptr[i], e1 = P.pptr[i + 1];
-  // recompute the candidates (A operand: W^T with the k-permutation, B: own
+  // recompute the candidate (A operand: W^T with the k-permutation, B: own
   // row's stored parent state, units 16t + 4g + v in component v)
-  V acc[NT];
+  V acc[TPC];
 #pragma unroll
-  for (int ot = 0; ot < NT; ++ot) acc[ot] = V{0, 0, 0, 0};
+  for (int ot = 0; ot < TPC; ++ot) acc[ot] = V{0, 0, 0, 0};
   for (int e = e0; e < e1; ++e) {
     const int pj = P.pidx[e];
     const T* hp = Hbuf + (size_t(pj) * Rpad + row) * CH + 4 * g;
-    const T* Ae = P.AF + P.afoff[i] + size_t(e - e0) * (KS * NT * 64) + lane;
+    const T* Ae = P.AF + P.afoff[i] + size_t(e - e0) * (KS * NT * 64) + size_t(s) * TPC * 64 + lane;
 #pragma unroll
     for (int t = 0; t < TPC; ++t) {
       const V hb = *reinterpret_cast<const V*>(hp + 16 * t);
@@ -109,64 +117,71 @@ __global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i, const u
         const int q = 4 * t + v;
         const T b = hb[v];
 #pragma unroll
-        for (int ot = 0; ot < NT; ++ot) acc[ot] = mfma(Ae[(q * NT + ot) * 64], b, acc[ot]);
+        for (int ot = 0; ot < TPC; ++ot) acc[ot] = mfma(Ae[(q * NT + ot) * 64], b, acc[ot]);
       }
     }
   }
   const T* vi = P.v + size_t(i) * 4 * CH;
   const T* ei = P.eta + size_t(i) * CH;
-  T ps[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
+  {
     T p = 0;
 #pragma unroll
     for (int t = 0; t < TPC; ++t) {
       const int u0 = 16 * t + 4 * g;
       const V vv = *reinterpret_cast<const V*>(vi + s * CH + u0);
       const V ee = *reinterpret_cast<const V*>(ei + u0);
-      V x = acc[s * TPC + t] + vv;
+      V x = acc[t] + vv;
       if (P.tadd) x += *reinterpret_cast<const V*>(P.tadd + (size_t(row) * 4 + s) * CH + u0);
-      acc[s * TPC + t] = x;
+      acc[t] = x;
+      xb[(s * TPC + t) * 64 + lane] = x;
       p += ee.x * x.x * x.x + ee.y * x.y * x.y + ee.z * x.z * x.z + ee.w * x.w * x.w;
     }
     p += __shfl_xor(p, 16);
     p += __shfl_xor(p, 32);
-    ps[s] = p;
+    pb[s * 64 + lane] = p;
   }
   int ca, cb;
   counts_below(lo, hi, i, ca, cb);
   const int si = site_state(lo, hi, i);
+  if (CPLX) {
+    // z of the row's own candidate
+    T zr = T(0), zi = T(0);
+#pragma unroll
+    for (int t = 0; t < TPC; ++t) {
+      const int u0 = 16 * t + 4 * g;
+      const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
+      const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
+      const V x = acc[t];
+      zr += wa.x * x.x + wa.y * x.y + wa.z * x.z + wa.w * x.w;
+      zi += wb.x * x.x + wb.y * x.y + wb.z * x.z + wb.w * x.w;
+    }
+    zr += __shfl_xor(zr, 16);
+    zr += __shfl_xor(zr, 32);
+    zi += __shfl_xor(zi, 16);
+    zi += __shfl_xor(zi, 32);
+    if (s == si && g == 0) {
+      zb[j] = zr;
+      zb[16 + j] = zi;
+    }
+  }
+  __syncthreads();
+  T ps[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) ps[k] = pb[k * 64 + lane];
   const int rest = P.K - 1 - i;
   bool ok[4];
   T Z = 0;
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    ok[s] = allowed(ca, cb, s, rest, P.na, P.nb);
-    if (ok[s]) Z += ps[s];
+  for (int k = 0; k < 4; ++k) {
+    ok[k] = allowed(ca, cb, k, rest, P.na, P.nb);
+    if (ok[k]) Z += ps[k];
   }
   const T psi_ = si == 0 ? ps[0] : si == 1 ? ps[1] : si == 2 ? ps[2] : ps[3];
   const T inv_p = T(1) / psi_, inv_z = T(1) / Z;
   // phase term (complex parameters): alpha, beta of this row
   T al = T(0), be = T(0);
   if (CPLX) {
-    T zr = T(0), zi = T(0);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s != si) continue;
-#pragma unroll
-      for (int t = 0; t < TPC; ++t) {
-        const int u0 = 16 * t + 4 * g;
-        const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
-        const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
-        const V x = acc[s * TPC + t];
-        zr += wa.x * x.x + wa.y * x.y + wa.z * x.z + wa.w * x.w;
-        zi += wb.x * x.x + wb.y * x.y + wb.z * x.z + wb.w * x.w;
-      }
-    }
-    zr += __shfl_xor(zr, 16);
-    zr += __shfl_xor(zr, 32);
-    zi += __shfl_xor(zi, 16);
-    zi += __shfl_xor(zi, 32);
+    T zr = zb[j], zi = zb[16 + j];
     zr += P.c[i];
     zi += P.c2[i];
     const T z2 = zr * zr + zi * zi;
@@ -175,69 +190,69 @@ __global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i, const u
       al = -gp * zi / z2;
       be = gp * zr / z2;
     }
-    if (g == 0) {
+    if (s == 0 && g == 0) {
       P.ab[2 * row] = al;
       P.ab[2 * row + 1] = be;
     }
   }
-  // d eta and dcand (in place of acc)
-  const T* dci = dcarry + (size_t(i) * Rpad + row) * CH + 4 * g;
-  V de[TPC];
+  // d eta: unit tiles s, s + 4, .., each over the four candidates
+  for (int t = s; t < TPC; t += 4) {
+    V de = V{0, 0, 0, 0};
 #pragma unroll
-  for (int t = 0; t < TPC; ++t) de[t] = V{0, 0, 0, 0};
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-#pragma unroll
-    for (int t = 0; t < TPC; ++t) {
-      const int u0 = 16 * t + 4 * g;
-      const V ee = *reinterpret_cast<const V*>(ei + u0);
-      const V x = acc[s * TPC + t];
-      V d = V{0, 0, 0, 0};
-      if (ok[s]) {
-        const T f = (s == si ? inv_p : T(0)) - inv_z;
-        d = gg * f * ee * x;
-        de[t] -= T(0.5) * gg * inv_z * x * x;
-      }
-      if (s == si) {
-        d += *reinterpret_cast<const V*>(dci + 16 * t);
-        de[t] += T(0.5) * gg * inv_p * x * x;
-        if (CPLX) {
-          const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
-          const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
-          d += al * wa + be * wb;
-        }
-      }
-      acc[s * TPC + t] = d;
-      *reinterpret_cast<V*>(Dc + size_t(row) * 4 * CH + s * CH + u0) = d;
+    for (int k = 0; k < 4; ++k) {
+      const V x = xb[(k * TPC + t) * 64 + lane];
+      if (ok[k]) de -= T(0.5) * gg * inv_z * x * x;
+      if (k == si) de += T(0.5) * gg * inv_p * x * x;
     }
+    *reinterpret_cast<V*>(Eeta + size_t(row) * CH + 16 * t + 4 * g) = de;
   }
+  // dcand of candidate s (in place of acc, and of its states in LDS)
+  const bool oks = allowed(ca, cb, s, rest, P.na, P.nb);
+  const T* dci = dcarry + (size_t(i) * Rpad + row) * CH + 4 * g;
 #pragma unroll
-  for (int t = 0; t < TPC; ++t)
-    *reinterpret_cast<V*>(Eeta + size_t(row) * CH + 16 * t + 4 * g) = de[t];
-  // parents: dcarry_j[row][kk] += sum_{s,u} dcand[row][s,u] M_ij^s[u][kk]
-  // A = dcand (rows x (s,u)), own registers; B = BT-packed M, k-step (s,t,v)
-  for (int e = e0; e < e1; ++e) {
-    const int pj = P.pidx[e];
-    const T* Be = P.BT + P.btoff[i] + size_t(e - e0) * (4 * KS * TPC * 64) + lane;
-#pragma unroll
-    for (int ot = 0; ot < TPC; ++ot) {
-      V o = V{0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int t = 0; t < TPC; ++t)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int q = (s * TPC + t) * 4 + v;
-            o = mfma(acc[s * TPC + t][v], Be[(q * TPC + ot) * 64], o);
-          }
-      // o: rows out_row(g, v) of the tile, column kk = 16 ot + j
-      T* dcp = dcarry + size_t(pj) * Rpad * CH;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t r = row0 + out_row<T>(g, v);
-        dcp[size_t(r) * CH + 16 * ot + j] += o[v];
+  for (int t = 0; t < TPC; ++t) {
+    const int u0 = 16 * t + 4 * g;
+    const V ee = *reinterpret_cast<const V*>(ei + u0);
+    const V x = acc[t];
+    V d = V{0, 0, 0, 0};
+    if (oks) {
+      const T f = (s == si ? inv_p : T(0)) - inv_z;
+      d = gg * f * ee * x;
+    }
+    if (s == si) {
+      d += *reinterpret_cast<const V*>(dci + 16 * t);
+      if (CPLX) {
+        const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
+        const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
+        d += al * wa + be * wb;
       }
+    }
+    acc[t] = d;
+    *reinterpret_cast<V*>(Dc + size_t(row) * 4 * CH + s * CH + u0) = d;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TPC; ++t) xb[(s * TPC + t) * 64 + lane] = acc[t];
+  __syncthreads();
+  // parents: dcarry_j[row][kk] += sum_{s,u} dcand[row][s,u] M_ij^s[u][kk]
+  // A = dcand (rows x (s,u)), the lane's own quads; B = BT-packed M, k-step (s,t,v)
+  for (int u = s; u < (e1 - e0) * TPC; u += 4) {
+    const int e = e0 + u / TPC, ot = u % TPC;
+    const int pj = P.pidx[e];
+    const T* Be = P.BT + P.btoff[i] + size_t(e - e0) * (4 * KS * TPC * 64) + size_t(ot) * 64 + lane;
+    V o = V{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const V d = xb[k * 64 + lane];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o = mfma(d[v], Be[size_t(4 * k + v) * TPC * 64], o);
+    }
+    // o: rows out_row(g, v) of the tile, column kk = 16 ot + j
+    T* dcp = dcarry + size_t(pj) * Rpad * CH;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t r = row0 + out_row<T>(g, v);
+      dcp[size_t(r) * CH + 16 * ot + j] += o[v];
     }
   }
 }
@@ -287,27 +302,35 @@ __global__ __launch_bounds__(256) void k_bwd_dm(AdjParams<T> P, int i, int64_t R
   }
 }
 
-// dv and deta: column sums over the rows of each split (one thread per unit)
+// dv and deta: column sums over the rows of each split.  One workgroup per 64
+// columns and split; its 16 wavefronts take every 16th row each, so that all the
+// loads of a column are in flight at once (one thread per column walked its rows
+// one load after the other: 67 us per site at K = 50, chi = 32, 4096 rows), and
+// their FP64 sums are added in order.
 template <typename T, int CH>
-__global__ void k_bwd_colsum(AdjParams<T> P, int i, int64_t Rpad, int rows_per_split, int nsplit,
-                             const T* Dc, const T* Eeta, double* gpart, int64_t n_params) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int ncol = 5 * CH;   // 4 CH of v, CH of eta
-  if (t >= int64_t(ncol) * nsplit) return;
-  const int split = int(t / ncol);
-  const int col = int(t % ncol);
+__global__ __launch_bounds__(1024) void k_bwd_colsum(AdjParams<T> P, int i, int64_t Rpad, int rows_per_split,
+                                                     const T* Dc, const T* Eeta, double* gpart, int64_t n_params) {
+  __shared__ double part[16][64];
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int col = blockIdx.x * 64 + lane;   // 4 CH of v, CH of eta
+  const int split = blockIdx.y;
   const int64_t r0 = int64_t(split) * rows_per_split;
   const int64_t r1 = r0 + rows_per_split < Rpad ? r0 + rows_per_split : Rpad;
   double acc = 0.0;
-  if (col < 4 * CH) {
-    for (int64_t r = r0; r < r1; ++r) acc += double(Dc[size_t(r) * 4 * CH + col]);
-    const int s = col / CH, u = col % CH;
-    if (u < P.chi) gpart[size_t(split) * n_params + P.offV[i] + s * P.chi + u] = acc;
-  } else {
-    const int u = col - 4 * CH;
-    for (int64_t r = r0; r < r1; ++r) acc += double(Eeta[size_t(r) * CH + u]);
-    if (u < P.chi) gpart[size_t(split) * n_params + P.offEta[i] + u] = acc;
+  if (col < 5 * CH) {
+    const T* x = col < 4 * CH ? Dc + col : Eeta + (col - 4 * CH);
+    const int ld = col < 4 * CH ? 4 * CH : CH;
+#pragma unroll 4
+    for (int64_t r = r0 + wv; r < r1; r += 16) acc += double(x[size_t(r) * ld]);
   }
+  part[wv][lane] = acc;
+  __syncthreads();
+  if (wv != 0 || col >= 5 * CH) return;
+#pragma unroll
+  for (int w = 1; w < 16; ++w) acc += part[w][lane];
+  const int s = col / CH, u = col % CH;   // s = 4: eta
+  if (u < P.chi)
+    gpart[size_t(split) * n_params + (s < 4 ? P.offV[i] + s * P.chi : P.offEta[i]) + u] = acc;
 }
 
 // complex parameters: dw[u] = sum_rows alpha x[u], dw2[u] = sum beta x[u],
@@ -474,10 +497,10 @@ hipError_t run_site(const AdjParams<T>& P, int i, const uint64_t* m, int64_t R, 
                     int nsplit, double* gpart, int64_t n_params, hipStream_t st) {
   const int64_t tiles = Rpad / 16;
   if (P.cotp)
-    hipLaunchKernelGGL((k_bwd_site<T, CH, true>), dim3(grid_for(tiles, 4)), dim3(256), 0, st, P, i, m, R, Rpad,
+    hipLaunchKernelGGL((k_bwd_site<T, CH, true>), dim3(unsigned(tiles)), dim3(256), 0, st, P, i, m, R, Rpad,
                        cot, Hbuf, dcarry, Dc, Eeta);
   else
-    hipLaunchKernelGGL((k_bwd_site<T, CH, false>), dim3(grid_for(tiles, 4)), dim3(256), 0, st, P, i, m, R, Rpad,
+    hipLaunchKernelGGL((k_bwd_site<T, CH, false>), dim3(unsigned(tiles)), dim3(256), 0, st, P, i, m, R, Rpad,
                        cot, Hbuf, dcarry, Dc, Eeta);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -493,8 +516,8 @@ hipError_t run_site(const AdjParams<T>& P, int i, const uint64_t* m, int64_t R, 
                        rows_per_split, nsplit, Hbuf, Dc, gpart, n_params);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_bwd_colsum<T, CH>), dim3(grid_for(int64_t(5 * CH) * nsplit, 256)), dim3(256), 0, st,
-                     P, i, Rpad, rows_per_split, nsplit, Dc, Eeta, gpart, n_params);
+  hipLaunchKernelGGL((k_bwd_colsum<T, CH>), dim3((5 * CH + 63) / 64, nsplit), dim3(1024), 0, st, P, i, Rpad,
+                     rows_per_split, Dc, Eeta, gpart, n_params);
   return hipGetLastError();
 }
 
