@@ -310,13 +310,15 @@ __global__ __launch_bounds__(256) void k_ising_E(CorrParams C, const uint64_t* s
 }
 
 // log|f(m)| and sign f(m) of the rows: a wavefront takes kIsingRowsPerWave
-// consecutive rows, kIsingBatch at a time, with hidden units across lanes; a
-// batch's rows are decoded with scalar loads and their table reads issued
-// together, so the wavefront keeps several rows' loads in flight.  Tables E and
-// S in precision TT (FP32 for the FP32/BF16 paths: they then round like the
+// consecutive rows, four at a time, 16 lanes each over the hidden units.  Tables E
+// and S in precision TT (FP32 for the FP32/BF16 paths: they then round like the
 // FP32 cos that follows), theta accumulated in FP64, cos and log in precision
-// T, the sum of logs in FP64.
-constexpr int kIsingRowsPerWave = 16, kIsingBatch = 2;
+// T, the sum of logs in FP64.  It is bound by the VALU (theta, cos and log per row
+// and unit), so the lanes should be full: 64 lanes over N_h = 80 units left 37%
+// of them idle and summed each row over the whole wavefront (7.6 M rows of 1024
+// samples at K = 20, N_h = 80, correlator and reduction: FP32 4.17 -> 1.96 ms, FP64
+// 7.1 -> 4.0 ms).
+constexpr int kIsingRowsPerWave = 16;
 
 // lowest set bit of the 128-bit (lo, hi), cleared; -1 if none
 __device__ inline int pop_lowest(uint64_t& lo, uint64_t& hi) {
@@ -339,63 +341,53 @@ __global__ __launch_bounds__(256) void k_ising_rows(CorrParams C, const TT* S, c
                                                     const double* theta, const TT* E, int64_t R, double* lf,
                                                     int8_t* sf) {
   const int64_t wave = (int64_t(blockIdx.x) * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x)) >> 6;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, grp = lane >> 4, kk = lane & 15;
   const int64_t r0 = wave * kIsingRowsPerWave;
   if (r0 >= R) return;
   const int64_t r1 = r0 + kIsingRowsPerWave < R ? r0 + kIsingRowsPerWave : R;
   const int nv = 2 * C.K, nh = C.nh;
-  for (int64_t rb = r0; rb < r1; rb += kIsingBatch) {
-    // per row four fixed slots: the two created orbitals (delta +1), then the
-    // two annihilated ones (delta -1); an absent slot has delta 0 and points
-    // at orbital 0, so every row issues the same loads and adds exact zeros
-    int ch[kIsingBatch][4];
-    double dl[kIsingBatch][4];
-    const TT* Eo[kIsingBatch];
-    const double* To[kIsingBatch];
+  for (int64_t rb = r0; rb < r1; rb += 4) {
+    // four fixed slots: the two created orbitals (delta +1), then the two
+    // annihilated ones (delta -1); an absent slot has delta 0 and points at
+    // orbital 0, so every row issues the same loads and adds exact zeros
+    const bool live = rb + grp < r1;
+    const int64_t r = live ? rb + grp : r1 - 1;
+    const int64_t o = owner[r];
+    const uint64_t mlo = m[2 * r], mhi = m[2 * r + 1];
+    const uint64_t nlo = samples[2 * o], nhi = samples[2 * o + 1];
+    uint64_t clo = mlo & ~nlo, chi = mhi & ~nhi, alo = nlo & ~mlo, ahi = nhi & ~mhi;
+    int ch[4];
+    double dl[4];
 #pragma unroll
-    for (int j = 0; j < kIsingBatch; ++j) {
-      const int64_t r = rb + j < r1 ? rb + j : r1 - 1;
-      const int64_t o = owner[r];
-      const uint64_t mlo = m[2 * r], mhi = m[2 * r + 1];
-      const uint64_t nlo = samples[2 * o], nhi = samples[2 * o + 1];
-      uint64_t clo = mlo & ~nlo, chi = mhi & ~nhi, alo = nlo & ~mlo, ahi = nhi & ~mhi;
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int P = a < 2 ? pop_lowest(clo, chi) : pop_lowest(alo, ahi);
-        ch[j][a] = P < 0 ? 0 : P;
-        dl[j][a] = P < 0 ? 0.0 : (a < 2 ? 1.0 : -1.0);
-      }
-      Eo[j] = E + size_t(o) * nv * nh;
-      To[j] = theta + size_t(o) * nh;
+    for (int a = 0; a < 4; ++a) {
+      const int P = a < 2 ? pop_lowest(clo, chi) : pop_lowest(alo, ahi);
+      ch[a] = P < 0 ? 0 : P;
+      dl[a] = P < 0 ? 0.0 : (a < 2 ? 1.0 : -1.0);
     }
-    double acc[kIsingBatch];
-    int neg[kIsingBatch];
+    const TT* Eo = E + size_t(o) * nv * nh;
+    const double* To = theta + size_t(o) * nh;
+    double acc = 0.0;
+    int neg = 0;
+    for (int k = kk; k < nh; k += 16) {
+      double th = To[k];
 #pragma unroll
-    for (int j = 0; j < kIsingBatch; ++j) { acc[j] = 0.0; neg[j] = 0; }
-    for (int k = lane; k < nh; k += 64) {
+      for (int a = 0; a < 4; ++a) th += (dl[a] * dl[a]) * double(Eo[size_t(ch[a]) * nh + k]);
 #pragma unroll
-      for (int j = 0; j < kIsingBatch; ++j) {
-        double th = To[j][k];
+      for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int a = 0; a < 4; ++a) th += (dl[j][a] * dl[j][a]) * double(Eo[j][size_t(ch[j][a]) * nh + k]);
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b = a + 1; b < 4; ++b)
-            th += (dl[j][a] * dl[j][b]) * double(S[(size_t(ch[j][a]) * nv + ch[j][b]) * nh + k]);
-        const T cv = tcos(T(th));
-        acc[j] += double(tlog(tabs(cv)));
-        neg[j] ^= cv < T(0) ? 1 : 0;
-      }
+        for (int b = a + 1; b < 4; ++b) th += (dl[a] * dl[b]) * double(S[(size_t(ch[a]) * nv + ch[b]) * nh + k]);
+      const T cv = tcos(T(th));
+      acc += double(tlog(tabs(cv)));
+      neg ^= cv < T(0) ? 1 : 0;
     }
 #pragma unroll
-    for (int j = 0; j < kIsingBatch; ++j) {
-      const double sum = wave_sum(acc[j]);
-      const int odd = __popcll(__ballot(neg[j])) & 1;
-      if (lane == 0 && rb + j < r1) {
-        lf[rb + j] = sum;
-        sf[rb + j] = int8_t(odd ? -1 : 1);
-      }
+    for (int x = 8; x > 0; x >>= 1) {
+      acc += __shfl_xor(acc, x);
+      neg ^= __shfl_xor(neg, x);
+    }
+    if (kk == 0 && live) {
+      lf[r] = acc;
+      sf[r] = int8_t(neg ? -1 : 1);
     }
   }
 }
