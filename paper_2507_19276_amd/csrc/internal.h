@@ -55,7 +55,7 @@ struct PsiParams {
   const int* wsl;                // [K] ring slot receiving site i's carried state
   const uint64_t* live;          // [K+1] bit s: the state of site s < i is read by a site >= i (live[K] = 0:
                                  // rows with no change below K, the samples' own rows among them, resume at K)
-  const T* A;                    // [edges + 1][CH/4][CH/4][64] k-permuted MFMA A operands, see runtime.cpp
+  const T* A;                    // [edges + 1][CH/4][CH/4][64] k-permuted MFMA A operands, see bind.hip
   const T* v;                    // [K][4][chip]
   const T* eta;                  // [K][chip]
   const T* w;                    // [K][chip]
@@ -67,7 +67,7 @@ struct PsiParams {
   // BDG-TensorRNN term on MFMA (chip <= 32, chi' <= 8): the operand stream
   // (per tensor site: projections [parent][k-step][lane], core
   // [k-step][tile 0..1][lane], output factor [state][tile][v][lane], built in
-  // runtime.cpp) and per site {chi' (0: none), offsets of the three parts}
+  // runtime.cpp build_ta) and per site {chi' (0: none), offsets of the three parts}
   const T* TA = nullptr;
   const int* tsite = nullptr;    // [K][4]
 };
@@ -161,7 +161,7 @@ struct B16Params {
   const int* slot;               // [edges] ring slot read by each edge (W: a parentless site's zero edge)
   const int* wsl;                // [K]
   const uint64_t* live;          // [K+1]
-  const uint16_t* A;             // BF16 A stream, per forward edge + one zero edge (runtime.cpp)
+  const uint16_t* A;             // BF16 A stream, per forward edge + one zero edge (bind.hip)
   const uint16_t* Alo = nullptr; // the same stream's lo parts (split form)
   const float* v;                // [K][4][chip]
   const float* eta;              // [K][chip]
@@ -207,6 +207,37 @@ struct Rows {
   uint32_t* sec;     // [R]   c2 | state at c1 << 8 | c3 << 16 | state at c2 << 24 (next changed sites,
                      //       K when absent); may be null
 };
+
+// ---- parameter layouts (bind.hip) ---------------------------------------
+// the packed (realified) parameters on the device and the graph
+struct PackParams {
+  int K, chi, chip, n_fwd;       // n_fwd forward edges; one more zero edge is written past them
+  bool fold;                     // sqrt(eta) folded in
+  const int* fptr;               // [K+1] forward edges (a parentless site has one zero edge)
+  const int* pptr;               // [K+1] graph edges
+  const int* pidx;
+  const double* prm;
+  const int64_t* offM;           // [edges]
+  const int64_t* offV;           // [K]
+  const int64_t* offEta;         // [K]; w and c follow eta
+  const int64_t* offW2;          // [K] complex parameters (c2 follows w2), else null
+};
+// AF, BT, w2, c2 nullable
+hipError_t launch_pack_f64(const PackParams& P, double* A, double* AF, double* BT, double* v, double* eta, double* w,
+                           double* c, double* w2, double* c2, hipStream_t st);
+hipError_t launch_pack_f32(const PackParams& P, float* A, float* AF, float* BT, float* v, float* eta, float* w,
+                           float* c, float* w2, float* c2, hipStream_t st);
+int64_t bf16_edge_values(int chip);
+hipError_t launch_pack_bf16(const PackParams& P, uint16_t* A, uint16_t* Alo, hipStream_t st);
+// W [nh][nv] -> Wt [nv][nh]; W2 (nullable) -> S, S32 (CorrParams)
+hipError_t launch_pack_corr(int nv, int nh, const double* W, double* Wt, const double* W2, double* S, float* S32,
+                            hipStream_t st);
+// flags (device int[3]): [0] lowest i chi + u with eta < 0 or NaN (2^31 - 1: none),
+// [1] an eta is zero, [2] an entry of prm [n] is not finite
+hipError_t launch_check_params(int K, int chi, const int64_t* offEta, const double* prm, int64_t n, int* flags,
+                               hipStream_t st);
+// the realified vector r of a packed complex vector p
+hipError_t launch_realify(const CxMap& M, int K, const double* p, double* r, hipStream_t st);
 
 // ---- launchers (enumerate.hip) ----------------------------------------
 hipError_t launch_validate(const uint64_t* samples, int64_t N, int K, int na, int nb, int* bad,

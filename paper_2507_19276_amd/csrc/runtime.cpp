@@ -380,6 +380,9 @@ struct nqs_ansatz {
   int64_t cx_offB = 0;
   // the triangular-normaliser forward of FP64 rows (psi_tri.h): whether the
   // graph takes it (create), whether the bound parameters do (bind), its operands
+  int n_fwd = 0;            // forward edges
+  int* d_flags = nullptr;   // bind: checks of the bound vector
+  double* d_real = nullptr; // complex parameters: the realified vector
   bool tri_graph = false, tri = false;
   int dmax = 1;
   int* d_qoff = nullptr;
@@ -397,7 +400,8 @@ struct nqs_ansatz {
                     (void*)bfAlo,
                     (void*)d_cb, (void*)d_cW, (void*)d_cW1t, (void*)d_cS, (void*)d_cS32, (void*)d_tn_edge,
                     (void*)d_tn_site, (void*)tn64, (void*)tn32, (void*)d_offM, (void*)d_offV,
-                    (void*)d_offEta, (void*)d_cx, (void*)d_tsite, (void*)d_qoff, (void*)triQ, (void*)tri_rho, (void*)tri_G})
+                    (void*)d_offEta, (void*)d_cx, (void*)d_tsite, (void*)d_flags, (void*)d_real, (void*)d_qoff, (void*)triQ,
+                    (void*)tri_rho, (void*)tri_G})
       if (p) (void)hipFree(p);
   }
   template <typename T>
@@ -469,81 +473,20 @@ nqs_status upload(T** dst, const std::vector<T>& src) {
   return NQS_OK;
 }
 
-// Forward MFMA A operands: W_i^T tiles over the forward edges (the parents of
-// each site in order; a parentless site gets one zero edge), then one more
-// zero edge so that the kernel's one-edge-ahead fetch stays in bounds.  Per
-// edge [k-step q][output tile ot][lane]: lane l holds W^T[o][k] = M_ij^s[u][k]
-// with s = o / chip, u = o % chip (zero outside chi), tile row m = l%16 and
-// parent unit k = 16 (q/4) + 4 (l/16) + q%4.  The 16x16x4 f32 MFMA returns
-// row m = 4 g + v of the tile in register v of lane group g = lane/16; the f64
-// MFMA returns row m = g + 4 v.  Tile row m therefore carries unit
-// o = 16 ot + m for f32 and o = 16 ot + 4 (m%4) + m/4 for f64, so that in both
-// cases lane group g ends up with units 16 ot + 4 g + v, and k-step q of lane
-// group g reads the parent unit that the same lane produced in register q%4 of
-// output tile q/4.
-//
-// fold = true: every operand carries sigma = sqrt(eta) (requires eta > 0):
-// A' = sigma_i[u] M[u][k] / sigma_j[k], v' = sigma_i v, w' = w / sigma_i, so the
-// forward kernel carries sigma h and P^s = sum x'^2.  The adjoint operands are
-// built only for the unfolded layout.
+// The tensor term's MFMA operands (PsiParams::TA), from a host copy of the
+// packed parameters; with fold every operand carries sqrt(eta) as the edges' do.
 template <typename T>
-nqs_status build_layout(nqs_ansatz* a, const std::vector<double>& prm, PsiLayout<T>& L, bool fold) {
+nqs_status build_ta(nqs_ansatz* a, const std::vector<double>& prm, PsiLayout<T>& L, bool fold) {
   const int K = a->K, chi = a->chi, CH = a->chip;
-  const int KS = CH / 4, NT = CH / 4;
-  const size_t ES = size_t(KS) * NT * 64;
   std::vector<double> sig(size_t(K) * chi, 1.0);
   if (fold)
     for (int i = 0; i < K; ++i)
       for (int u = 0; u < chi; ++u) sig[size_t(i) * chi + u] = std::sqrt(prm[a->offEta[i] + u]);
-  std::vector<T> A;
-  for (int i = 0; i < K; ++i) {
-    if (a->pptr[i + 1] == a->pptr[i]) A.resize(A.size() + ES, T(0));   // zero edge
-    for (int e = a->pptr[i]; e < a->pptr[i + 1]; ++e) {
-      const double* M = prm.data() + a->offM[e];
-      const double* sj = sig.data() + size_t(a->pidx[e]) * chi;
-      const double* si = sig.data() + size_t(i) * chi;
-      for (int q = 0; q < KS; ++q)
-        for (int ot = 0; ot < NT; ++ot)
-          for (int l = 0; l < 64; ++l) {
-            const int mrow = l & 15;
-            const int o = ot * 16 + (sizeof(T) == 8 ? 4 * (mrow & 3) + (mrow >> 2) : mrow);
-            const int k = 16 * (q >> 2) + 4 * (l >> 4) + (q & 3);
-            const int s = o / CH, u = o % CH;
-            double val = 0.0;
-            if (u < chi && k < chi) val = si[u] * M[(size_t(s) * chi + u) * chi + k] / sj[k];
-            A.push_back(T(val));
-          }
-    }
-  }
-  A.resize(A.size() + ES, T(0));   // fetch-ahead edge
-  std::vector<T> v(size_t(K) * 4 * CH, T(0)), eta(size_t(K) * CH, T(0)), w(size_t(K) * CH, T(0)), c(K);
-  for (int i = 0; i < K; ++i) {
-    const double* si = sig.data() + size_t(i) * chi;
-    for (int s = 0; s < 4; ++s)
-      for (int u = 0; u < chi; ++u)
-        v[(size_t(i) * 4 + s) * CH + u] = T(si[u] * prm[a->offV[i] + s * chi + u]);
-    for (int u = 0; u < chi; ++u) {
-      eta[size_t(i) * CH + u] = T(prm[a->offEta[i] + u]);
-      w[size_t(i) * CH + u] = T(prm[a->offW[i] + u] / si[u]);
-    }
-    c[i] = T(prm[a->offC[i]]);
-  }
-  std::vector<T> w2, c2;
-  if (a->cplx) {
-    w2.assign(size_t(K) * CH, T(0));
-    c2.resize(K);
-    for (int i = 0; i < K; ++i) {
-      const double* si = sig.data() + size_t(i) * chi;
-      for (int u = 0; u < chi; ++u) w2[size_t(i) * CH + u] = T(prm[a->offW2x[i] + u] / si[u]);
-      c2[i] = T(prm[a->offC2x[i]]);
-    }
-  }
   // the tensor term's MFMA operands (see PsiParams::TA); A row m of a tile
   // carries logical row o(m) so that lane group g holds rows 4g + v in its
   // output registers v (f64 MFMA rows g + 4v)
-  std::vector<T> TA;
-  if (a->tn_mfma) {
-    TA.assign(a->ta_size, T(0));
+  std::vector<T> TA(a->ta_size, T(0));
+  {
     auto orow = [](int m) { return sizeof(T) == 8 ? 4 * (m & 3) + (m >> 2) : m; };
     const int KSq = CH / 4, TPCq = CH / 16;
     for (int i = 0; i < K; ++i) {
@@ -597,139 +540,49 @@ nqs_status build_layout(nqs_ansatz* a, const std::vector<double>& prm, PsiLayout
             }
     }
   }
-  auto upload_cx = [&]() -> nqs_status {
-    nqs_status st;
-    if (a->tn_mfma && (st = upload(&L.TA, TA)) != NQS_OK) return st;
-    if (!a->cplx) return NQS_OK;
-    if ((st = upload(&L.w2, w2)) != NQS_OK) return st;
-    return upload(&L.c2, c2);
-  };
-  if (fold) {
-    L.free_all();
-    L.folded = true;
-    nqs_status st;
-    if ((st = upload(&L.A, A)) != NQS_OK) return st;
-    if ((st = upload(&L.v, v)) != NQS_OK) return st;
-    if ((st = upload(&L.eta, eta)) != NQS_OK) return st;
-    if ((st = upload(&L.w, w)) != NQS_OK) return st;
-    if ((st = upload(&L.c, c)) != NQS_OK) return st;
-    return upload_cx();
-  }
-  // adjoint operands.  AF: like A but k-step q = 4t + v pairs lane group k'
-  // with parent unit 16t + 4k' + v.  BT: k-step q = (s*TPC + t)*4 + v over the
-  // candidate units (s, 16t + 4k' + v) and output tiles ot over the parent
-  // unit kk = 16 ot + n: B[k'][n] = M_ij^s[u][kk].
-  const int TPC = CH / 16;
-  std::vector<int64_t> afoff(K), btoff(K);
-  std::vector<T> AF, BT;
-  for (int i = 0; i < K; ++i) {
-    afoff[i] = int64_t(AF.size());
-    btoff[i] = int64_t(BT.size());
-    for (int e = a->pptr[i]; e < a->pptr[i + 1]; ++e) {
-      const double* M = prm.data() + a->offM[e];
-      for (int q = 0; q < KS; ++q)
-        for (int ot = 0; ot < NT; ++ot)
-          for (int l = 0; l < 64; ++l) {
-            const int mrow = l & 15;
-            const int o = ot * 16 + (sizeof(T) == 8 ? 4 * (mrow & 3) + (mrow >> 2) : mrow);
-            const int k = 16 * (q >> 2) + 4 * (l >> 4) + (q & 3);
-            const int s = o / CH, u = o % CH;
-            double val = 0.0;
-            if (u < chi && k < chi) val = M[(size_t(s) * chi + u) * chi + k];
-            AF.push_back(T(val));
-          }
-      for (int q = 0; q < 4 * KS; ++q)
-        for (int ot = 0; ot < TPC; ++ot)
-          for (int l = 0; l < 64; ++l) {
-            const int v = q & 3, t = (q >> 2) % TPC, s = (q >> 2) / TPC;
-            const int u = 16 * t + 4 * (l >> 4) + v;
-            const int kk = 16 * ot + (l & 15);
-            double val = 0.0;
-            if (u < chi && kk < chi) val = M[(size_t(s) * chi + u) * chi + kk];
-            BT.push_back(T(val));
-          }
-    }
-  }
-  L.free_all();
-  nqs_status st;
-  if ((st = upload(&L.AF, AF)) != NQS_OK) return st;
-  if ((st = upload(&L.afoff, afoff)) != NQS_OK) return st;
-  if ((st = upload(&L.BT, BT)) != NQS_OK) return st;
-  if ((st = upload(&L.btoff, btoff)) != NQS_OK) return st;
-  if ((st = upload(&L.A, A)) != NQS_OK) return st;
-  if ((st = upload(&L.v, v)) != NQS_OK) return st;
-  if ((st = upload(&L.eta, eta)) != NQS_OK) return st;
-  if ((st = upload(&L.w, w)) != NQS_OK) return st;
-  if ((st = upload(&L.c, c)) != NQS_OK) return st;
-  return upload_cx();
+  if (L.TA) { (void)hipFree(L.TA); L.TA = nullptr; }
+  return upload(&L.TA, TA);
 }
 
-// round-to-nearest-even FP32 -> BF16 bit pattern (finite inputs)
-uint16_t to_bf16(float f) {
-  uint32_t b;
-  std::memcpy(&b, &f, 4);
-  b += 0x7FFFu + ((b >> 16) & 1u);
-  return uint16_t(b >> 16);
+template <typename T>
+nqs_status ensure(T** p, int64_t n) {
+  if (!*p) HIPCHK(hipMalloc((void**)p, size_t(std::max<int64_t>(n, 1)) * sizeof(T)));
+  return NQS_OK;
 }
 
-// BF16 forward A stream (psi_bf16.hip): per forward edge (a parentless site
-// has one zero edge; one more zero edge at the end), TPC/2 pair k-steps of
-// [output tile ot][lane][8] then, when TPC = chip/16 is odd, one k-step of
-// [ot][lane][4].  Lane l holds tile row m = l%16 (output unit o = 16 ot + m,
-// the FP32 output layout) and, for lane group g = l/16, the parent units
-// k = 16 (2q + e/4) + 4 g + e%4 (pair step q, element e) or 16 (TPC-1) + 4 g + e
-// (odd step): each lane's own quads of the parent state.  With fold the
-// operands carry sigma = sqrt(eta) as in build_layout.  Round to nearest even.
-// A second stream of the same layout holds the lo parts of the split form:
-// bf16(x - bf16(x)) with the difference taken in FP64.
-nqs_status build_bf16(nqs_ansatz* a, const std::vector<double>& prm, bool fold) {
-  const int K = a->K, chi = a->chi, CH = a->chip, NT = CH / 4, TPC = CH / 16, NP = TPC / 2;
-  const size_t EQ = size_t(NP) * NT * 64 * 8 + size_t(TPC & 1) * NT * 64 * 4;   // bf16 values per edge
-  std::vector<double> sig(size_t(K) * chi, 1.0);
-  if (fold)
-    for (int i = 0; i < K; ++i)
-      for (int u = 0; u < chi; ++u) sig[size_t(i) * chi + u] = std::sqrt(prm[a->offEta[i] + u]);
-  std::vector<uint16_t> A, Alo;
-  auto value = [&](int e, int i, int o, int k) {
-    const int s = o / CH, u = o % CH;
-    if (u >= chi || k >= chi) {
-      Alo.push_back(0);
-      return uint16_t(0);
-    }
-    const double* M = prm.data() + a->offM[e];
-    const double v = sig[size_t(i) * chi + u] * M[(size_t(s) * chi + u) * chi + k] /
-                     sig[size_t(a->pidx[e]) * chi + k];
-    const uint16_t hi = to_bf16(float(v));
-    uint32_t bits = uint32_t(hi) << 16;
-    float fhi;
-    std::memcpy(&fhi, &bits, 4);
-    Alo.push_back(to_bf16(float(v - double(fhi))));
-    return hi;
-  };
-  for (int i = 0; i < K; ++i) {
-    if (a->pptr[i + 1] == a->pptr[i]) {   // zero edge
-      A.resize(A.size() + EQ, 0);
-      Alo.resize(Alo.size() + EQ, 0);
-    }
-    for (int e = a->pptr[i]; e < a->pptr[i + 1]; ++e) {
-      for (int q = 0; q < NP; ++q)
-        for (int ot = 0; ot < NT; ++ot)
-          for (int l = 0; l < 64; ++l)
-            for (int el = 0; el < 8; ++el)
-              A.push_back(value(e, i, 16 * ot + (l & 15), 16 * (2 * q + el / 4) + 4 * (l >> 4) + el % 4));
-      if (TPC & 1)
-        for (int ot = 0; ot < NT; ++ot)
-          for (int l = 0; l < 64; ++l)
-            for (int el = 0; el < 4; ++el)
-              A.push_back(value(e, i, 16 * ot + (l & 15), 16 * (TPC - 1) + 4 * (l >> 4) + el));
+// The layouts of one precision (bind.hip), folded (every operand carries
+// sigma = sqrt(eta), which requires eta > 0: A' = sigma_i[u] M[u][k] / sigma_j[k],
+// v' = sigma_i v, w' = w / sigma_i, so the forward kernel carries sigma h and
+// P^s = sum x'^2) or not (with the adjoint's operands).  The buffers are kept from
+// one bind to the next.
+template <typename T>
+nqs_status pack_layout(nqs_ansatz* a, PackParams P, PsiLayout<T>& L, bool fold, hipStream_t st) {
+  const int64_t ES = int64_t(a->chip / 4) * (a->chip / 4) * 64, ne = a->pptr[a->K], K = a->K, CH = a->chip;
+  nqs_status s;
+  L.folded = fold;
+  if ((s = ensure(&L.A, (P.n_fwd + 1) * ES)) != NQS_OK) return s;
+  if ((s = ensure(&L.v, K * 4 * CH)) != NQS_OK) return s;
+  if ((s = ensure(&L.eta, K * CH)) != NQS_OK) return s;
+  if ((s = ensure(&L.w, K * CH)) != NQS_OK) return s;
+  if ((s = ensure(&L.c, K)) != NQS_OK) return s;
+  if (a->cplx && (s = ensure(&L.w2, K * CH)) != NQS_OK) return s;
+  if (a->cplx && (s = ensure(&L.c2, K)) != NQS_OK) return s;
+  if (!fold) {
+    if ((s = ensure(&L.AF, ne * ES)) != NQS_OK) return s;
+    if ((s = ensure(&L.BT, ne * ES)) != NQS_OK) return s;
+    if (!L.afoff) {
+      std::vector<int64_t> off(K);
+      for (int i = 0; i < a->K; ++i) off[i] = a->pptr[i] * ES;
+      if ((s = upload(&L.afoff, off)) != NQS_OK) return s;
+      if ((s = upload(&L.btoff, off)) != NQS_OK) return s;
     }
   }
-  A.resize(A.size() + EQ, 0);   // fetch-ahead edge
-  Alo.resize(Alo.size() + EQ, 0);
-  if (a->bfA) { (void)hipFree(a->bfA); a->bfA = nullptr; }
-  if (a->bfAlo) { (void)hipFree(a->bfAlo); a->bfAlo = nullptr; }
-  nqs_status st = upload(&a->bfA, A);
-  return st != NQS_OK ? st : upload(&a->bfAlo, Alo);
+  P.fold = fold;
+  if constexpr (sizeof(T) == 8)
+    HIPCHK(launch_pack_f64(P, L.A, fold ? nullptr : L.AF, fold ? nullptr : L.BT, L.v, L.eta, L.w, L.c, L.w2, L.c2, st));
+  else
+    HIPCHK(launch_pack_f32(P, L.A, fold ? nullptr : L.AF, fold ? nullptr : L.BT, L.v, L.eta, L.w, L.c, L.w2, L.c2, st));
+  return NQS_OK;
 }
 
 // algorithmic flops of one site of one row: 8 chi^2 d (four candidates, d
@@ -1140,6 +993,7 @@ nqs_status nqs_ansatz_create(nqs_ctx* ctx, int K, int n_alpha, int n_beta, int c
     HIPCHK(hipMalloc((void**)&a->tri_rho, size_t(K) * sizeof(double)));
     HIPCHK(hipMalloc((void**)&a->tri_G, size_t(K) * a->tri_gstride * sizeof(double)));
   }
+  a->n_fwd = fptr[K];
   if ((st = upload(&a->d_fptr, fptr)) != NQS_OK) return st;
   if ((st = upload(&a->d_fslot, fslot)) != NQS_OK) return st;
   if ((st = upload(&a->d_offM, a->offM)) != NQS_OK) return st;
@@ -1231,129 +1085,88 @@ int64_t nqs_ansatz_n_params(const nqs_ansatz* ans) { return ans ? ans->n_params 
 nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStream_t stream) {
   if (!ans || !params) return fail(NQS_EINVAL, "NULL argument");
   DeviceGuard g(ans->ctx->device);
-  std::vector<double> prm(ans->n_params);
-  HIPCHK(hipMemcpyAsync(prm.data(), params, prm.size() * sizeof(double), hipMemcpyDeviceToHost, stream));
+  nqs_status st;
+  if ((st = ensure(&ans->d_flags, 3)) != NQS_OK) return st;
+  // eta of the caller's vector: cx_offEta for complex parameters (chi_c units)
+  const int64_t* off_eta = ans->cplx ? ans->d_cx + 5 * ans->K : ans->d_offEta;
+  HIPCHK(launch_check_params(ans->K, ans->chi_c, off_eta, params, ans->n_params, ans->d_flags, stream));
+  int flags[3];
+  HIPCHK(hipMemcpyAsync(flags, ans->d_flags, sizeof flags, hipMemcpyDeviceToHost, stream));
   HIPCHK(hipStreamSynchronize(stream));
-  if (ans->cplx) {
-    // the realified vector: per edge and state M_r = [[Re M, -Im M], [Im M, Re M]],
-    // v_r = [Re v; Im v], eta_r = [eta; eta], w_r = [Re w; -Im w], c_r = Re c,
-    // w2 = [Im w; Re w], c2 = Im c; the correlator block as it is
-    const int n = ans->chi_c, n2 = 2 * n;
-    for (int i = 0; i < ans->K; ++i)
-      for (int u = 0; u < n; ++u)
-        if (!(prm[ans->cx_offEta[i] + u] >= 0.0))
-          return fail(NQS_EINVAL, "eta[%d][%d] = %g is negative or NaN", i, u, prm[ans->cx_offEta[i] + u]);
-    std::vector<double> r(ans->nr_params, 0.0);
-    for (int i = 0; i < ans->K; ++i) {
-      for (int e = ans->pptr[i]; e < ans->pptr[i + 1]; ++e)
-        for (int s = 0; s < 4; ++s)
-          for (int u = 0; u < n; ++u)
-            for (int k = 0; k < n; ++k) {
-              const double* z = prm.data() + ans->cx_offM[e] + 2 * ((int64_t(s) * n + u) * n + k);
-              double* B = r.data() + ans->offM[e] + int64_t(s) * n2 * n2;
-              B[int64_t(u) * n2 + k] = z[0];
-              B[int64_t(u) * n2 + k + n] = -z[1];
-              B[int64_t(u + n) * n2 + k] = z[1];
-              B[int64_t(u + n) * n2 + k + n] = z[0];
-            }
-      for (int s = 0; s < 4; ++s)
-        for (int u = 0; u < n; ++u) {
-          r[ans->offV[i] + s * n2 + u] = prm[ans->cx_offV[i] + 2 * (s * n + u)];
-          r[ans->offV[i] + s * n2 + n + u] = prm[ans->cx_offV[i] + 2 * (s * n + u) + 1];
-        }
-      for (int u = 0; u < n; ++u) {
-        const double et = prm[ans->cx_offEta[i] + u];
-        const double wr = prm[ans->cx_offW[i] + 2 * u], wi = prm[ans->cx_offW[i] + 2 * u + 1];
-        r[ans->offEta[i] + u] = et;
-        r[ans->offEta[i] + n + u] = et;
-        r[ans->offW[i] + u] = wr;
-        r[ans->offW[i] + n + u] = -wi;
-        r[ans->offW2x[i] + u] = wi;
-        r[ans->offW2x[i] + n + u] = wr;
-      }
-      r[ans->offC[i]] = prm[ans->cx_offC[i]];
-      r[ans->offC2x[i]] = prm[ans->cx_offC[i] + 1];
-    }
-    std::copy(prm.begin() + ans->cx_offB, prm.end(), r.begin() + ans->offB);
-    prm.swap(r);
+  if (flags[0] != 0x7FFFFFFF) {
+    const int i = flags[0] / ans->chi_c, u = flags[0] % ans->chi_c;
+    double v = 0.0;
+    HIPCHK(hipMemcpy(&v, params + (ans->cplx ? ans->cx_offEta[i] : ans->offEta[i]) + u, sizeof v,
+                     hipMemcpyDeviceToHost));
+    return fail(NQS_EINVAL, "eta[%d][%d] = %g is negative or NaN", i, u, v);
   }
-  for (int i = 0; i < ans->K; ++i)
-    for (int u = 0; u < ans->chi; ++u)
-      if (!(prm[ans->offEta[i] + u] >= 0.0))
-        return fail(NQS_EINVAL, "eta[%d][%d] = %g is negative or NaN", i, u, prm[ans->offEta[i] + u]);
-  // the old layouts are replaced from here on: until every one is rebuilt the
+  // the old layouts are overwritten from here on: until every one is rebuilt the
   // ansatz counts as unbound, so a failure below leaves calls refusing it
   // instead of launching on half-built layouts
   ans->bound = false;
-  nqs_status st;
-  if ((st = build_layout<double>(ans, prm, ans->L64, false)) != NQS_OK) return st;
-  if ((st = build_layout<float>(ans, prm, ans->L32, false)) != NQS_OK) return st;
-  bool all_pos = true;
-  for (int i = 0; i < ans->K; ++i)
-    for (int u = 0; u < ans->chi; ++u) all_pos = all_pos && prm[ans->offEta[i] + u] > 0.0;
-  ans->has_fold = false;
-  ans->F64.free_all();
-  ans->F32.free_all();
-  if (all_pos) {
-    if ((st = build_layout<double>(ans, prm, ans->F64, true)) != NQS_OK) return st;
-    if ((st = build_layout<float>(ans, prm, ans->F32, true)) != NQS_OK) return st;
-    ans->has_fold = true;
+  const double* prm = params;
+  if (ans->cplx) {
+    if ((st = ensure(&ans->d_real, ans->nr_params)) != NQS_OK) return st;
+    HIPCHK(launch_realify(ans->cxmap(), ans->K, params, ans->d_real, stream));
+    prm = ans->d_real;
   }
-  // the triangular factors of the folded layout, made on the device (not from
-  // infinities or NaN: a factorisation would spread them over every candidate)
-  ans->tri = false;
-  bool finite = ans->tri_graph && ans->has_fold;
-  for (size_t k = 0; finite && k < prm.size(); ++k) finite = std::isfinite(prm[k]);
-  double* d_real = nullptr;   // complex parameters: the realified vector
-  struct FreeReal {
-    double** p;
-    ~FreeReal() { if (*p) (void)hipFree(*p); }
-  } free_real{&d_real};
-  if (finite) {
-    if (ans->cplx && (st = upload(&d_real, prm)) != NQS_OK) return st;
+  PackParams P{};
+  P.K = ans->K; P.chi = ans->chi; P.chip = ans->chip; P.n_fwd = ans->n_fwd;
+  P.fptr = ans->d_fptr; P.pptr = ans->d_pptr; P.pidx = ans->d_pidx; P.prm = prm;
+  P.offM = ans->d_offM; P.offV = ans->d_offV; P.offEta = ans->d_offEta;
+  P.offW2 = ans->cplx ? ans->d_cx + 2 * ans->K : nullptr;
+  if ((st = pack_layout<double>(ans, P, ans->L64, false, stream)) != NQS_OK) return st;
+  if ((st = pack_layout<float>(ans, P, ans->L32, false, stream)) != NQS_OK) return st;
+  ans->has_fold = flags[1] == 0;   // every eta > 0
+  if (ans->has_fold) {
+    if ((st = pack_layout<double>(ans, P, ans->F64, true, stream)) != NQS_OK) return st;
+    if ((st = pack_layout<float>(ans, P, ans->F32, true, stream)) != NQS_OK) return st;
+  }
+  // the triangular factors of the folded layout (not from infinities or NaN: a
+  // factorisation would spread them over every candidate)
+  ans->tri = ans->tri_graph && ans->has_fold && flags[2] == 0;
+  if (ans->tri) {
     TriBuild B;
     B.chi = ans->chi; B.chip = ans->chip;
     B.pptr = ans->d_pptr; B.pidx = ans->d_pidx;
-    B.prm = ans->cplx ? d_real : params;
-    B.offM = ans->d_offM; B.offV = ans->d_offV; B.offEta = ans->d_offEta;
-    B.offW2 = ans->cplx ? ans->d_cx + 2 * ans->K : nullptr;
+    B.prm = prm;
+    B.offM = ans->d_offM; B.offV = ans->d_offV; B.offEta = ans->d_offEta; B.offW2 = P.offW2;
     B.G = ans->tri_G; B.gstride = ans->tri_gstride;
     HIPCHK(launch_tri_build(B, ans->tri_params(), ans->triQ, ans->tri_rho, stream));
-    HIPCHK(hipStreamSynchronize(stream));   // the caller's buffer may change after the call
-    ans->tri = true;
   }
-  if (!ans->cplx && (st = build_bf16(ans, prm, ans->has_fold)) != NQS_OK) return st;
-  if (ans->tensor && (st = build_tn(ans, prm)) != NQS_OK) return st;
-  if (ans->d_cb) { (void)hipFree(ans->d_cb); ans->d_cb = nullptr; }
-  if (ans->d_cW) { (void)hipFree(ans->d_cW); ans->d_cW = nullptr; }
-  if (ans->d_cW1t) { (void)hipFree(ans->d_cW1t); ans->d_cW1t = nullptr; }
-  if (ans->d_cS) { (void)hipFree(ans->d_cS); ans->d_cS = nullptr; }
-  if (ans->d_cS32) { (void)hipFree(ans->d_cS32); ans->d_cS32 = nullptr; }
+  if (!ans->cplx) {
+    P.fold = ans->has_fold;
+    const int64_t n = bf16_edge_values(ans->chip) * (ans->n_fwd + 1);
+    if ((st = ensure(&ans->bfA, n)) != NQS_OK) return st;
+    if ((st = ensure(&ans->bfAlo, n)) != NQS_OK) return st;
+    HIPCHK(launch_pack_bf16(P, ans->bfA, ans->bfAlo, stream));
+  }
   if (ans->nh) {
-    const int nh = ans->nh, nv = 2 * ans->K;
-    std::vector<double> b(prm.begin() + ans->offB, prm.begin() + ans->offB + nh);
-    std::vector<double> W(prm.begin() + ans->offWc, prm.begin() + ans->offWc + int64_t(nh) * nv);
-    if ((st = upload(&ans->d_cb, b)) != NQS_OK) return st;
-    if ((st = upload(&ans->d_cW, W)) != NQS_OK) return st;
-    // hidden unit fastest: W^T [P][k] (both correlators' row kernels read it)
-    std::vector<double> Wt(size_t(nv) * nh);
-    for (int k = 0; k < nh; ++k)
-      for (int P = 0; P < nv; ++P) Wt[size_t(P) * nh + k] = W[size_t(k) * nv + P];
-    if ((st = upload(&ans->d_cW1t, Wt)) != NQS_OK) return st;
-    if (ans->ising) {
-      // S [P][Q][k] = (W2[k][P][Q] + W2[k][Q][P]) / 2
-      std::vector<double> Sy(size_t(nv) * nv * nh);
-      const double* W2 = prm.data() + ans->offW2;
-      for (int k = 0; k < nh; ++k)
-        for (int P = 0; P < nv; ++P)
-          for (int Q = 0; Q < nv; ++Q)
-            Sy[(size_t(P) * nv + Q) * nh + k] =
-                0.5 * (W2[(size_t(k) * nv + P) * nv + Q] + W2[(size_t(k) * nv + Q) * nv + P]);
-      if ((st = upload(&ans->d_cS, Sy)) != NQS_OK) return st;
-      std::vector<float> Sy32(Sy.begin(), Sy.end());
-      if ((st = upload(&ans->d_cS32, Sy32)) != NQS_OK) return st;
-    }
+    const int64_t nh = ans->nh, nv = 2 * ans->K;
+    if ((st = ensure(&ans->d_cb, nh)) != NQS_OK) return st;
+    if ((st = ensure(&ans->d_cW, nh * nv)) != NQS_OK) return st;
+    if ((st = ensure(&ans->d_cW1t, nh * nv)) != NQS_OK) return st;
+    if (ans->ising && (st = ensure(&ans->d_cS, nv * nv * nh)) != NQS_OK) return st;
+    if (ans->ising && (st = ensure(&ans->d_cS32, nv * nv * nh)) != NQS_OK) return st;
+    HIPCHK(hipMemcpyAsync(ans->d_cb, prm + ans->offB, size_t(nh) * sizeof(double), hipMemcpyDeviceToDevice, stream));
+    HIPCHK(hipMemcpyAsync(ans->d_cW, prm + ans->offWc, size_t(nh * nv) * sizeof(double), hipMemcpyDeviceToDevice,
+                          stream));
+    HIPCHK(launch_pack_corr(int(nv), ans->nh, ans->d_cW, ans->d_cW1t, ans->ising ? prm + ans->offW2 : nullptr,
+                            ans->d_cS, ans->d_cS32, stream));
   }
+  if (ans->tensor) {
+    std::vector<double> host(ans->n_params);
+    HIPCHK(hipMemcpyAsync(host.data(), params, host.size() * sizeof(double), hipMemcpyDeviceToHost, stream));
+    HIPCHK(hipStreamSynchronize(stream));
+    if (ans->tn_mfma) {
+      if ((st = build_ta<double>(ans, host, ans->L64, false)) != NQS_OK) return st;
+      if ((st = build_ta<float>(ans, host, ans->L32, false)) != NQS_OK) return st;
+      if (ans->has_fold && (st = build_ta<double>(ans, host, ans->F64, true)) != NQS_OK) return st;
+      if (ans->has_fold && (st = build_ta<float>(ans, host, ans->F32, true)) != NQS_OK) return st;
+    }
+    if ((st = build_tn(ans, host)) != NQS_OK) return st;
+  }
+  HIPCHK(hipStreamSynchronize(stream));   // the caller's buffer may change after the call
   ans->bound = true;
   return NQS_OK;
 }
