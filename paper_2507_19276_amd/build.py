@@ -9,8 +9,9 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libnqs.so")
 BUILD = os.path.join(ROOT, "_build")
 SOURCES = ["enumerate.hip", "order.hip", "nodes.hip", "psi.hip", "psi_tri.hip", "psi_tri_16.hip",
-           "psi_tri_32.hip", "psi_tri_48.hip", "psi_tri_64.hip", "psi_bf16.hip", "energy.hip", "adjoint.hip", "unique.hip", "vmc.hip", "bind.hip", "tensor_rnn.hip", "static_ws.hip",
-           "runtime.cpp", "serve.cpp"]
+           "psi_tri_32.hip", "psi_tri_48.hip", "psi_tri_64.hip", "psi_f32_16.hip", "psi_f32_32.hip", "psi_f32_48.hip",
+           "psi_f32_64.hip", "psi_bf16.hip", "energy.hip", "adjoint.hip", "unique.hip", "vmc.hip", "bind.hip",
+           "tensor_rnn.hip", "static_ws.hip", "runtime.cpp", "serve.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -19,7 +20,8 @@ FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # instead of copying them out of the accumulation registers, and the kernels
 # need fewer registers in total.
 EXTRA = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("psi.hip", "psi_tri.hip", "psi_tri_16.hip",
-           "psi_tri_32.hip", "psi_tri_48.hip", "psi_tri_64.hip", "psi_bf16.hip", "adjoint.hip")}
+           "psi_tri_32.hip", "psi_tri_48.hip", "psi_tri_64.hip", "psi_f32_16.hip", "psi_f32_32.hip", "psi_f32_48.hip",
+           "psi_f32_64.hip", "psi_bf16.hip", "adjoint.hip")}
 
 
 def build(verbose: bool = False) -> str:

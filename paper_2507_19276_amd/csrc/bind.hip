@@ -134,6 +134,36 @@ __global__ __launch_bounds__(256) void k_pack_bf16(PackParams P, uint16_t* A, ui
   Alo[int64_t(blockIdx.y) * EQ + x] = lo;
 }
 
+// The FP32 rows' stream (psi_tri.h): per site, candidate s, unit tile tt and parent
+// tile kt one block [lane][4]: lane l holds row 16 tt + l % 16 and columns
+// 16 kt + 4 (l / 16) + 0..3; block 0 of a site also writes its vectors.  One
+// workgroup per (block, site).
+__global__ __launch_bounds__(64) void k_pack_tri32(PackParams P, const int* qoff, int dmax, float* Q, int vofs) {
+#pragma clang fp contract(off)
+  const int i = blockIdx.y, CH = P.chip, TPC = CH / 16, b = blockIdx.x, l = threadIdx.x;
+  const int d = P.pptr[i + 1] - P.pptr[i], n = (d > 0 ? d : 1) * TPC, LC = tri_lc32(CH, d > 0 ? d : 1);
+  if (b == 0) {
+    float* V = Q + vofs / 4 + int64_t(i) * 6 * CH;
+    const double* e = P.prm + P.offEta[i];
+    for (int x = l; x < 4 * CH; x += 64) {
+      const int u = x % CH;
+      V[x] = u < P.chi ? float(sqrt(e[u]) * P.prm[P.offV[i] + (x / CH) * P.chi + u]) : 0.0f;
+    }
+    for (int u = l; u < CH; u += 64) {
+      V[4 * CH + u] = u < P.chi ? float(e[P.chi + u] / sqrt(e[u])) : 0.0f;
+      V[5 * CH + u] = u < P.chi && P.offW2 ? float(P.prm[P.offW2[i] + u] / sqrt(e[u])) : 0.0f;
+    }
+  }
+  if (b >= 4 * LC) return;
+  const int s = b / LC, t = b % LC, tt = t / n, kt = t % n;
+  const int u = 16 * tt + (l & 15);
+  for (int v = 0; v < 4; ++v) {
+    const int p = 16 * kt + 4 * (l >> 4) + v, e = p / CH, k = p % CH;
+    const bool in = t < TPC * n && e < d && k < P.chi && u < P.chi;
+    Q[(int64_t(qoff[i]) + b) * 256 + 4 * l + v] = in ? float(edge_value(P, i, P.pptr[i] + e, s, u, k)) : 0.0f;
+  }
+}
+
 // the correlator's W transposed (hidden unit fastest: [P][k])
 __global__ __launch_bounds__(256) void k_pack_wt(int nv, int nh, const double* W, double* Wt) {
   const int64_t x = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -228,6 +258,11 @@ hipError_t launch_pack_f64(const PackParams& P, double* A, double* AF, double* B
 hipError_t launch_pack_f32(const PackParams& P, float* A, float* AF, float* BT, float* v, float* eta, float* w,
                            float* c, float* w2, float* c2, hipStream_t st) {
   return pack<float>(P, A, AF, BT, v, eta, w, c, w2, c2, st);
+}
+
+hipError_t launch_pack_tri32(const PackParams& P, const int* qoff, int dmax, float* Q, int vofs, hipStream_t st) {
+  hipLaunchKernelGGL(k_pack_tri32, dim3(4 * tri_lc32(P.chip, dmax), P.K), dim3(64), 0, st, P, qoff, dmax, Q, vofs);
+  return hipGetLastError();
 }
 
 int64_t bf16_edge_values(int chip) {

@@ -227,6 +227,8 @@ hipError_t launch_pack_f64(const PackParams& P, double* A, double* AF, double* B
                            double* c, double* w2, double* c2, hipStream_t st);
 hipError_t launch_pack_f32(const PackParams& P, float* A, float* AF, float* BT, float* v, float* eta, float* w,
                            float* c, float* w2, float* c2, hipStream_t st);
+// the FP32 rows' stream and vectors (TriParams::Q, floats)
+hipError_t launch_pack_tri32(const PackParams& P, const int* qoff, int dmax, float* Q, int vofs, hipStream_t st);
 int64_t bf16_edge_values(int chip);
 hipError_t launch_pack_bf16(const PackParams& P, uint16_t* A, uint16_t* Alo, hipStream_t st);
 // W [nh][nv] -> Wt [nv][nh]; W2 (nullable) -> S, S32 (CorrParams)
@@ -343,10 +345,18 @@ __host__ __device__ constexpr int tri_site_blocks(int CH, int d) { return tri_lr
 __host__ __device__ constexpr int tri_tiles(int CH, int dm) {
   return CH == 16 || dm <= 2 ? 2 : 1;
 }
+// FP32: the parts C_0 .. C_3 alone, in blocks of 256 floats (rows m of a block in
+// the MFMA's own order), a window of kTriWindow32 blocks, unpadded at chip 16
+// (where the four parts are unrolled); tiles of rows: psi_tri.h
+constexpr int kTriWindow32 = 4;
+__host__ __device__ constexpr int tri_lc32(int CH, int d) {
+  return CH == 16 ? d : tri_pad((CH / 16) * (d * CH / 16), kTriWindow32);
+}
+__host__ __device__ constexpr int tri_tiles32(int CH) { return CH <= 32 ? 2 : 1; }
 constexpr int kTriMaxDegree = 3;
 constexpr size_t kTriRingBytes = 64 * 1024;   // LDS ring of one wavefront at most
 
-// The triangular-normaliser forward of FP64 rows (psi_tri.h): edge tables and
+// The forward of sorted rows (psi_tri.h): edge tables and
 // vectors of the folded layout, and the operand stream.
 struct TriParams {
   int K, chip, na, nb, W, dmax;  // W: ring slots; dmax: largest in-degree, 1..kTriMaxDegree
@@ -354,13 +364,13 @@ struct TriParams {
   const int* slot;
   const int* wsl;
   const uint64_t* live;
-  const double* Q;               // blocks of 16x16 operands, then the sites' vectors
+  const void* Q;                 // blocks of 16x16 operands, then the sites' vectors (doubles or floats)
   int qbytes, vofs;              // size of Q and byte offset of the vectors: per site
-                                 // (r [dmax][chip] of Z = |R x + r|^2 + rho, v [4][chip], w [chip], w2 [chip])
+                                 // (FP64: r [dmax][chip] of Z = |R x + r|^2 + rho,) v [4][chip], w [chip], w2 [chip]
   const int* qoff;               // [K] first block of each site
-  const double* rho;             // [K]
-  const double* c;               // [K]
-  const double* c2;              // complex parameters, as in PsiParams
+  const double* rho;             // [K] (FP64)
+  const void* c;                 // [K]
+  const void* c2;                // complex parameters, as in PsiParams
 };
 // what the operands are made from: packed (realified) parameters on the device
 struct TriBuild {
@@ -378,6 +388,8 @@ struct TriBuild {
 hipError_t launch_tri_build(const TriBuild& B, const TriParams& P, double* Q, double* rho, hipStream_t st);
 hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
                           hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                          hipStream_t st, const PsiStates<float>& X, int mode, double* phs);
 hipError_t launch_tri_16(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
                          hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
 hipError_t launch_tri_32(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
@@ -386,6 +398,14 @@ hipError_t launch_tri_48(const TriParams& P, const uint64_t* m, int64_t R, doubl
                          hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
 hipError_t launch_tri_64(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
                          hipStream_t st, const PsiStates<double>& X, int mode, double* phs);
+hipError_t launch_tri_16(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<float>& X, int mode, double* phs);
+hipError_t launch_tri_32(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<float>& X, int mode, double* phs);
+hipError_t launch_tri_48(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<float>& X, int mode, double* phs);
+hipError_t launch_tri_64(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                         hipStream_t st, const PsiStates<float>& X, int mode, double* phs);
 // lphi/sphi (and phs, nullable) of the pass's own rows from the samples' values
 hipError_t launch_own_rows(int64_t n0, int64_t n1, const int64_t* rowptr, int64_t row_base, const double* lphi_s,
                            const int8_t* sphi_s, const double* phs_s, double* lphi, int8_t* sphi, double* phs,

@@ -1,0 +1,9 @@
+// The FP32 forward of psi_tri.h at chi padded to 32.
+#include "psi_tri.h"
+
+namespace nqs {
+hipError_t launch_tri_32(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
+                         const PsiStates<float>& X, int mode, double* phs) {
+  return run_tri_ch<float, 32>(P, m, R, lphi, sphi, st, X, mode, phs);
+}
+}  // namespace nqs

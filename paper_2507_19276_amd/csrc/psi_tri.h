@@ -1,4 +1,5 @@
-// FP64 forward of the BDG-RNN / MPS-RNN rows with the conditional's
+// Forward of the BDG-RNN / MPS-RNN rows of a local energy, sorted so that a
+// wavefront's rows agree on nearly every site; in FP64 with the conditional's
 // normaliser from a triangular factor (arXiv:2507.19276, Sec. 2.1 Eqs.
 // (9)-(10), Sec. 2.2 Eq. (12) without the tensor term; realified complex
 // parameters as in psi.hip).
@@ -29,6 +30,22 @@
 // chi = 16, 4096 samples 12.0 -> 8.9 ms (MFMA busy 44%: eight sites per row, and a
 // wavefront's start, four dependent reads, is a third of its life); the same with
 // complex parameters, 1024 samples 10.8 -> 5.7 ms.
+//
+// FP32 rows (QUAD false) keep the four-candidate sum and psi.hip's order of
+// operations, so their bits are psi.hip's; what they take from here is the work
+// that the row order saves and psi.hip's four-candidates-at-once form cannot:
+//  - one candidate at a time, so chip / 16 accumulators per tile of rows instead of
+//    chip / 4, and two wavefronts per SIMD at chi = 64 instead of one;
+//  - no candidate that is forbidden to every row of the wavefront (near the chain's
+//    end and in every site of a row whose mask has closed);
+//  - the choice of the carried state is a register copy when the rows agree.
+// FP32 MFMA and VALU instructions share their units too (chip 16: MFMA busy 42% +
+// VALU 44%).  Two tiles of rows to chip 32, one above (3x3x2 lattice chi = 64, 2048
+// samples: row kernel 102 ms in psi.hip, 112 with two tiles, 70 with one; chi = 48:
+// 54 with two, 39 with one; dense K = 20 chi = 16: 6.8 in psi.hip, 5.0 with two, 4.8
+// with four; lattice chi = 16: 4.7, 3.2, 4.7).  Row kernels, psi.hip and now: dense
+// K = 20 chi = 64 100 -> 51 ms, chi = 64 chain 68 -> 40 ms, chi = 32 K = 50 NN+NNN
+// (512 samples) 13.5 -> 12.1 ms, complex chain 5.7 -> 4.4 ms.
 #pragma once
 #include "device.h"
 
@@ -36,19 +53,25 @@ namespace nqs {
 
 namespace {
 
-// wavefronts per SIMD the registers are kept to
-constexpr int tri_occ(int CH, int DM) { return CH == 16 ? (DM == 3 ? 2 : 3) : (CH == 32 ? 2 : 1); }
+// wavefronts per SIMD the registers are kept to (FP32 needs at most what two leave
+// at every size; one instead ran dense chi = 64 at 59 against 51 ms)
+template <typename T> constexpr int tri_occ(int CH, int DM) {
+  if (sizeof(T) == 4) return 2;
+  return CH == 16 ? (DM == 3 ? 2 : 3) : (CH == 32 ? 2 : 1);
+}
 
-template <int CH, int NTL, int DM, int STORE, bool CPLX>
-__global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, const uint64_t* __restrict__ m, int64_t R,
-                                                 double* __restrict__ lphi, int8_t* __restrict__ sphi,
-                                                 PsiStates<double> X, double* __restrict__ phs) {
+template <typename T, int CH, int NTL, int DM, int STORE, bool CPLX>
+__global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P, const uint64_t* __restrict__ m,
+                                                                    int64_t R, double* __restrict__ lphi,
+                                                                    int8_t* __restrict__ sphi, PsiStates<T> X,
+                                                                    double* __restrict__ phs) {
   // as in psi.hip every operation is written out: a resumed row ends
   // bit-identical to one evaluated from site 0
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) unsigned char smem[];
-  typedef d4 V;
-  constexpr int TPC = CH / 16, RW = 16 * NTL, PW = tri_pw(CH), RP = tri_rp(CH);
+  typedef typename V4<T>::type V;
+  constexpr bool QUAD = sizeof(T) == 8;   // Z from the triangular factor; else from the four candidates
+  constexpr int TPC = CH / 16, RW = 16 * NTL, PW = QUAD ? tri_pw(CH) : kTriWindow32, RP = tri_rp(CH);
   constexpr int SLOT = NTL * TPC * 64;
   // an FP64 MFMA's result takes its 16 passes and more to arrive: with one tile
   // of rows a row group is squared only after the next group's MFMAs
@@ -62,8 +85,8 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
   const CInt* slots = (const CInt*)(P.slot);
   const CInt* wsl = (const CInt*)(P.wsl);
   const CInt* qoff = (const CInt*)(P.qoff);
-  const CT<double>* cc = (const CT<double>*)(P.c);
-  const CT<double>* cc2 = (const CT<double>*)(P.c2);
+  const CT<T>* cc = (const CT<T>*)(P.c);
+  const CT<T>* cc2 = (const CT<T>*)(P.c2);
   const CT<double>* rho = (const CT<double>*)(P.rho);
   // rows come in the order of their resume sites; node units in the order of
   // launch_order_nodes, whose wavefronts start at their lowest changed site
@@ -101,8 +124,8 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
 #pragma unroll
   for (int t = 1; t < NTL; ++t)
     if (t == own) orow = rowt[t];
-  double prod = 1.0, prod2 = 1.0;   // prod2 (STORE 1): with Z summed over the candidates, as psi.hip
-  double zr = 1.0, zi = 0.0;
+  T prod = T(1), prod2 = T(1);   // prod2 (QUAD, STORE 1): with Z summed over the candidates, as psi.hip
+  T zr = T(1), zi = T(0);
   int pexp = 0, pexp2 = 0, sgn = 1, ca = 0, cb = 0;
   uint64_t badm = 0;   // lanes whose own row took a state its mask forbids
   if (X.perm && i0 > 0) {
@@ -126,7 +149,7 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
       V* wr = ring + size_t(wsl[s]) * SLOT;
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
-        const double* src = s >= nb[t] ? X.nhs + size_t(nco[t] + __popcll(nmk[t] & low_bits(s))) * CH + 4 * g
+        const T* src = s >= nb[t] ? X.nhs + size_t(nco[t] + __popcll(nmk[t] & low_bits(s))) * CH + 4 * g
                                        : X.hs + (size_t(s) * X.ns + X.owner[rowt[t]]) * CH + 4 * g;
 #pragma unroll
         for (int tt = 0; tt < TPC; ++tt) wr[(t * TPC + tt) * 64] = *reinterpret_cast<const V*>(src + 16 * tt);
@@ -139,7 +162,7 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
       if (t == own) { onb = nb[t]; ono = no[t]; }
     if (i0 >= onb) {
       const size_t so = size_t(ono + (i0 - onb));
-      const LogProd<double> lp = X.nlp[so];
+      const LogProd<T> lp = X.nlp[so];
       prod = lp.m;
       pexp = lp.e;
       sgn = lp.s;
@@ -194,7 +217,7 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
     }
     if (STORE == 2 && writer && olive && i >= sc1 && i <= se1) {
       const size_t so = size_t(soff + (i - sc1));
-      X.nlp[so] = LogProd<double>{prod, pexp, sgn};
+      X.nlp[so] = LogProd<T>{prod, pexp, sgn};
       if (CPLX) {
         X.npz[2 * so] = zr;
         X.npz[2 * so + 1] = zi;
@@ -216,10 +239,11 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
   // The rows' masks at one site as lane masks of the own rows: allowed states,
   // all four allowed, own state; and the wavefront's parts there: bit 0 = some
   // row has all four states allowed (Z from R), bit 1 + s = candidate s is some
-  // row's state, or an allowed state of a row whose mask forbids another.
+  // row's state, or an allowed state of a row whose mask forbids another (not
+  // QUAD: of any row).
   struct Masks {
     uint64_t full, a0, a1, b0, b1;   // state s = a + 2 b is allowed where a's and b's masks have the lane
-    uint32_t pt;
+    uint32_t pt, own;                // own: bit s = s is some row's state
   };
   auto masks = [&](int i, int a, int b, int s) {
     Masks M;
@@ -231,13 +255,15 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
     const uint64_t sl = __ballot(s & 1), sh = __ballot(s & 2);
     M.full = M.a0 & M.a1 & M.b0 & M.b1;
     M.pt = M.full ? 1u : 0u;
+    M.own = 0u;
     uint64_t ok = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const uint64_t st = ((k & 1) ? sl : ~sl) & ((k & 2) ? sh : ~sh);
       const uint64_t al = ((k & 1) ? M.a1 : M.a0) & ((k & 2) ? M.b1 : M.b0);
-      const uint64_t need = STORE == 1 ? ~0ull : (st | (al & ~M.full));
+      const uint64_t need = QUAD && STORE == 1 ? ~0ull : (st | (QUAD ? al & ~M.full : al));
       M.pt |= need ? 2u << k : 0u;
+      M.own |= st ? 1u << k : 0u;
       ok |= st & al;
     }
     badm |= ~ok;
@@ -246,18 +272,22 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
   // Operands and vectors come through one buffer resource: the lane's part of
   // the offset is fixed and the rest is scalar, so a load takes no vector
   // arithmetic.
-  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(P.Q), 0, P.qbytes, 0x00020000);
-  const int lane32 = 32 * lane, g32 = 32 * g;
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(P.Q), 0, P.qbytes, 0x00020000);
+  const int laneq = int(sizeof(V)) * lane, gq = int(sizeof(V)) * g;
   auto quad = [&](int vofs, int sofs) {
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    const d2 x = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vofs, sofs, 0));
-    const d2 y = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vofs + 16, sofs, 0));
-    return V{x.x, x.y, y.x, y.y};
+    if constexpr (QUAD) {
+      typedef double d2 __attribute__((ext_vector_type(2)));
+      const d2 x = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vofs, sofs, 0));
+      const d2 y = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vofs + 16, sofs, 0));
+      return V{x.x, x.y, y.x, y.y};
+    } else {
+      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, vofs, sofs, 0));
+    }
   };
-  auto ld = [&](int blk) { return quad(lane32, blk * 2048); };
-  // vectors of site i: r [DM][CH], v [4][CH], w [CH], w2 [CH]
-  constexpr int VR = 0, VV = DM * CH, VW = VV + 4 * CH, VW2 = VW + CH, VS = (DM + 6) * CH;
-  auto vec = [&](int i, int at) { return quad(g32, P.vofs + (i * VS + at) * 8); };
+  auto ld = [&](int blk) { return quad(laneq, blk * int(256 * sizeof(T))); };
+  // vectors of site i: (QUAD: r [DM][CH],) v [4][CH], w [CH], w2 [CH]
+  constexpr int VR = 0, VV = QUAD ? DM * CH : 0, VW = VV + 4 * CH, VW2 = VW + CH, VS = VW2 + CH;
+  auto vec = [&](int i, int at) { return quad(gq, P.vofs + (i * VS + at) * int(sizeof(T))); };
   // first operand block of site i's parts pt
   auto first_part = [&](int i, uint32_t pt) {
     const int d = fptr[i + 1] - fptr[i];
@@ -269,19 +299,18 @@ __global__ __launch_bounds__(64, tri_occ(CH, DM)) void k_psi_tri(TriParams P, co
   V rb[RP];   // r of the site's first row group, fetched during the site before
   auto fetch_rb = [&](int i) {
 #pragma unroll
-    for (int r = 0; r < RP; ++r)
-rb[r] = vec(i, VR + 16 * r);
+    for (int r = 0; r < RP; ++r) rb[r] = vec(i, VR + 16 * r);
   };
   if (i0 < iend) {
-    fetch_rb(i0);
+    if (QUAD) fetch_rb(i0);
     M = masks(i0, ca, cb, site_state(olo, ohi, i0));
-    const int p = first_part(i0, M.pt);
+    const int p = QUAD ? first_part(i0, M.pt) : qoff[i0];
 #pragma unroll
     for (int q = 0; q < PW; ++q) an[q] = ld(p + q);
   }
   auto site = [&](int i, auto DD) {
     constexpr int D = decltype(DD)::value, n = D * TPC;
-    constexpr int LR = tri_lr(CH, D), LC = tri_lc(CH, D);
+    constexpr int LR = QUAD ? tri_lr(CH, D) : 0, LC = QUAD ? tri_lc(CH, D) : tri_lc32(CH, D);
     const int b0 = qoff[i];
     const int e0 = fptr[i];
     V b[n][NTL];
@@ -302,7 +331,7 @@ rb[r] = vec(i, VR + 16 * r);
       for (int tt = 0; tt < TPC; ++tt)
         vb[tt] = vec(i, VV + s * CH + 16 * tt);
     };
-    fetch_v(__builtin_ctz(cand));
+    fetch_v(QUAD ? __builtin_ctz(cand) : 0);
     // the next site's parts: they follow from the occupations alone, and their
     // scalar work runs beside the MFMAs of the candidate
     const int osi = site_state(olo, ohi, i);
@@ -313,7 +342,7 @@ rb[r] = vec(i, VR + 16 * r);
       cb += osi >> 1;
       if (i + 1 < iend) {
         Mn = masks(i + 1, ca, cb, site_state(olo, ohi, i + 1));
-        pn = first_part(i + 1, Mn.pt);
+        if (QUAD) pn = first_part(i + 1, Mn.pt);
       }
     };
     // one block: four k-steps into acc, then its window slot takes the block PW
@@ -335,7 +364,7 @@ rb[r] = vec(i, VR + 16 * r);
 #pragma unroll
       for (int k = from; k < len; ++k) an[k % PW] = ld(k + PW < len ? cur + (k + PW) : nxt + (k + PW - len));
     };
-    auto square = [&](const V (&x)[RP][NTL], double (&q)[NTL]) {
+    auto square = [&](const V (&x)[RP][NTL], T (&q)[NTL]) {
 #pragma unroll
       for (int r = 0; r < RP; ++r)
 #pragma unroll
@@ -343,16 +372,16 @@ rb[r] = vec(i, VR + 16 * r);
 #pragma unroll
           for (int v = 0; v < 4; ++v) q[t] = tfma(x[r][t][v], x[r][t][v], q[t]);
     };
-    double zz[NTL], Z = 0.0;
+    T zz[NTL], Z = T(0);
     V last[RP][NTL];   // the last rows of R x + r, squared after the next part's MFMAs
 #pragma unroll
     for (int t = 0; t < NTL; ++t) {
-      zz[t] = 0.0;
+      zz[t] = T(0);
 #pragma unroll
       for (int r = 0; r < RP; ++r) last[r][t] = V{0, 0, 0, 0};
     }
     const int C0 = b0 + LR;
-    if (M.pt & 1u) {
+    if (QUAD && (M.pt & 1u)) {
       const int cur = b0, nxt = C0 + LC * int(__builtin_ctz(cand));
       int blk = 0;
 #pragma unroll
@@ -378,7 +407,7 @@ rb[r] = vec(i, VR + 16 * r);
             if (LATE) last[r][t] = acc[r][t];
       }
       skip(n * (n + 1) / 2, LR, cur, nxt);
-      if (!LATE) Z = ReduceOwn<double, NTL>::run(zz) + double(rho[i]);
+      if (!LATE) Z = ReduceOwn<T, NTL>::run(zz) + T(rho[i]);
     }
     V ww[TPC], w2[TPC];
 #pragma unroll
@@ -386,16 +415,16 @@ rb[r] = vec(i, VR + 16 * r);
       ww[tt] = vec(i, VW + 16 * tt);
       if (CPLX) w2[tt] = vec(i, VW2 + 16 * tt);
     }
-    fetch_rb(i + 1 < iend ? i + 1 : i);
+    if (QUAD) fetch_rb(i + 1 < iend ? i + 1 : i);
     V h[TPC][NTL];
-    double Zs = 0.0, pc = 0.0;
+    T Zs = T(0), pc = T(0);
     // candidate s of all rows into x, P^s of the own row returned; Z on the way
     // when its last rows are still to be squared
     auto candidate = [&](int s, const int& nxt, int s_next, auto with_z, auto&& take, auto&& beside) {
       const int cur = C0 + LC * s;
-      double pp[NTL];
+      T pp[NTL];
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) pp[t] = 0.0;
+      for (int t = 0; t < NTL; ++t) pp[t] = T(0);
       int blk = 0;
       V acc[TPC][NTL];
 #pragma unroll
@@ -431,12 +460,87 @@ rb[r] = vec(i, VR + 16 * r);
       skip(TPC * n, LC, cur, nxt);
       if (LATE && decltype(with_z)::value) {
         square(last, zz);
-        Z = ReduceOwn<double, NTL>::run(zz) + double(rho[i]);
+        Z = ReduceOwn<T, NTL>::run(zz) + T(rho[i]);
       }
       finish((TPC - 1) / RP * RP);
-      return ReduceOwn<double, NTL>::run(pp);
+      return ReduceOwn<T, NTL>::run(pp);
     };
-    if ((cand & (cand - 1)) == 0) {
+    if constexpr (!QUAD) {
+      // the four candidates one after the other: their operands are one run of
+      // the stream, so the window needs no look-ahead, and a candidate that no row
+      // needs (forbidden to all, near the chain's end) only moves it on
+      int si[NTL];
+      const bool one = (M.own & (M.own - 1)) == 0;   // every row has the same state
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) si[t] = site_state(lo[t], hi[t], i);
+      auto step = [&](int s, auto off) {
+        constexpr int O = decltype(off)::value;   // window slot of the part's first block
+        const int cur = C0 + LC * s;
+        if ((cand >> s) & 1u) {
+          V acc[TPC][NTL];
+          T pp[NTL];
+#pragma unroll
+          for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+            for (int t = 0; t < NTL; ++t) acc[tt][t] = vb[tt];
+#pragma unroll
+          for (int t = 0; t < NTL; ++t) pp[t] = T(0);
+          if (s < 3) fetch_v(s + 1);
+#pragma unroll
+          for (int blk = 0; blk < LC; ++blk) {
+            constexpr int NB = TPC * n;
+            if (blk < NB) {
+              const V a = an[(O + blk) % PW];
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int t = 0; t < NTL; ++t) acc[blk / n][t] = mfma(a[v], b[blk % n][t][v], acc[blk / n][t]);
+            }
+            an[(O + blk) % PW] = ld(cur + blk + PW);
+            __builtin_amdgcn_sched_barrier(6);   // as in block()
+          }
+#pragma unroll
+          for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+            for (int t = 0; t < NTL; ++t)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) pp[t] = tfma(acc[tt][t][v], acc[tt][t][v], pp[t]);
+          if ((M.own >> s) & 1u) {
+            if (one) {
+#pragma unroll
+              for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+                for (int t = 0; t < NTL; ++t) h[tt][t] = acc[tt][t];
+            } else {
+#pragma unroll
+              for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+                for (int t = 0; t < NTL; ++t)
+#pragma unroll
+                  for (int v = 0; v < 4; ++v) h[tt][t][v] = si[t] == s ? acc[tt][t][v] : h[tt][t][v];
+            }
+          }
+          const T ps = ReduceOwn<T, NTL>::run(pp);
+          const uint64_t al = ((s & 1) ? M.a1 : M.a0) & ((s & 2) ? M.b1 : M.b0);
+          if (osi == s) pc = ps;
+          if ((al >> lane) & 1u) Zs += ps;
+        } else {
+          if (s < 3) fetch_v(s + 1);
+#pragma unroll
+          for (int blk = 0; blk < LC; ++blk) an[(O + blk) % PW] = ld(cur + blk + PW);
+        }
+      };
+      look_ahead();
+      if constexpr (LC % PW == 0) {
+#pragma unroll 1
+        for (int s = 0; s < 4; ++s) step(s, std::integral_constant<int, 0>{});
+      } else {
+        step(0, std::integral_constant<int, 0>{});
+        step(1, std::integral_constant<int, LC % PW>{});
+        step(2, std::integral_constant<int, 2 * LC % PW>{});
+        step(3, std::integral_constant<int, 3 * LC % PW>{});
+      }
+    } else if ((cand & (cand - 1)) == 0) {
       // one candidate: every row's own
       pc = candidate(__builtin_ctz(cand), pn, -1, std::true_type{}, [&](int tt, int t, const V& x) { h[tt][t] = x; }, look_ahead);
       Zs = pc;
@@ -446,7 +550,7 @@ rb[r] = vec(i, VR + 16 * r);
       for (int t = 0; t < NTL; ++t) si[t] = site_state(lo[t], hi[t], i);
       if (LATE) {
         square(last, zz);
-        Z = ReduceOwn<double, NTL>::run(zz) + double(rho[i]);
+        Z = ReduceOwn<T, NTL>::run(zz) + T(rho[i]);
       }
       look_ahead();
       bool first = true;   // the first candidate's state for every row, the later ones' for theirs
@@ -457,7 +561,7 @@ rb[r] = vec(i, VR + 16 * r);
         const int s2 = later ? __builtin_ctz(later) : -1;
         const uint64_t al = ((s & 1) ? M.a1 : M.a0) & ((s & 2) ? M.b1 : M.b0);
         const int nxt = later ? C0 + LC * s2 : pn;
-        const double ps = candidate(
+        const T ps = candidate(
             s, nxt, s2, std::false_type{},
             [&](int tt, int t, const V& x) {
               const bool mine = first || si[t] == s;
@@ -471,9 +575,9 @@ rb[r] = vec(i, VR + 16 * r);
       }
     }
     // the carried state and the sign (or phase) of w.h + c
-    double dp[NTL], dq[NTL];
+    T dp[NTL], dq[NTL];
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) dp[t] = dq[t] = 0.0;
+    for (int t = 0; t < NTL; ++t) dp[t] = dq[t] = T(0);
     V* wr = ring + size_t(wsl[i]) * SLOT;
 #pragma unroll
     for (int tt = 0; tt < TPC; ++tt) {
@@ -494,13 +598,13 @@ rb[r] = vec(i, VR + 16 * r);
           *reinterpret_cast<V*>(X.nhs + size_t(toff[t] + __popcll(tneed[t] & low_bits(i))) * CH + 16 * tt + 4 * g) = x;
       }
     }
-    const double dot = ReduceOwn<double, NTL>::run(dp) + double(cc[i]);
+    const T dot = ReduceOwn<T, NTL>::run(dp) + T(cc[i]);
     if (CPLX) {
-      const double di = ReduceOwn<double, NTL>::run(dq) + double(cc2[i]);
-      if (dot != 0.0 || di != 0.0) {
-        const double nr = zr * dot - zi * di;
-        const double ni = zr * di + zi * dot;
-        const double an_ = fabs(nr) > fabs(ni) ? fabs(nr) : fabs(ni);
+      const T di = ReduceOwn<T, NTL>::run(dq) + T(cc2[i]);
+      if (dot != T(0) || di != T(0)) {
+        const T nr = zr * dot - zi * di;
+        const T ni = zr * di + zi * dot;
+        const T an_ = fabs(nr) > fabs(ni) ? fabs(nr) : fabs(ni);
         int ez;
         (void)tfrexp(an_, &ez);
         zr = ldexp(nr, -ez);
@@ -508,13 +612,13 @@ rb[r] = vec(i, VR + 16 * r);
       }
     }
     int ex;
-    prod = tfrexp(prod * (pc / (((M.full >> lane) & 1u) ? Z : Zs)), &ex);
+    prod = tfrexp(prod * (pc / (QUAD && ((M.full >> lane) & 1u) ? Z : Zs)), &ex);
     pexp += ex;
-    if (STORE == 1) {
+    if (QUAD && STORE == 1) {
       prod2 = tfrexp(prod2 * (pc / Zs), &ex);
       pexp2 += ex;
     }
-    if (!CPLX && dot < 0.0) sgn = -sgn;
+    if (!CPLX && dot < T(0)) sgn = -sgn;
     M = Mn;
   };
   for (int i = i0; i < iend; ++i) {
@@ -531,52 +635,57 @@ rb[r] = vec(i, VR + 16 * r);
   store_pre(iend);
   if (writer && olive) {
     const bool bad = (badm >> lane) & 1u;
-    const double pf = STORE == 1 ? prod2 : prod;
-    lphi[orow] = bad ? -INFINITY : 0.5 * (log(pf) + double(STORE == 1 ? pexp2 : pexp) * 0.69314718055994530942);
+    const T pf = QUAD && STORE == 1 ? prod2 : prod;
+    lphi[orow] = bad ? -INFINITY
+                     : 0.5 * (log(double(pf)) + double(QUAD && STORE == 1 ? pexp2 : pexp) * 0.69314718055994530942);
     sphi[orow] = int8_t(bad ? 0 : sgn);
-    if (CPLX) phs[orow] = bad ? 0.0 : atan2(zi, zr);
+    if (CPLX) phs[orow] = bad ? 0.0 : atan2(double(zi), double(zr));
   }
 }
 
-template <int CH, int DM, int STORE, bool CPLX>
+template <typename T, int CH, int DM, int STORE, bool CPLX>
 hipError_t run_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
-                   const PsiStates<double>& X, double* phs) {
-  constexpr int NTL = tri_tiles(CH, DM);
+                   const PsiStates<T>& X, double* phs) {
+  constexpr int NTL = sizeof(T) == 8 ? tri_tiles(CH, DM) : tri_tiles32(CH);
   static_assert(NTL <= 4, "the node-need marks assume at most 64 rows per wavefront");
-  const size_t per_wave = size_t(P.W) * 16 * NTL * CH * sizeof(double);
+  const size_t per_wave = size_t(P.W) * 16 * NTL * CH * sizeof(T);
   if (per_wave > 160 * 1024) return hipErrorInvalidValue;
   // one wavefront per workgroup: its LDS goes to the next as soon as it ends
-  // (four to a workgroup: K = 50 row kernel 127 against 119 ms at 4096 samples)
-  hipLaunchKernelGGL((k_psi_tri<CH, NTL, DM, STORE, CPLX>), dim3(unsigned((R + 16 * NTL - 1) / (16 * NTL))), dim3(64),
-                     per_wave, st, P, m, R, lphi, sphi, X, phs);
+  // (four to a workgroup: K = 50 FP64 row kernel 127 against 119 ms at 4096 samples)
+  hipLaunchKernelGGL((k_psi_tri<T, CH, NTL, DM, STORE, CPLX>), dim3(unsigned((R + 16 * NTL - 1) / (16 * NTL))),
+                     dim3(64), per_wave, st, P, m, R, lphi, sphi, X, phs);
   return hipGetLastError();
 }
 
-template <int CH, int DM>
+template <typename T, int CH, int DM>
 hipError_t run_tri_modes(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
-                         const PsiStates<double>& X, int mode, double* phs) {
+                         const PsiStates<T>& X, int mode, double* phs) {
   const int store = mode == PSI_STORE ? 1 : (mode == PSI_NODE ? 2 : 0);
   if (phs) {
     switch (store) {
-      case 0: return run_tri<CH, DM, 0, true>(P, m, R, lphi, sphi, st, X, phs);
-      case 1: return run_tri<CH, DM, 1, true>(P, m, R, lphi, sphi, st, X, phs);
-      default: return run_tri<CH, DM, 2, true>(P, m, R, lphi, sphi, st, X, phs);
+      case 0: return run_tri<T, CH, DM, 0, true>(P, m, R, lphi, sphi, st, X, phs);
+      case 1: return run_tri<T, CH, DM, 1, true>(P, m, R, lphi, sphi, st, X, phs);
+      default: return run_tri<T, CH, DM, 2, true>(P, m, R, lphi, sphi, st, X, phs);
     }
   }
-  switch (store) {
-    case 0: return run_tri<CH, DM, 0, false>(P, m, R, lphi, sphi, st, X, phs);
-    case 1: return run_tri<CH, DM, 1, false>(P, m, R, lphi, sphi, st, X, phs);
-    default: return run_tri<CH, DM, 2, false>(P, m, R, lphi, sphi, st, X, phs);
+  if constexpr (sizeof(T) == 4 && CH == 16 && DM == 1) {
+    return hipErrorInvalidValue;   // psi.hip's (tri32 in runtime.cpp)
+  } else {
+    switch (store) {
+      case 0: return run_tri<T, CH, DM, 0, false>(P, m, R, lphi, sphi, st, X, phs);
+      case 1: return run_tri<T, CH, DM, 1, false>(P, m, R, lphi, sphi, st, X, phs);
+      default: return run_tri<T, CH, DM, 2, false>(P, m, R, lphi, sphi, st, X, phs);
+    }
   }
 }
 
-template <int CH>
+template <typename T, int CH>
 hipError_t run_tri_ch(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
-                      const PsiStates<double>& X, int mode, double* phs) {
+                      const PsiStates<T>& X, int mode, double* phs) {
   switch (P.dmax) {
-    case 1: return run_tri_modes<CH, 1>(P, m, R, lphi, sphi, st, X, mode, phs);
-    case 2: return run_tri_modes<CH, 2>(P, m, R, lphi, sphi, st, X, mode, phs);
-    case 3: return run_tri_modes<CH, 3>(P, m, R, lphi, sphi, st, X, mode, phs);
+    case 1: return run_tri_modes<T, CH, 1>(P, m, R, lphi, sphi, st, X, mode, phs);
+    case 2: return run_tri_modes<T, CH, 2>(P, m, R, lphi, sphi, st, X, mode, phs);
+    case 3: return run_tri_modes<T, CH, 3>(P, m, R, lphi, sphi, st, X, mode, phs);
     default: return hipErrorInvalidValue;
   }
 }

@@ -155,10 +155,13 @@ hipError_t launch_tri_build(const TriBuild& B, const TriParams& P, double* Q, do
   return hipGetLastError();
 }
 
-hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
-                          hipStream_t st, const PsiStates<double>& states, int mode, double* phs) {
+namespace {
+
+template <typename T>
+hipError_t dispatch_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
+                        const PsiStates<T>& states, int mode, double* phs) {
   if (R <= 0) return hipSuccess;
-  PsiStates<double> X = states;
+  PsiStates<T> X = states;
   if (mode == PSI_STORE || mode == PSI_ROWS) X.perm = nullptr;   // the kernel takes a null order as rows from site 0
   const bool resumed = mode == PSI_SEED || mode == PSI_NODE;
   if ((mode == PSI_STORE && !X.pm) || (resumed && !X.perm)) return hipErrorInvalidValue;
@@ -172,6 +175,17 @@ hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, doub
     case 64: return launch_tri_64(P, m, R, lphi, sphi, st, X, mode, phs);
     default: return hipErrorInvalidValue;
   }
+}
+
+}  // namespace
+
+hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                          hipStream_t st, const PsiStates<double>& X, int mode, double* phs) {
+  return dispatch_tri(P, m, R, lphi, sphi, st, X, mode, phs);
+}
+hipError_t launch_psi_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi,
+                          hipStream_t st, const PsiStates<float>& X, int mode, double* phs) {
+  return dispatch_tri(P, m, R, lphi, sphi, st, X, mode, phs);
 }
 
 }  // namespace nqs

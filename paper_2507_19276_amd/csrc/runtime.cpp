@@ -378,7 +378,7 @@ struct nqs_ansatz {
   int64_t nr_params = 0;
   std::vector<int64_t> offW2x, offC2x, cx_offM, cx_offV, cx_offEta, cx_offW, cx_offC;
   int64_t cx_offB = 0;
-  // the triangular-normaliser forward of FP64 rows (psi_tri.h): whether the
+  // the forward of sorted rows (psi_tri.h), FP64 with the triangular normaliser: whether the
   // graph takes it (create), whether the bound parameters do (bind), its operands
   int n_fwd = 0;            // forward edges
   int* d_flags = nullptr;   // bind: checks of the bound vector
@@ -388,6 +388,9 @@ struct nqs_ansatz {
   int* d_qoff = nullptr;
   double *triQ = nullptr, *tri_rho = nullptr, *tri_G = nullptr;
   int tri_bytes = 0, tri_vofs = 0;
+  int* d_qoff32 = nullptr;  // the FP32 rows' stream
+  float* triQ32 = nullptr;
+  int tri_bytes32 = 0, tri_vofs32 = 0;
   int64_t tri_gstride = 0;
   int64_t* d_cx = nullptr;  // device: rW, rC, rW2, rC2, cV, cEta, cW, cC ([K] each), then cM ([edges])
   ~nqs_ansatz() {
@@ -400,7 +403,8 @@ struct nqs_ansatz {
                     (void*)bfAlo,
                     (void*)d_cb, (void*)d_cW, (void*)d_cW1t, (void*)d_cS, (void*)d_cS32, (void*)d_tn_edge,
                     (void*)d_tn_site, (void*)tn64, (void*)tn32, (void*)d_offM, (void*)d_offV,
-                    (void*)d_offEta, (void*)d_cx, (void*)d_tsite, (void*)d_flags, (void*)d_real, (void*)d_qoff, (void*)triQ,
+                    (void*)d_offEta, (void*)d_cx, (void*)d_tsite, (void*)d_flags, (void*)d_real, (void*)d_qoff,
+                    (void*)triQ, (void*)d_qoff32, (void*)triQ32,
                     (void*)tri_rho, (void*)tri_G})
       if (p) (void)hipFree(p);
   }
@@ -427,12 +431,26 @@ struct nqs_ansatz {
     P.tsite = d_tsite;
     return P;
   }
+  // FP32 rows in psi_tri.h: all that have a triangular form in FP64, but for real
+  // chains at chip 16, whose sites are too small to gain from the row order (K = 20,
+  // 3001 samples: rows 4.45 against psi.hip's 4.40 ms, the order 0.15 ms more; a
+  // site there is a quarter selection and mask arithmetic in either kernel)
+  bool tri32() const { return tri && (chip > 16 || dmax > 1 || cplx); }
+  bool tri_rows(int precision) const {
+    return precision == NQS_F64 ? tri : (precision == NQS_F32 && tri32());
+  }
   TriParams tri_params() const {
     TriParams P;
     P.K = K; P.chip = chip; P.na = na; P.nb = nb; P.W = ring; P.dmax = dmax;
     P.pptr = d_fptr; P.slot = d_fslot; P.wsl = d_wsl; P.live = d_live;
     P.Q = triQ; P.qoff = d_qoff; P.qbytes = tri_bytes; P.vofs = tri_vofs; P.rho = tri_rho;
     P.c = F64.c; P.c2 = F64.c2;
+    return P;
+  }
+  TriParams tri_params32() const {
+    TriParams P = tri_params();
+    P.Q = triQ32; P.qoff = d_qoff32; P.qbytes = tri_bytes32; P.vofs = tri_vofs32; P.rho = nullptr;
+    P.c = F32.c; P.c2 = F32.c2;
     return P;
   }
   CxMap cxmap() const {
@@ -969,7 +987,7 @@ nqs_status nqs_ansatz_create(nqs_ctx* ctx, int K, int n_alpha, int n_beta, int c
   }
   a->d1 = true;
   for (int i = 0; i < K; ++i) a->d1 = a->d1 && fptr[i + 1] - fptr[i] == 1;
-  // FP64 rows take the triangular normaliser (psi_tri.h) where its operands
+  // Rows take psi_tri.h (FP32: tri32) where the FP64 triangular operands
   // are fewer than the four candidates' (up to three parents: n (n + 1) / 2 +
   // chi/16 n against 4 chi/16 n blocks for n = d chi/16, 126 against 192 at
   // chi = 64, d = 3) and the ring of one of its wavefronts, which holds more
@@ -990,6 +1008,16 @@ nqs_status nqs_ansatz_create(nqs_ctx* ctx, int K, int n_alpha, int n_beta, int c
     a->tri_vofs = int(nblk * 2048);
     a->tri_bytes = a->tri_vofs + K * (a->dmax + 6) * a->chip * int(sizeof(double));
     HIPCHK(hipMalloc((void**)&a->triQ, size_t(a->tri_bytes)));
+    int64_t nblk32 = 0;
+    for (int i = 0; i < K; ++i) {
+      qoff[i] = int(nblk32);
+      nblk32 += 4 * tri_lc32(a->chip, fptr[i + 1] - fptr[i]);
+    }
+    nblk32 += kTriWindow32;
+    if ((st = upload(&a->d_qoff32, qoff)) != NQS_OK) return st;
+    a->tri_vofs32 = int(nblk32 * 1024);
+    a->tri_bytes32 = a->tri_vofs32 + K * 6 * a->chip * int(sizeof(float));
+    HIPCHK(hipMalloc((void**)&a->triQ32, size_t(a->tri_bytes32)));
     HIPCHK(hipMalloc((void**)&a->tri_rho, size_t(K) * sizeof(double)));
     HIPCHK(hipMalloc((void**)&a->tri_G, size_t(K) * a->tri_gstride * sizeof(double)));
   }
@@ -1133,6 +1161,8 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
     B.offM = ans->d_offM; B.offV = ans->d_offV; B.offEta = ans->d_offEta; B.offW2 = P.offW2;
     B.G = ans->tri_G; B.gstride = ans->tri_gstride;
     HIPCHK(launch_tri_build(B, ans->tri_params(), ans->triQ, ans->tri_rho, stream));
+    P.fold = true;
+    HIPCHK(launch_pack_tri32(P, ans->d_qoff32, ans->dmax, ans->triQ32, ans->tri_vofs32, stream));
   }
   if (!ans->cplx) {
     P.fold = ans->has_fold;
@@ -1270,6 +1300,11 @@ nqs_status run_amplitudes(const nqs_ansatz* a, int precision, const uint64_t* m,
   if (a->cplx && !phs) return fail(NQS_EINVAL, "complex amplitudes need their phases");
   if (precision == NQS_F64 && a->tri && mode != PSI_PLAIN) {
     HIPCHK(launch_psi_tri(a->tri_params(), m, R, lphi, sphi, st, rs ? states<double>(*rs) : PsiStates<double>(), mode,
+                          a->cplx ? phs : nullptr));
+    return NQS_OK;
+  }
+  if (precision == NQS_F32 && a->tri32() && mode != PSI_PLAIN) {
+    HIPCHK(launch_psi_tri(a->tri_params32(), m, R, lphi, sphi, st, rs ? states<float>(*rs) : PsiStates<float>(), mode,
                           a->cplx ? phs : nullptr));
     return NQS_OK;
   }
@@ -1894,7 +1929,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
         // the rows' order first: it fixes which node states the row pass reads.
         // Its per-sample counts live in the node states' storage, written later.
         const size_t nhs_ints = size_t(scap) * ans->chip * (state_bytes(opts->precision) / sizeof(int32_t));
-        if (tri && size_t(ns) * (K + 1) <= nhs_ints)
+        if (ans->tri_rows(opts->precision) && size_t(ns) * (K + 1) <= nhs_ints)
           HIPCHK(launch_order_rows(row_site, P.rows.m, samples, P.rowptr, n0, n1, row_base, Rp, K,
                                    static_cast<int32_t*>(rs.nhs), rs.tot, rs.perm, rs.t0, stream));
         else
