@@ -27,6 +27,7 @@
 // units uses k-step (t, v) and lets lane group g supply unit 16t + 4g + v,
 // so values already in registers are valid A/B operands without a transpose.
 #include "internal.h"
+#include <algorithm>
 #include <cmath>
 
 namespace nqs {
@@ -73,18 +74,138 @@ __device__ inline void counts_below(uint64_t lo, uint64_t hi, int i, int& ca, in
   cb = __popcll(lo & mlo & (ev << 1)) + __popcll(hi & mhi & (ev << 1));
 }
 
-// Kernel A: one workgroup of four wavefronts = 16 rows of site i.  The sweep over
-// the sites is serial and a batch of a few thousand rows has only a few hundred
+// Operands of candidate s of one site and tile of 16 rows: an[q][ot] a window of WQ
+// k-steps over the site's edges (the stream of consecutive edges is contiguous),
+// hb the states of the first parent.
+template <typename T, int CH>
+struct SiteOperands {
+  typedef typename V4<T>::type V;
+  static constexpr int TPC = CH / 16, NT = 4 * TPC, KS = CH / 4, WQ = KS % 8 == 0 ? 8 : 4;
+  const T* A;
+  T an[WQ][TPC];
+  V hb[TPC];
+  __device__ void fetch(const AdjParams<T>& P, int i, int s, int lane) {
+    A = P.AF + P.afoff[i] + size_t(s) * TPC * 64 + lane;
+    if (P.pptr[i] == P.pptr[i + 1]) return;   // no operands there
+#pragma unroll
+    for (int q = 0; q < WQ; ++q)
+#pragma unroll
+      for (int ot = 0; ot < TPC; ++ot) an[q][ot] = A[(q * NT + ot) * 64];
+  }
+  // acc += sum over the d edges of M^s h_j, k-steps in order; hb holds the first
+  // parent's states, load(h, e) loads edge e's
+  template <typename F> __device__ void contract(int d, V (&acc)[TPC], F&& load) {
+    const int last = d * KS - 1;
+    for (int e = 0; e < d; ++e) {
+      V hn[TPC];
+      load(hn, e + 1 < d ? e + 1 : e);
+#pragma unroll
+      for (int q = 0; q < KS; ++q) {
+#pragma unroll
+        for (int ot = 0; ot < TPC; ++ot) acc[ot] = mfma(an[q % WQ][ot], hb[q / 4][q % 4], acc[ot]);
+        const int nx = e * KS + q + WQ, at = nx < last ? nx : last;
+#pragma unroll
+        for (int ot = 0; ot < TPC; ++ot) an[q % WQ][ot] = A[(size_t(at) * NT + ot) * 64];
+      }
+#pragma unroll
+      for (int t = 0; t < TPC; ++t) hb[t] = hn[t];
+    }
+  }
+};
+
+// The carried states h_i^{s_i} of every row and site, the unfolded parameters'
+// (the values and order of operations of psi.hip's storing forward).  One workgroup
+// of four wavefronts = 16 rows: wavefront s computes candidate s and stores it for the
+// rows whose state it is (none: no work); nothing else of the forward is needed,
+// so a site is one contraction and one barrier.  The states of the last sites
+// stay in LDS, others are read back.  psi.hip's forward, with 32 rows and all
+// four candidates to a wavefront, left most of the chip idle at a training
+// batch (NN+NNN K = 50, chi = 32, FP64, 4096 rows: 128 wavefronts, 430 us; here
+// 151).  Used up to kAdjStatesRows rows; psi.hip's, which reads each operand once for
+// two to four tiles of rows, is better beyond (whole gradients in FP64, here against
+// psi.hip's: 4096 rows 1.06 against 1.32 ms, 16384 3.07 against 3.11, 24000 4.22
+// against 4.04, 40000 8.0 against 7.7).
+template <typename T, int CH>
+__global__ __launch_bounds__(256) void k_adj_states(AdjParams<T> P, const uint64_t* m, int64_t R, int64_t Rpad, T* Hbuf) {
+  typedef typename V4<T>::type V;
+  constexpr int TPC = CH / 16;
+  // sites in LDS: 32 KB; site i takes the slot of i - NW, which is not read from here
+  // any more, so one barrier a site is enough
+  constexpr int NW = 2048 / (CH * int(sizeof(T)));
+  __shared__ V hl[NW * TPC * 64];
+  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int j = lane & 15, g = lane >> 4;
+  const int64_t row = int64_t(blockIdx.x) * 16 + j;
+  const int64_t rr = row < R ? row : R - 1;
+  const uint64_t lo = m[2 * rr], hi = m[2 * rr + 1];
+  SiteOperands<T, CH> ops;
+  ops.fetch(P, 0, s, lane);
+  for (int i = 0; i < P.K; ++i) {
+    const int e0 = P.pptr[i], e1 = P.pptr[i + 1];
+    const bool mine = site_state(lo, hi, i) == s;
+    V acc[TPC];
+#pragma unroll
+    for (int t = 0; t < TPC; ++t)
+      acc[t] = *reinterpret_cast<const V*>(P.v + (size_t(i) * 4 + s) * CH + 16 * t + 4 * g);
+    if (__ballot(mine)) {
+      auto load = [&](V (&h)[TPC], int e) {
+        const int pj = P.pidx[e0 + e];
+#pragma unroll
+        for (int t = 0; t < TPC; ++t)
+          h[t] = i - pj < NW ? hl[(pj % NW * TPC + t) * 64 + lane]
+                              : *reinterpret_cast<const V*>(Hbuf + (size_t(pj) * Rpad + row) * CH + 16 * t + 4 * g);
+      };
+      if (e1 > e0) load(ops.hb, 0);
+      ops.contract(e1 - e0, acc, load);
+#pragma unroll
+      for (int t = 0; t < TPC; ++t)
+        if (mine) {
+          *reinterpret_cast<V*>(Hbuf + (size_t(i) * Rpad + row) * CH + 16 * t + 4 * g) = acc[t];
+          hl[(i % NW * TPC + t) * 64 + lane] = acc[t];
+        }
+    }
+    if (i + 1 < P.K) ops.fetch(P, i + 1, s, lane);
+    __syncthreads();
+  }
+}
+
+// Sites of one sweep step share two launches (kernel A, then kernel B): a row's
+// cotangents depend on no other row, so a workgroup of A can walk several sites.
+// What it leaves for B (dcand and deta of its sites) needs 5 chip values per row
+// and site; the first site of a step has the buffers Dc and Eeta, the later ones
+// use the dcarry slots of sites that are done (above the step's first site), five
+// each, so the sweep needs no more memory than with one site at a time.  At K = 50
+// 16 steps instead of 50: with a launch of A, one of dM and one of column sums per
+// site, of 4 to 12 us each and 3 us apart, the sweep took 1.8 ms of a chi = 32 batch
+// of 4096 rows in FP64, now 0.7 (8 or 16 sites at most: the same; 4: 2% more).
+constexpr int kSweepStep = 8;   // sites per step at most
+inline int sweep_sites(int K, int i) {   // of the step that starts at site i
+  const int c = 1 + (K - 1 - i) / 5, most = i + 1 < kSweepStep ? i + 1 : kSweepStep;
+  return c < most ? c : most;
+}
+template <typename T>
+__device__ inline T* step_dc(int K, int c, int64_t slot, T* Dc, T* dcarry) {
+  return c == 0 ? Dc : dcarry + (K - 5 * c) * slot;
+}
+template <typename T>
+__device__ inline T* step_eta(int K, int c, int64_t slot, T* Eeta, T* dcarry) {
+  return c == 0 ? Eeta : dcarry + (K - 5 * c + 4) * slot;
+}
+
+// Kernel A: one workgroup of four wavefronts = 16 rows of sites i0, i0 - 1, ..,
+// i0 - nsites + 1.  A batch of a few thousand rows has only a few hundred
 // tiles, so a launch lasts as long as one tile's chain of loads and MFMAs:
 // wavefront s recomputes candidate s (its states and P^s go to the others
 // through LDS), and the parents' cotangents are split over (edge, unit tile).
 // Every sum keeps one order, so a gradient's bits do not depend on the split.
 // (NN+NNN K = 50, chi = 32, FP64, 4096 rows: 46 us per site with one wavefront
-// per tile.)
+// per tile, 12 with four and a launch per site, 8.6 now.  Operands and states
+// fetched a phase ahead changed nothing there and cost large batches occupancy:
+// 40000 rows 8.3 against 8.0 ms.)
 template <typename T, int CH, bool CPLX>
-__global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i, const uint64_t* m, int64_t R,
+__global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i0, int nsites, const uint64_t* m, int64_t R,
                                                   int64_t Rpad, const double* cot, const T* Hbuf,
-                                                  T* dcarry, T* Dc, T* Eeta) {
+                                                  T* dcarry, T* Dc0, T* Eeta0) {
   typedef typename V4<T>::type V;
   constexpr int TPC = CH / 16, NT = 4 * TPC, KS = CH / 4;
   __shared__ V xb[NT * 64];       // candidates, then dcand: [s][tile][lane]
@@ -99,173 +220,217 @@ __global__ __launch_bounds__(256) void k_bwd_site(AdjParams<T> P, int i, const u
   const uint64_t lo = m[2 * rr], hi = m[2 * rr + 1];
   const double gd = live ? cot[row] : 0.0;
   const T gg = T(gd);
-  const int e0 = P.pptr[i], e1 = P.pptr[i + 1];
-  // recompute the candidate (A operand: W^T with the k-permutation, B: own
-  // row's stored parent state, units 16t + 4g + v in component v)
-  V acc[TPC];
+  for (int c = 0; c < nsites; ++c) {
+    // (also: the cotangents pushed to this site by the sites before are written)
+    if (c > 0) __syncthreads();
+    const int i = i0 - c;
+    T* Dc = step_dc(P.K, c, Rpad * CH, Dc0, dcarry);
+    T* Eeta = step_eta(P.K, c, Rpad * CH, Eeta0, dcarry);
+    const int e0 = P.pptr[i], e1 = P.pptr[i + 1];
+    // recompute the candidate (A operand: W^T with the k-permutation, B: own
+    // row's stored parent state, units 16t + 4g + v in component v)
+    V acc[TPC];
 #pragma unroll
-  for (int ot = 0; ot < TPC; ++ot) acc[ot] = V{0, 0, 0, 0};
-  for (int e = e0; e < e1; ++e) {
-    const int pj = P.pidx[e];
-    const T* hp = Hbuf + (size_t(pj) * Rpad + row) * CH + 4 * g;
-    const T* Ae = P.AF + P.afoff[i] + size_t(e - e0) * (KS * NT * 64) + size_t(s) * TPC * 64 + lane;
+    for (int ot = 0; ot < TPC; ++ot) acc[ot] = V{0, 0, 0, 0};
+    for (int e = e0; e < e1; ++e) {
+      const int pj = P.pidx[e];
+      const T* hp = Hbuf + (size_t(pj) * Rpad + row) * CH + 4 * g;
+      const T* Ae = P.AF + P.afoff[i] + size_t(e - e0) * (KS * NT * 64) + size_t(s) * TPC * 64 + lane;
 #pragma unroll
-    for (int t = 0; t < TPC; ++t) {
-      const V hb = *reinterpret_cast<const V*>(hp + 16 * t);
+      for (int t = 0; t < TPC; ++t) {
+        const V hb = *reinterpret_cast<const V*>(hp + 16 * t);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int q = 4 * t + v;
-        const T b = hb[v];
+        for (int v = 0; v < 4; ++v) {
+          const int q = 4 * t + v;
+          const T b = hb[v];
 #pragma unroll
-        for (int ot = 0; ot < TPC; ++ot) acc[ot] = mfma(Ae[(q * NT + ot) * 64], b, acc[ot]);
+          for (int ot = 0; ot < TPC; ++ot) acc[ot] = mfma(Ae[(q * NT + ot) * 64], b, acc[ot]);
+        }
       }
     }
-  }
-  const T* vi = P.v + size_t(i) * 4 * CH;
-  const T* ei = P.eta + size_t(i) * CH;
-  {
-    T p = 0;
+    const T* vi = P.v + size_t(i) * 4 * CH;
+    const T* ei = P.eta + size_t(i) * CH;
+    {
+      T p = 0;
 #pragma unroll
-    for (int t = 0; t < TPC; ++t) {
-      const int u0 = 16 * t + 4 * g;
-      const V vv = *reinterpret_cast<const V*>(vi + s * CH + u0);
-      const V ee = *reinterpret_cast<const V*>(ei + u0);
-      V x = acc[t] + vv;
-      if (P.tadd) x += *reinterpret_cast<const V*>(P.tadd + (size_t(row) * 4 + s) * CH + u0);
-      acc[t] = x;
-      xb[(s * TPC + t) * 64 + lane] = x;
-      p += ee.x * x.x * x.x + ee.y * x.y * x.y + ee.z * x.z * x.z + ee.w * x.w * x.w;
+      for (int t = 0; t < TPC; ++t) {
+        const int u0 = 16 * t + 4 * g;
+        const V vv = *reinterpret_cast<const V*>(vi + s * CH + u0);
+        const V ee = *reinterpret_cast<const V*>(ei + u0);
+        V x = acc[t] + vv;
+        if (P.tadd) x += *reinterpret_cast<const V*>(P.tadd + (size_t(row) * 4 + s) * CH + u0);
+        acc[t] = x;
+        xb[(s * TPC + t) * 64 + lane] = x;
+        p += ee.x * x.x * x.x + ee.y * x.y * x.y + ee.z * x.z * x.z + ee.w * x.w * x.w;
+      }
+      p += __shfl_xor(p, 16);
+      p += __shfl_xor(p, 32);
+      pb[s * 64 + lane] = p;
     }
-    p += __shfl_xor(p, 16);
-    p += __shfl_xor(p, 32);
-    pb[s * 64 + lane] = p;
-  }
-  int ca, cb;
-  counts_below(lo, hi, i, ca, cb);
-  const int si = site_state(lo, hi, i);
-  if (CPLX) {
-    // z of the row's own candidate
-    T zr = T(0), zi = T(0);
+    int ca, cb;
+    counts_below(lo, hi, i, ca, cb);
+    const int si = site_state(lo, hi, i);
+    if (CPLX) {
+      // z of the row's own candidate
+      T zr = T(0), zi = T(0);
 #pragma unroll
-    for (int t = 0; t < TPC; ++t) {
-      const int u0 = 16 * t + 4 * g;
-      const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
-      const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
-      const V x = acc[t];
-      zr += wa.x * x.x + wa.y * x.y + wa.z * x.z + wa.w * x.w;
-      zi += wb.x * x.x + wb.y * x.y + wb.z * x.z + wb.w * x.w;
-    }
-    zr += __shfl_xor(zr, 16);
-    zr += __shfl_xor(zr, 32);
-    zi += __shfl_xor(zi, 16);
-    zi += __shfl_xor(zi, 32);
-    if (s == si && g == 0) {
-      zb[j] = zr;
-      zb[16 + j] = zi;
-    }
-  }
-  __syncthreads();
-  T ps[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) ps[k] = pb[k * 64 + lane];
-  const int rest = P.K - 1 - i;
-  bool ok[4];
-  T Z = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    ok[k] = allowed(ca, cb, k, rest, P.na, P.nb);
-    if (ok[k]) Z += ps[k];
-  }
-  const T psi_ = si == 0 ? ps[0] : si == 1 ? ps[1] : si == 2 ? ps[2] : ps[3];
-  const T inv_p = T(1) / psi_, inv_z = T(1) / Z;
-  // phase term (complex parameters): alpha, beta of this row
-  T al = T(0), be = T(0);
-  if (CPLX) {
-    T zr = zb[j], zi = zb[16 + j];
-    zr += P.c[i];
-    zi += P.c2[i];
-    const T z2 = zr * zr + zi * zi;
-    const T gp = live ? T(P.cotp[row]) : T(0);
-    if (z2 > T(0)) {
-      al = -gp * zi / z2;
-      be = gp * zr / z2;
-    }
-    if (s == 0 && g == 0) {
-      P.ab[2 * row] = al;
-      P.ab[2 * row + 1] = be;
-    }
-  }
-  // d eta: unit tiles s, s + 4, .., each over the four candidates
-  for (int t = s; t < TPC; t += 4) {
-    V de = V{0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const V x = xb[(k * TPC + t) * 64 + lane];
-      if (ok[k]) de -= T(0.5) * gg * inv_z * x * x;
-      if (k == si) de += T(0.5) * gg * inv_p * x * x;
-    }
-    *reinterpret_cast<V*>(Eeta + size_t(row) * CH + 16 * t + 4 * g) = de;
-  }
-  // dcand of candidate s (in place of acc, and of its states in LDS)
-  const bool oks = allowed(ca, cb, s, rest, P.na, P.nb);
-  const T* dci = dcarry + (size_t(i) * Rpad + row) * CH + 4 * g;
-#pragma unroll
-  for (int t = 0; t < TPC; ++t) {
-    const int u0 = 16 * t + 4 * g;
-    const V ee = *reinterpret_cast<const V*>(ei + u0);
-    const V x = acc[t];
-    V d = V{0, 0, 0, 0};
-    if (oks) {
-      const T f = (s == si ? inv_p : T(0)) - inv_z;
-      d = gg * f * ee * x;
-    }
-    if (s == si) {
-      d += *reinterpret_cast<const V*>(dci + 16 * t);
-      if (CPLX) {
+      for (int t = 0; t < TPC; ++t) {
+        const int u0 = 16 * t + 4 * g;
         const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
         const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
-        d += al * wa + be * wb;
+        const V x = acc[t];
+        zr += wa.x * x.x + wa.y * x.y + wa.z * x.z + wa.w * x.w;
+        zi += wb.x * x.x + wb.y * x.y + wb.z * x.z + wb.w * x.w;
+      }
+      zr += __shfl_xor(zr, 16);
+      zr += __shfl_xor(zr, 32);
+      zi += __shfl_xor(zi, 16);
+      zi += __shfl_xor(zi, 32);
+      if (s == si && g == 0) {
+        zb[j] = zr;
+        zb[16 + j] = zi;
       }
     }
-    acc[t] = d;
-    *reinterpret_cast<V*>(Dc + size_t(row) * 4 * CH + s * CH + u0) = d;
-  }
-  __syncthreads();
+    __syncthreads();
+    T ps[4];
 #pragma unroll
-  for (int t = 0; t < TPC; ++t) xb[(s * TPC + t) * 64 + lane] = acc[t];
-  __syncthreads();
-  // parents: dcarry_j[row][kk] += sum_{s,u} dcand[row][s,u] M_ij^s[u][kk]
-  // A = dcand (rows x (s,u)), the lane's own quads; B = BT-packed M, k-step (s,t,v)
-  for (int u = s; u < (e1 - e0) * TPC; u += 4) {
-    const int e = e0 + u / TPC, ot = u % TPC;
-    const int pj = P.pidx[e];
-    const T* Be = P.BT + P.btoff[i] + size_t(e - e0) * (4 * KS * TPC * 64) + size_t(ot) * 64 + lane;
-    V o = V{0, 0, 0, 0};
+    for (int k = 0; k < 4; ++k) ps[k] = pb[k * 64 + lane];
+    const int rest = P.K - 1 - i;
+    bool ok[4];
+    T Z = 0;
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      const V d = xb[k * 64 + lane];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) o = mfma(d[v], Be[size_t(4 * k + v) * TPC * 64], o);
+    for (int k = 0; k < 4; ++k) {
+      ok[k] = allowed(ca, cb, k, rest, P.na, P.nb);
+      if (ok[k]) Z += ps[k];
     }
-    // o: rows out_row(g, v) of the tile, column kk = 16 ot + j
-    T* dcp = dcarry + size_t(pj) * Rpad * CH;
+    const T psi_ = si == 0 ? ps[0] : si == 1 ? ps[1] : si == 2 ? ps[2] : ps[3];
+    const T inv_p = T(1) / psi_, inv_z = T(1) / Z;
+    // phase term (complex parameters): alpha, beta of this row
+    T al = T(0), be = T(0);
+    if (CPLX) {
+      T zr = zb[j], zi = zb[16 + j];
+      zr += P.c[i];
+      zi += P.c2[i];
+      const T z2 = zr * zr + zi * zi;
+      const T gp = live ? T(P.cotp[row]) : T(0);
+      if (z2 > T(0)) {
+        al = -gp * zi / z2;
+        be = gp * zr / z2;
+      }
+      if (s == 0 && g == 0) {
+        P.ab[2 * row] = al;
+        P.ab[2 * row + 1] = be;
+      }
+    }
+    // d eta: unit tiles s, s + 4, .., each over the four candidates
+    for (int t = s; t < TPC; t += 4) {
+      V de = V{0, 0, 0, 0};
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t r = row0 + out_row<T>(g, v);
-      dcp[size_t(r) * CH + 16 * ot + j] += o[v];
+      for (int k = 0; k < 4; ++k) {
+        const V x = xb[(k * TPC + t) * 64 + lane];
+        if (ok[k]) de -= T(0.5) * gg * inv_z * x * x;
+        if (k == si) de += T(0.5) * gg * inv_p * x * x;
+      }
+      *reinterpret_cast<V*>(Eeta + size_t(row) * CH + 16 * t + 4 * g) = de;
+    }
+    // dcand of candidate s (in place of acc, and of its states in LDS)
+    const bool oks = allowed(ca, cb, s, rest, P.na, P.nb);
+    const T* dci = dcarry + (size_t(i) * Rpad + row) * CH + 4 * g;
+#pragma unroll
+    for (int t = 0; t < TPC; ++t) {
+      const int u0 = 16 * t + 4 * g;
+      const V ee = *reinterpret_cast<const V*>(ei + u0);
+      const V x = acc[t];
+      V d = V{0, 0, 0, 0};
+      if (oks) {
+        const T f = (s == si ? inv_p : T(0)) - inv_z;
+        d = gg * f * ee * x;
+      }
+      if (s == si) {
+        d += *reinterpret_cast<const V*>(dci + 16 * t);
+        if (CPLX) {
+          const V wa = *reinterpret_cast<const V*>(P.w + size_t(i) * CH + u0);
+          const V wb = *reinterpret_cast<const V*>(P.w2 + size_t(i) * CH + u0);
+          d += al * wa + be * wb;
+        }
+      }
+      acc[t] = d;
+      *reinterpret_cast<V*>(Dc + size_t(row) * 4 * CH + s * CH + u0) = d;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TPC; ++t) xb[(s * TPC + t) * 64 + lane] = acc[t];
+    __syncthreads();
+    // parents: dcarry_j[row][kk] += sum_{s,u} dcand[row][s,u] M_ij^s[u][kk]
+    // A = dcand (rows x (s,u)), the lane's own quads; B = BT-packed M, k-step (s,t,v)
+    for (int u = s; u < (e1 - e0) * TPC; u += 4) {
+      const int e = e0 + u / TPC, ot = u % TPC;
+      const int pj = P.pidx[e];
+      const T* Be = P.BT + P.btoff[i] + size_t(e - e0) * (4 * KS * TPC * 64) + size_t(ot) * 64 + lane;
+      V o = V{0, 0, 0, 0};
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        const V d = xb[k * 64 + lane];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o = mfma(d[v], Be[size_t(4 * k + v) * TPC * 64], o);
+      }
+      // o: rows out_row(g, v) of the tile, column kk = 16 ot + j
+      T* dcp = dcarry + size_t(pj) * Rpad * CH;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t r = row0 + out_row<T>(g, v);
+        dcp[size_t(r) * CH + 16 * ot + j] += o[v];
+      }
     }
   }
 }
 
-// Kernel B: dM_ij^s[u][kk] = sum_{rows in split} Dc[row][s,u] Hbuf[j][row][kk]
-// One wavefront per (edge, output tile of (s,u) x kk, split).
+// Kernel B, per site (blockIdx.y) of the step:
+//  - dM_ij^s[u][kk] = sum_{rows in split} Dc[row][s,u] Hbuf[j][row][kk], one
+//    wavefront per (edge, output tile of (s,u) x kk, split);
+//  - dv and deta, column sums over the rows of each split, one workgroup per 64
+//    columns and split (blocks from dmb on).  Its wavefronts hold four sums a
+//    column, each over every 16th row, so that many loads are in flight (one thread
+//    per column walked its rows one load after the other: 67 us per site at
+//    K = 50, chi = 32, 4096 rows); the 16 FP64 sums are added in order.
 template <typename T, int CH>
-__global__ __launch_bounds__(256) void k_bwd_dm(AdjParams<T> P, int i, int64_t Rpad, int rows_per_split,
-                                                int nsplit, const T* Hbuf, const T* Dc, double* gpart,
-                                                int64_t n_params) {
+__global__ __launch_bounds__(256) void k_bwd_sums(AdjParams<T> P, int i0, int dmb, int64_t Rpad, int rows_per_split,
+                                                  int nsplit, const T* Hbuf, T* dcarry, T* Dc0, T* Eeta0,
+                                                  double* gpart, int64_t n_params) {
   typedef typename V4<T>::type V;
   constexpr int MT = 4 * CH / 16, KT = CH / 16;
+  __shared__ double part[16][64];
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int i = i0 - int(blockIdx.y);
+  const T* Dc = step_dc(P.K, int(blockIdx.y), Rpad * CH, Dc0, dcarry);
+  if (int(blockIdx.x) >= dmb) {
+    const int cb = int(blockIdx.x) - dmb;
+    const int col = (cb / nsplit) * 64 + lane, split = cb % nsplit;   // 4 CH of v, CH of eta
+    const T* Eeta = step_eta(P.K, int(blockIdx.y), Rpad * CH, Eeta0, dcarry);
+    const int64_t r0 = int64_t(split) * rows_per_split;
+    const int64_t r1 = r0 + rows_per_split < Rpad ? r0 + rows_per_split : Rpad;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (col < 5 * CH) {
+      const T* x = col < 4 * CH ? Dc + col : Eeta + (col - 4 * CH);
+      const int ld = col < 4 * CH ? 4 * CH : CH;
+      // Rpad and rows_per_split are multiples of 16
+#pragma unroll 2
+      for (int64_t r = r0 + wv; r < r1; r += 16)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] += double(x[size_t(r + 4 * q) * ld]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[wv + 4 * q][lane] = acc[q];
+    __syncthreads();
+    if (wv != 0 || col >= 5 * CH) return;
+    double sum = acc[0];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) sum += part[w][lane];
+    const int s = col / CH, u = col % CH;   // s = 4: eta
+    if (u < P.chi)
+      gpart[size_t(split) * n_params + (s < 4 ? P.offV[i] + s * P.chi : P.offEta[i]) + u] = sum;
+    return;
+  }
   const int e0 = P.pptr[i], d = P.pptr[i + 1] - e0;
   const int64_t unit = int64_t(blockIdx.x) * 4 + wv;
   const int64_t total = int64_t(d) * MT * KT * nsplit;
@@ -285,6 +450,7 @@ __global__ __launch_bounds__(256) void k_bwd_dm(AdjParams<T> P, int i, int64_t R
   V acc = V{0, 0, 0, 0};
   const T* Ap = Dc + size_t(mt) * 16 + mperm;
   const T* Bp = Hbuf + size_t(pj) * Rpad * CH + size_t(kt) * 16 + mrow;
+#pragma unroll 4
   for (int64_t r = r0 + kq; r < r1; r += 4) {
     const T a = Ap[size_t(r) * 4 * CH];
     const T b = Bp[size_t(r) * CH];
@@ -300,37 +466,6 @@ __global__ __launch_bounds__(256) void k_bwd_dm(AdjParams<T> P, int i, int64_t R
     if (u < P.chi && kk < P.chi)
       out[P.offM[e0 + el] + (int64_t(s) * P.chi + u) * P.chi + kk] = double(acc[v]);
   }
-}
-
-// dv and deta: column sums over the rows of each split.  One workgroup per 64
-// columns and split; its 16 wavefronts take every 16th row each, so that all the
-// loads of a column are in flight at once (one thread per column walked its rows
-// one load after the other: 67 us per site at K = 50, chi = 32, 4096 rows), and
-// their FP64 sums are added in order.
-template <typename T, int CH>
-__global__ __launch_bounds__(1024) void k_bwd_colsum(AdjParams<T> P, int i, int64_t Rpad, int rows_per_split,
-                                                     const T* Dc, const T* Eeta, double* gpart, int64_t n_params) {
-  __shared__ double part[16][64];
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int col = blockIdx.x * 64 + lane;   // 4 CH of v, CH of eta
-  const int split = blockIdx.y;
-  const int64_t r0 = int64_t(split) * rows_per_split;
-  const int64_t r1 = r0 + rows_per_split < Rpad ? r0 + rows_per_split : Rpad;
-  double acc = 0.0;
-  if (col < 5 * CH) {
-    const T* x = col < 4 * CH ? Dc + col : Eeta + (col - 4 * CH);
-    const int ld = col < 4 * CH ? 4 * CH : CH;
-#pragma unroll 4
-    for (int64_t r = r0 + wv; r < r1; r += 16) acc += double(x[size_t(r) * ld]);
-  }
-  part[wv][lane] = acc;
-  __syncthreads();
-  if (wv != 0 || col >= 5 * CH) return;
-#pragma unroll
-  for (int w = 1; w < 16; ++w) acc += part[w][lane];
-  const int s = col / CH, u = col % CH;   // s = 4: eta
-  if (u < P.chi)
-    gpart[size_t(split) * n_params + (s < 4 ? P.offV[i] + s * P.chi : P.offEta[i]) + u] = acc;
 }
 
 // complex parameters: dw[u] = sum_rows alpha x[u], dw2[u] = sum beta x[u],
@@ -492,15 +627,15 @@ inline unsigned grid_for(int64_t units, int per_block) {
 }
 
 template <typename T, int CH>
-hipError_t run_site(const AdjParams<T>& P, int i, const uint64_t* m, int64_t R, int64_t Rpad,
-                    const double* cot, const T* Hbuf, T* dcarry, T* Dc, T* Eeta, int rows_per_split,
-                    int nsplit, double* gpart, int64_t n_params, hipStream_t st) {
+hipError_t run_sites(const AdjParams<T>& P, int i, int nsites, const uint64_t* m, int64_t R, int64_t Rpad,
+                     const double* cot, const T* Hbuf, T* dcarry, T* Dc, T* Eeta, int rows_per_split,
+                     int nsplit, double* gpart, int64_t n_params, hipStream_t st) {
   const int64_t tiles = Rpad / 16;
   if (P.cotp)
-    hipLaunchKernelGGL((k_bwd_site<T, CH, true>), dim3(unsigned(tiles)), dim3(256), 0, st, P, i, m, R, Rpad,
+    hipLaunchKernelGGL((k_bwd_site<T, CH, true>), dim3(unsigned(tiles)), dim3(256), 0, st, P, i, nsites, m, R, Rpad,
                        cot, Hbuf, dcarry, Dc, Eeta);
   else
-    hipLaunchKernelGGL((k_bwd_site<T, CH, false>), dim3(unsigned(tiles)), dim3(256), 0, st, P, i, m, R, Rpad,
+    hipLaunchKernelGGL((k_bwd_site<T, CH, false>), dim3(unsigned(tiles)), dim3(256), 0, st, P, i, nsites, m, R, Rpad,
                        cot, Hbuf, dcarry, Dc, Eeta);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -509,15 +644,12 @@ hipError_t run_site(const AdjParams<T>& P, int i, const uint64_t* m, int64_t R, 
                        0, st, P, i, Rpad, rows_per_split, nsplit, Hbuf, gpart, n_params);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  const int d = P.pptr_host[i + 1] - P.pptr_host[i];
-  if (d > 0) {
-    const int64_t units = int64_t(d) * (4 * CH / 16) * (CH / 16) * nsplit;
-    hipLaunchKernelGGL((k_bwd_dm<T, CH>), dim3(grid_for(units, 4)), dim3(256), 0, st, P, i, Rpad,
-                       rows_per_split, nsplit, Hbuf, Dc, gpart, n_params);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((k_bwd_colsum<T, CH>), dim3((5 * CH + 63) / 64, nsplit), dim3(1024), 0, st, P, i, Rpad,
-                     rows_per_split, Dc, Eeta, gpart, n_params);
+  int d = 0;
+  for (int c = 0; c < nsites; ++c) d = std::max(d, P.pptr_host[i - c + 1] - P.pptr_host[i - c]);
+  const int dmb = int(grid_for(int64_t(d) * (4 * CH / 16) * (CH / 16) * nsplit, 4));
+  hipLaunchKernelGGL((k_bwd_sums<T, CH>), dim3(unsigned(dmb + (5 * CH + 63) / 64 * nsplit), unsigned(nsites)),
+                     dim3(256), 0, st, P, i, dmb, Rpad, rows_per_split, nsplit, Hbuf, dcarry, Dc, Eeta, gpart,
+                     n_params);
   return hipGetLastError();
 }
 
@@ -525,21 +657,24 @@ template <typename T>
 hipError_t run_sweep(const AdjParams<T>& P0, const uint64_t* m, int64_t R, int64_t Rpad, const double* cot,
                      const T* Hbuf, T* dcarry, T* Dc, T* Eeta, int rows_per_split, int nsplit, double* gpart,
                      int64_t n_params, hipStream_t st, const TnAdj<T>* tn) {
-  for (int i = P0.K - 1; i >= 0; --i) {
+  int n = 1;
+  for (int i = P0.K - 1; i >= 0; i -= n) {
     hipError_t e;
     // a tensor site: its term t^s of every row first (added to the recomputed
-    // candidates), its own gradient and the parents' cotangents after dcand
+    // candidates), its own gradient and the parents' cotangents after dcand.  The
+    // tensor term and the phase term have buffers for one site: a step each
     const bool tsite = tn && tn->tq_host[i] > 0;
+    n = tn || P0.cotp ? 1 : sweep_sites(P0.K, i);
     AdjParams<T> P = P0;
     P.tadd = tsite ? tn->TT : nullptr;
     if (tsite && (e = launch_tn_bwd_site(*tn, P0.pidx, i, 0, Rpad, Hbuf, Dc, dcarry, rows_per_split, nsplit, gpart,
                                          n_params, st)) != hipSuccess)
       return e;
     switch (P.chip) {
-      case 16: e = run_site<T, 16>(P, i, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
-      case 32: e = run_site<T, 32>(P, i, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
-      case 48: e = run_site<T, 48>(P, i, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
-      case 64: e = run_site<T, 64>(P, i, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
+      case 16: e = run_sites<T, 16>(P, i, n, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
+      case 32: e = run_sites<T, 32>(P, i, n, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
+      case 48: e = run_sites<T, 48>(P, i, n, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
+      case 64: e = run_sites<T, 64>(P, i, n, m, R, Rpad, cot, Hbuf, dcarry, Dc, Eeta, rows_per_split, nsplit, gpart, n_params, st); break;
       default: e = hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
@@ -551,6 +686,30 @@ hipError_t run_sweep(const AdjParams<T>& P0, const uint64_t* m, int64_t R, int64
 }
 
 }  // namespace
+
+template <typename T>
+hipError_t run_states(const AdjParams<T>& P, int W, const uint64_t* m, int64_t R, int64_t Rpad, T* Hbuf,
+                      hipStream_t st) {
+  if (!psi_ring_fits(W, P.chip, int(sizeof(T)))) return hipErrorInvalidValue;   // as psi.hip's forward
+  const dim3 grid(unsigned(Rpad / 16));
+  switch (P.chip) {
+    case 16: hipLaunchKernelGGL((k_adj_states<T, 16>), grid, dim3(256), 0, st, P, m, R, Rpad, Hbuf); break;
+    case 32: hipLaunchKernelGGL((k_adj_states<T, 32>), grid, dim3(256), 0, st, P, m, R, Rpad, Hbuf); break;
+    case 48: hipLaunchKernelGGL((k_adj_states<T, 48>), grid, dim3(256), 0, st, P, m, R, Rpad, Hbuf); break;
+    case 64: hipLaunchKernelGGL((k_adj_states<T, 64>), grid, dim3(256), 0, st, P, m, R, Rpad, Hbuf); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_adj_states(const AdjParams<double>& P, int W, const uint64_t* m, int64_t R, int64_t Rpad,
+                             double* Hbuf, hipStream_t st) {
+  return run_states<double>(P, W, m, R, Rpad, Hbuf, st);
+}
+hipError_t launch_adj_states(const AdjParams<float>& P, int W, const uint64_t* m, int64_t R, int64_t Rpad,
+                             float* Hbuf, hipStream_t st) {
+  return run_states<float>(P, W, m, R, Rpad, Hbuf, st);
+}
 
 hipError_t launch_bwd_sweep_f64(const AdjParams<double>& P, const uint64_t* m, int64_t R, int64_t Rpad,
                                 const double* cot, const double* Hbuf, double* dcarry, double* Dc,

@@ -580,6 +580,15 @@ hipError_t launch_gather_logpsi_phase(int64_t N, const double* lphi, const int8_
                                       hipStream_t st);
 
 // ---- launchers (adjoint.hip) -------------------------------------------
+constexpr int64_t kAdjStatesRows = 16384;   // see k_adj_states
+// the carried states of rows at every site into Hbuf [K][Rpad][chip] (no tensor
+// term); W: ring slots of psi.hip's forward, whose limits hold here too
+hipError_t launch_adj_states(const AdjParams<double>& P, int W, const uint64_t* m, int64_t R, int64_t Rpad,
+                             double* Hbuf, hipStream_t st);
+hipError_t launch_adj_states(const AdjParams<float>& P, int W, const uint64_t* m, int64_t R, int64_t Rpad,
+                             float* Hbuf, hipStream_t st);
+// whether a wavefront's ring of W states fits the LDS in psi.hip (esz: bytes per element)
+bool psi_ring_fits(int W, int chip, int esz);
 // tn (nullable): the tensor term's part of the sweep
 hipError_t launch_bwd_sweep_f64(const AdjParams<double>& P, const uint64_t* m, int64_t R, int64_t Rpad,
                                 const double* cot, const double* Hbuf, double* dcarry, double* Dc,

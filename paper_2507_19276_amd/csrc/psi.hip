@@ -794,6 +794,10 @@ hipError_t dispatch_psi(const PsiParams<T>& P, const uint64_t* m, int64_t R, dou
 
 }  // namespace
 
+bool psi_ring_fits(int W, int chip, int esz) {
+  return size_t(W) * 16 * (esz == 8 ? ntiles<double>(chip) : ntiles<float>(chip)) * chip * esz <= 160 * 1024;
+}
+
 hipError_t launch_psi_f64(const PsiParams<double>& P, const uint64_t* m, int64_t R, double* lphi,
                           int8_t* sphi, hipStream_t st, const PsiStates<double>& X, int mode, double* phs) {
   return dispatch_psi<double>(P, m, R, lphi, sphi, st, X, mode, phs);

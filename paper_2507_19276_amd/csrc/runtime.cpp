@@ -1632,8 +1632,9 @@ nqs_status nqs_logpsi_vjp_phase(nqs_ctx* ctx, const nqs_ansatz* ans, const uint6
   void* dcarry = S.get<unsigned char>(hsz * esz);
   void* Dc = S.get<unsigned char>(size_t(Rpad) * 4 * ans->chip * esz);
   void* Eeta = S.get<unsigned char>(size_t(Rpad) * ans->chip * esz);
-  double* lphi = S.get<double>(N);
-  int8_t* sphi = S.get<int8_t>(N);
+  const bool own_states = !ans->tensor && N <= kAdjStatesRows;
+  double* lphi = own_states ? nullptr : S.get<double>(N);
+  int8_t* sphi = own_states ? nullptr : S.get<int8_t>(N);
   double* gpart = S.get<double>(size_t(nsplit) * np);
   double* cotp = S.get<double>(Rpad);
   double* cotq = phase ? S.get<double>(Rpad) : nullptr;
@@ -1686,6 +1687,8 @@ nqs_status nqs_logpsi_vjp_phase(nqs_ctx* ctx, const nqs_ansatz* ans, const uint6
     if (ans->tensor) {
       A = tn_adj((double*)tnb, ans->tn<double>(ans->tn64));
       HIPCHK(launch_psi_tn_f64(A.P, samples, N, lphi, sphi, stream, (double*)Hbuf, Rpad));
+    } else if (own_states) {
+      HIPCHK(launch_adj_states(ans->adj(ans->L64), ans->ring, samples, N, Rpad, (double*)Hbuf, stream));
     } else {
       PsiStates<double> X;
       X.hs = (double*)Hbuf;
@@ -1700,6 +1703,8 @@ nqs_status nqs_logpsi_vjp_phase(nqs_ctx* ctx, const nqs_ansatz* ans, const uint6
     if (ans->tensor) {
       A = tn_adj((float*)tnb, ans->tn<float>(ans->tn32));
       HIPCHK(launch_psi_tn_f32(A.P, samples, N, lphi, sphi, stream, (float*)Hbuf, Rpad));
+    } else if (own_states) {
+      HIPCHK(launch_adj_states(ans->adj(ans->L32), ans->ring, samples, N, Rpad, (float*)Hbuf, stream));
     } else {
       PsiStates<float> X;
       X.hs = (float*)Hbuf;
