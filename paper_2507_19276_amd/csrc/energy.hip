@@ -528,11 +528,29 @@ __global__ __launch_bounds__(256) void k_reduce_cx(int64_t n0, int64_t n1, const
 __global__ __launch_bounds__(1024) void k_batch_sums(int64_t N, const double* counts, const double* eloc,
                                                      const double* etnum, const double* fsq,
                                                      const double* eloc_im, const double* etnum_im,
-                                                     double* out) {
+                                                     const int64_t* Dn, const int64_t* Un, BatchSums* res) {
+  double* out = res->v;
   __shared__ double red[4][1024];
+  __shared__ unsigned long long rows[2];
   __shared__ double E_sh;
   const int tid = threadIdx.x;
   double sc = 0, sf2 = 0, se = 0, sei = 0, nn = 0;
+  if (tid < 2) rows[tid] = 0;
+  __syncthreads();
+  unsigned long long nd = 0, nu = 0;
+  for (int64_t n = tid; n < N; n += 1024) {
+    nd += uint64_t(Dn[n]);
+    nu += uint64_t(Un[n]);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    nd += __shfl_xor(nd, o);
+    nu += __shfl_xor(nu, o);
+  }
+  if ((tid & 63) == 0) {
+    atomicAdd(&rows[0], nd);
+    atomicAdd(&rows[1], nu);
+  }
   for (int64_t n = tid; n < N; n += 1024) {
     const double c = counts ? counts[n] : 1.0;
     if (isnan(eloc[n])) { nn += 1; continue; }
@@ -571,6 +589,8 @@ __global__ __launch_bounds__(1024) void k_batch_sums(int64_t N, const double* co
   if (tid == 0) {
     out[0] = tsc; out[1] = tsf; out[2] = tse; out[3] = E; out[4] = tsf / tsc;
     out[5] = red[0][0] / tsf; out[6] = red[1][0]; out[7] = etnum_im ? tsei / tsf : 0.0;
+    res->det_rows = int64_t(rows[0]);
+    res->draw_rows = int64_t(rows[1]);
   }
 }
 
@@ -697,10 +717,10 @@ hipError_t launch_reduce(int64_t n0, int64_t n1, const int64_t* rowptr, int64_t 
 }
 
 hipError_t launch_batch_sums(int64_t N, const double* counts, const double* eloc, const double* etnum,
-                             const double* fsq, double* out, hipStream_t st, const double* eloc_im,
-                             const double* etnum_im) {
-  hipLaunchKernelGGL(k_batch_sums, dim3(1), dim3(1024), 0, st, N, counts, eloc, etnum, fsq, eloc_im, etnum_im,
-                     out);
+                             const double* fsq, const int64_t* Dn, const int64_t* Un, BatchSums* out, hipStream_t st,
+                             const double* eloc_im, const double* etnum_im) {
+  hipLaunchKernelGGL(k_batch_sums, dim3(1), dim3(1024), 0, st, N, counts, eloc, etnum, fsq, eloc_im, etnum_im, Dn,
+                     Un, out);
   return hipGetLastError();
 }
 

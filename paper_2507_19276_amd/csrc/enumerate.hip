@@ -788,7 +788,7 @@ __global__ __launch_bounds__(256) void k_draw(HamDev H, EnumGeom G, const uint64
 }
 
 // rowptr[n] = sum_{n' < n} (1 + |D_n'| + U_n'), single workgroup of 1024 threads
-__global__ __launch_bounds__(1024) void k_row_counts(int64_t N, const int64_t* Dn, const int64_t* Un,
+__global__ __launch_bounds__(1024) void k_row_counts(int64_t N, const int64_t* Dn, int64_t* Un, bool drawn,
                                                      int64_t* rowptr) {
   __shared__ int64_t part[1024];
   __shared__ int64_t carry;
@@ -797,7 +797,8 @@ __global__ __launch_bounds__(1024) void k_row_counts(int64_t N, const int64_t* D
   __syncthreads();
   for (int64_t base = 0; base < N; base += 1024) {
     const int64_t n = base + tid;
-    const int64_t v = n < N ? 1 + Dn[n] + Un[n] : 0;
+    const int64_t v = n < N ? 1 + Dn[n] + (drawn ? Un[n] : 0) : 0;
+    if (!drawn && n < N) Un[n] = 0;
     part[tid] = v;
     __syncthreads();
     for (int o = 1; o < 1024; o <<= 1) {
@@ -1040,9 +1041,9 @@ hipError_t launch_draw(const HamDev& H, const EnumGeom& G, const uint64_t* sampl
   return hipGetLastError();
 }
 
-hipError_t launch_row_counts(int64_t N, const int64_t* Dn, const int64_t* Un, int64_t* rowptr,
+hipError_t launch_row_counts(int64_t N, const int64_t* Dn, int64_t* Un, bool drawn, int64_t* rowptr,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_row_counts, dim3(1), dim3(1024), 0, st, N, Dn, Un, rowptr);
+  hipLaunchKernelGGL(k_row_counts, dim3(1), dim3(1024), 0, st, N, Dn, Un, drawn, rowptr);
   return hipGetLastError();
 }
 

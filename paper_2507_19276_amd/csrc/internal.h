@@ -242,7 +242,7 @@ hipError_t launch_check_params(int K, int chi, const int64_t* offEta, const doub
 hipError_t launch_realify(const CxMap& M, int K, const double* p, double* r, hipStream_t st);
 
 // ---- launchers (enumerate.hip) ----------------------------------------
-hipError_t launch_validate(const uint64_t* samples, int64_t N, int K, int na, int nb, int* bad,
+hipError_t launch_validate(const uint64_t* samples, int64_t N, int K, int na, int nb, int32_t* bad /* device or pinned */,
                            hipStream_t st);
 hipError_t launch_enum_count(const HamDev& H, const EnumGeom& G, const uint64_t* samples, int64_t N,
                              double eps, int qshift, uint64_t* masks, uint64_t* qpref, uint64_t* segq,
@@ -253,7 +253,8 @@ hipError_t launch_draw(const HamDev& H, const EnumGeom& G, const uint64_t* sampl
                        double eps, int qshift, int n_eps, DrawKeys keys, const uint64_t* qpref,
                        const uint64_t* segq_off, const uint64_t* Qn, int32_t* urank, double* ucoef,
                        uint64_t* um, int64_t* Un, hipStream_t st);
-hipError_t launch_row_counts(int64_t N, const int64_t* Dn, const int64_t* Un, int64_t* rowptr,
+// drawn: whether Un holds the drawn rows' counts (else it is cleared)
+hipError_t launch_row_counts(int64_t N, const int64_t* Dn, int64_t* Un, bool drawn, int64_t* rowptr,
                              hipStream_t st);
 hipError_t launch_fill(const HamDev& H, const EnumGeom& G, const uint64_t* samples, int64_t n0, int64_t n1,
                        const uint64_t* masks, const uint32_t* segd_off, const int64_t* rowptr,
@@ -564,8 +565,13 @@ hipError_t launch_reduce(int64_t n0, int64_t n1, const int64_t* rowptr, int64_t 
                          double* fsq, hipStream_t st);
 // eloc_im, etnum_im (nullable): complex local energies; then the variance
 // takes |E_loc - E|^2 and out[7] = sum c Im Etilde_num / sum c |f|^2
+struct BatchSums {
+  double v[8];                    // sum c, sum c|f|^2, sum c Etilde_num, E, B, variance, NaN samples, E_im
+  int64_t det_rows, draw_rows;    // sums of Dn and Un
+};
+// out: device or pinned memory
 hipError_t launch_batch_sums(int64_t N, const double* counts, const double* eloc, const double* etnum,
-                             const double* fsq, double* out /*[8]*/, hipStream_t st,
+                             const double* fsq, const int64_t* Dn, const int64_t* Un, BatchSums* out, hipStream_t st,
                              const double* eloc_im = nullptr, const double* etnum_im = nullptr);
 hipError_t launch_gather_logpsi(int64_t N, const double* lphi, const int8_t* sphi, const double* lf,
                                 const int8_t* sf, double* logabs, int8_t* sign, hipStream_t st);

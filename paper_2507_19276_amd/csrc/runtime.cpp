@@ -87,6 +87,7 @@ struct nqs_ctx {
   // blocks handed back with work still queued on their stream: they count as
   // in use until the event recorded after that work has completed
   std::vector<std::pair<hipEvent_t, std::vector<void*>>> pending;
+  std::vector<void*> mail;                    // idle mailboxes (struct Mail), one made with the context
 
   void free_block_locked(void* p) {
     auto it = sizes.find(p);
@@ -206,10 +207,52 @@ struct nqs_ctx {
       (void)hipEventDestroy(pe.first);
     }
     for (auto& kv : sizes) (void)hipFree(kv.first);
+    for (void* p : mail) (void)hipHostFree(p);
   }
 };
 
 namespace {
+
+// What a call's kernels report to the host, in pinned memory that they write
+// directly: a small result then costs the wait for its stream alone, not a copy
+// (and a clearing fill before it) of 10 to 40 us each.  A K = 6 batch of 256
+// samples spent a third of its 0.45 ms on eight of them.
+constexpr int64_t kMailRows = 4096;
+struct Mail {
+  int32_t bad, overflow;
+  int64_t nodes[2];             // nodes and entries of the pass
+  BatchSums sums;
+  int64_t tot[65];              // rows by resume site of the pass
+  int64_t rowptr[kMailRows + 1];
+};
+
+// A context's mailbox for one call on one stream.
+struct MailSlot {
+  nqs_ctx* ctx;
+  hipStream_t st;
+  Mail* m = nullptr;
+  bool idle = true;   // no queued work writes to it (else the stream is waited for)
+  MailSlot(nqs_ctx* c, hipStream_t s) : ctx(c), st(s) {
+    {
+      std::lock_guard<std::mutex> lk(ctx->mu);
+      if (!ctx->mail.empty()) {
+        m = static_cast<Mail*>(ctx->mail.back());
+        ctx->mail.pop_back();
+      }
+    }
+    void* p = nullptr;
+    if (!m && hipHostMalloc(&p, sizeof(Mail), hipHostMallocDefault) == hipSuccess) m = static_cast<Mail*>(p);
+    if (!m) (void)hipGetLastError();
+  }
+  MailSlot(const MailSlot&) = delete;
+  MailSlot& operator=(const MailSlot&) = delete;
+  ~MailSlot() {
+    if (!m) return;
+    if (!idle) (void)hipStreamSynchronize(st);
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    ctx->mail.push_back(m);
+  }
+};
 
 // Bump allocator over a fixed device array (the static workspace of the
 // allocation-free entry point): one per call; the workspaces of the call
@@ -683,6 +726,7 @@ nqs_status nqs_ctx_create(int device, nqs_ctx** out) {
   // this device's static workspace (once per device; only nqs_eloc_noalloc uses it)
   c->arena_err = static_workspace_setup(device);
   if (c->arena_err == hipSuccess) c->arena = static_workspace(device);
+  { MailSlot first(c, nullptr); }
   *out = c;
   return NQS_OK;
 }
@@ -1206,17 +1250,17 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
 namespace {
 
 nqs_status check_samples(nqs_ctx* ctx, const uint64_t* samples, int64_t N, int K, int na, int nb,
-                         hipStream_t st, Arena* arena = nullptr) {
+                         hipStream_t st) {
   if (N == 0) return NQS_OK;
-  Scratch S(ctx, st, arena);
-  int* bad = S.get<int>(1);
-  if (!bad) return fail(NQS_ENOMEM, "workspace allocation failed");
-  HIPCHK(hipMemsetAsync(bad, 0, sizeof(int), st));
-  HIPCHK(launch_validate(samples, N, K, na, nb, bad, st));
-  int hb = 0;
-  HIPCHK(hipMemcpyAsync(&hb, bad, sizeof(int), hipMemcpyDeviceToHost, st));
+  MailSlot ms(ctx, st);
+  if (!ms.m) return fail(NQS_ENOMEM, "workspace allocation failed");
+  volatile int32_t* bad = &ms.m->bad;
+  *bad = 0;
+  ms.idle = false;
+  HIPCHK(launch_validate(samples, N, K, na, nb, &ms.m->bad, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (hb) return fail(NQS_EINVAL, "a sample lies outside the (%d,%d) sector of K=%d", na, nb, K);
+  ms.idle = true;
+  if (*bad) return fail(NQS_EINVAL, "a sample lies outside the (%d,%d) sector of K=%d", na, nb, K);
   return NQS_OK;
 }
 
@@ -1468,15 +1512,19 @@ nqs_status count_and_draw(Scratch& S, const nqs_instance* inst, const uint64_t* 
     k.sample_base = uint32_t(o.sample_base);
     HIPCHK(launch_draw(H, P.G, samples, N, o.eps, P.qshift, ne, k, P.qpref, P.segq, P.Qn, P.urank, P.ucoef,
                        P.um, P.Un, st));
-  } else {
-    HIPCHK(hipMemsetAsync(P.Un, 0, sizeof(int64_t) * N, st));
   }
-  HIPCHK(launch_row_counts(N, P.Dn, P.Un, P.rowptr, st));
+  HIPCHK(launch_row_counts(N, P.Dn, P.Un, ne > 0, P.rowptr, st));
   HIPCHK(launch_diag(H, samples, N, P.hdiag, st));
   if (ev) HIPCHK(hipEventRecord(ev[2], st));
   P.rowptr_host.resize(N + 1);
-  HIPCHK(hipMemcpyAsync(P.rowptr_host.data(), P.rowptr, sizeof(int64_t) * (N + 1), hipMemcpyDeviceToHost, st));
+  MailSlot ms(S.ctx, st);
+  const bool pinned = ms.m && N <= kMailRows;   // larger: the copy through the runtime's own staging buffers
+  int64_t* to = pinned ? ms.m->rowptr : P.rowptr_host.data();
+  ms.idle = false;
+  HIPCHK(hipMemcpyAsync(to, P.rowptr, sizeof(int64_t) * (N + 1), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
+  ms.idle = true;
+  if (pinned) std::memcpy(P.rowptr_host.data(), to, sizeof(int64_t) * (N + 1));
   P.R = P.rowptr_host[N];
   return NQS_OK;
 }
@@ -1747,13 +1795,17 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
   if (N > (int64_t(1) << 31) - 1) return fail(NQS_EUNSUPPORTED, "N too large");
   if ((s = check_supported(ans, opts->precision)) != NQS_OK) return s;
   DeviceGuard g(ctx->device);
-  if ((s = check_samples(ctx, samples, N, inst->K, inst->na, inst->nb, stream, arena)) != NQS_OK) return s;
+  if ((s = check_samples(ctx, samples, N, inst->K, inst->na, inst->nb, stream)) != NQS_OK) return s;
   if (N == 0) {
     if (stats) { std::memset(stats, 0, sizeof *stats); stats->n_conn = inst->H.n_conn; }
     return NQS_OK;
   }
   Scratch S(ctx, stream, arena);
-  hipEvent_t ev[3] = {}, pe[3] = {};
+  MailSlot ms(ctx, stream);
+  if (!ms.m) return fail(NQS_ENOMEM, "workspace allocation failed");
+  Mail* const mail = ms.m;
+  mail->overflow = 0;
+  hipEvent_t ev[3] = {}, pe[4] = {};
   const bool timing = stats != nullptr;
   if (timing) {
     for (auto& e : ev) HIPCHK(hipEventCreate(&e));
@@ -1761,7 +1813,11 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
   }
   struct EvGuard {
     hipEvent_t* a; hipEvent_t* b; bool on;
-    ~EvGuard() { if (on) for (int k = 0; k < 3; ++k) { (void)hipEventDestroy(a[k]); (void)hipEventDestroy(b[k]); } }
+    ~EvGuard() {
+      if (!on) return;
+      for (int k = 0; k < 3; ++k) (void)hipEventDestroy(a[k]);
+      for (int k = 0; k < 4; ++k) (void)hipEventDestroy(b[k]);
+    }
   } evg{ev, pe, timing};
   Pipeline P{};
   if ((s = count_and_draw(S, inst, samples, N, *opts, P, stream, timing ? ev : nullptr)) != NQS_OK) return s;
@@ -1784,7 +1840,6 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
   double* et_i = cx ? (etnum_im ? etnum_im : S.get<double>(N)) : nullptr;
   double* phs = ans->cplx ? S.get<double>(cap_used) : nullptr;
   double* f2 = fsq ? fsq : S.get<double>(N);
-  double* sums = S.get<double>(8);
   const int K = ans->K;
   const bool resume = resumes(*opts) && (!ans->tensor || ans->tn_mfma) && cap_used < (int64_t(1) << 31);
   Resume rs;
@@ -1825,7 +1880,6 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
   int64_t *nent = nullptr, *nslt = nullptr, *nbase = nullptr, *ebase = nullptr, *ntot = nullptr;
   int64_t* sbsum = nullptr;
   NodeRec* nrec = nullptr;
-  int* sover = nullptr;
   uint8_t *row_site = nullptr, *nt0s = nullptr, *ntmp_k = nullptr;
   int32_t* ntmp_p = nullptr;
   int32_t* ncnt_s = nullptr;
@@ -1839,7 +1893,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
     nslt = S.get<int64_t>(max_pass_samples);
     nbase = S.get<int64_t>(max_pass_samples);
     ebase = S.get<int64_t>(max_pass_samples);
-    ntot = S.get<int64_t>(3);
+    ntot = S.get<int64_t>(1);
     nl.m = S.get<uint64_t>(size_t(caps.nodes) * 2);
     nl.owner = S.get<int32_t>(caps.nodes);
     nl.c1 = S.get<uint8_t>(caps.nodes);
@@ -1851,10 +1905,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
     ntmp_k = S.get<uint8_t>(size_t(caps.nodes) * 2);
     nl.need = S.get<uint64_t>(caps.nodes);
     nrec = S.get<NodeRec>(caps.nodes);
-    if (!tn) {
-      sbsum = S.get<int64_t>(slot_blocks(caps.nodes));
-      sover = S.get<int>(1);
-    }
+    if (!tn) sbsum = S.get<int64_t>(slot_blocks(caps.nodes));
     ncnt_s = S.get<int32_t>(size_t(order_blocks(cap_used)) * (K + 1));
     ntot_s = S.get<int64_t>(K + 1);
     lphi_n = S.get<double>(caps.nodes);
@@ -1870,7 +1921,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
     P.rows.sec = S.get<uint32_t>(cap_used);
   }
   if (S.oom) return fail(NQS_ENOMEM, "workspace allocation failed");
-  if (sover) HIPCHK(hipMemsetAsync(sover, 0, sizeof(int), stream));
+  ms.idle = false;
   if (ans->nh) HIPCHK(launch_corr_theta(ans->corr(), samples, N, theta, Etab, opts->precision, stream));
   float ms_rows = 0, ms_amp = 0, ms_red = 0, ms_psi = 0;
   int64_t site_rows = 0;
@@ -1910,7 +1961,26 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
         NQS_OK)
       return s;
   }
+  // times and row counts of the pass queued last, whose events the next one takes
+  bool queued = false;
+  auto pass_times = [&]() -> nqs_status {
+    if (!queued) return NQS_OK;
+    queued = false;
+    HIPCHK(hipEventSynchronize(pe[3]));
+    float t = 0;
+    HIPCHK(hipEventElapsedTime(&t, pe[0], pe[1])); ms_rows += t;
+    HIPCHK(hipEventElapsedTime(&t, pe[1], pe[2])); ms_amp += t;
+    HIPCHK(hipEventElapsedTime(&t, pe[2], pe[3])); ms_red += t;
+    HIPCHK(hipEventElapsedTime(&t, kq[0], kq[1])); ms_psi += t;
+    if (resume)
+      for (int k = 0; k <= K; ++k) {
+        site_rows += mail->tot[k] * (K - k);
+        psi_flops += double(mail->tot[k]) * tail_flops[k];
+      }
+    return NQS_OK;
+  };
   for (auto& pr : passes) {
+    if ((s = pass_times()) != NQS_OK) return s;
     const int64_t n0 = pr.first, n1 = pr.second;
     const int64_t Rp = P.rowptr_host[n1] - P.rowptr_host[n0];
     if (timing) HIPCHK(hipEventRecord(pe[0], stream));
@@ -1924,10 +1994,10 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
         const int64_t ns = n1 - n0, row_base = P.rowptr_host[n0];
         HIPCHK(launch_node_count(P.rows.t0, P.rows.sec, samples, P.rowptr, n0, n1, row_base, K, ans->W, pair, ncnt,
                                  nent, nslt, stream));
-        HIPCHK(launch_node_scan(ns, caps, ncnt, nent, nslt, nbase, ebase, ntot, stream));
-        int64_t tot2[2] = {0, 0};
-        HIPCHK(hipMemcpyAsync(tot2, ntot, sizeof tot2, hipMemcpyDeviceToHost, stream));
+        HIPCHK(launch_node_scan(ns, caps, ncnt, nent, nslt, nbase, ebase, mail->nodes, stream));
         HIPCHK(hipStreamSynchronize(stream));
+        const volatile int64_t* vt = mail->nodes;
+        const int64_t tot2[2] = {vt[0], vt[1]};
         HIPCHK(launch_node_assign(P.rows.t0, P.rows.sec, samples, P.rowptr, n0, n1, row_base, K, ans->W, pair, nbase,
                                   ebase, nl, row_node, row_site, stream));
         const int64_t nn = tot2[0];
@@ -1943,7 +2013,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
           HIPCHK(launch_node_need(rs.perm, rs.t0, Rp, ans->W, row_node, nl.c1, nl.need, stream));
           // node records; carried-state slots only for the sites some row
           // reads (the tensor-term kernels store every site, a slot per entry)
-          HIPCHK(launch_node_records(nl, nn, !tn, scap, sbsum, ntot + 2, nrec, sover, stream));
+          HIPCHK(launch_node_records(nl, nn, !tn, scap, sbsum, ntot, nrec, &mail->overflow, stream));
           // the node pass: resumed from the samples at the changed site, stores compactly
           // node units by changed site, and from chi = 32 on by (changed
           // site, last site): a wavefront starts at its first unit's changed
@@ -1980,15 +2050,8 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
       if ((s = run_amplitudes(ans, opts->precision, P.rows.m, Rp, lphi, sphi, stream, &rs, PSI_SEED, phs)) != NQS_OK)
         return s;
       if (timing) HIPCHK(hipEventRecord(kq[1], stream));
-      if (stats) {
-        std::vector<int64_t> tot(K + 1);
-        HIPCHK(hipMemcpyAsync(tot.data(), rs.tot, sizeof(int64_t) * (K + 1), hipMemcpyDeviceToHost, stream));
-        HIPCHK(hipStreamSynchronize(stream));
-        for (int k = 0; k <= K; ++k) {
-          site_rows += tot[k] * (K - k);
-          psi_flops += double(tot[k]) * tail_flops[k];
-        }
-      }
+      if (stats)   // read with the pass's times
+        HIPCHK(hipMemcpyAsync(mail->tot, rs.tot, sizeof(int64_t) * (K + 1), hipMemcpyDeviceToHost, stream));
     } else {
       if (timing) HIPCHK(hipEventRecord(kq[0], stream));
       if ((s = run_amplitudes(ans, opts->precision, P.rows.m, Rp, lphi, sphi, stream, nullptr, PSI_ROWS, phs)) !=
@@ -2010,35 +2073,23 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
     else
       HIPCHK(launch_reduce(n0, n1, P.rowptr, P.rowptr_host[n0], P.rows.coef, lphi, sphi, lf, sf, P.hdiag, el, et,
                            logabs, sign, f2, stream));
-    if (timing) {
-      hipEvent_t done;
-      HIPCHK(hipEventCreate(&done));
-      HIPCHK(hipEventRecord(done, stream));
-      HIPCHK(hipEventSynchronize(done));
-      float t = 0;
-      HIPCHK(hipEventElapsedTime(&t, pe[0], pe[1])); ms_rows += t;
-      HIPCHK(hipEventElapsedTime(&t, pe[1], pe[2])); ms_amp += t;
-      HIPCHK(hipEventElapsedTime(&t, pe[2], done)); ms_red += t;
-      HIPCHK(hipEventElapsedTime(&t, kq[0], kq[1])); ms_psi += t;
-      (void)hipEventDestroy(done);
-    }
+    if (timing) HIPCHK(hipEventRecord(pe[3], stream));
+    queued = timing;
   }
-  HIPCHK(launch_batch_sums(N, counts, el, et, f2, sums, stream, el_i, et_i));
-  double hs[8] = {0};
-  int slot_overflow = 0;
-  if (stats) HIPCHK(hipMemcpyAsync(hs, sums, sizeof hs, hipMemcpyDeviceToHost, stream));
-  if (sover) HIPCHK(hipMemcpyAsync(&slot_overflow, sover, sizeof(int), hipMemcpyDeviceToHost, stream));
+  if (stats) HIPCHK(launch_batch_sums(N, counts, el, et, f2, P.Dn, P.Un, &mail->sums, stream, el_i, et_i));
   HIPCHK(hipStreamSynchronize(stream));
-  if (slot_overflow) return fail(NQS_EDEVICE, "node state slots exceeded their capacity");
+  ms.idle = true;
+  if (*static_cast<const volatile int32_t*>(&mail->overflow))
+    return fail(NQS_EDEVICE, "node state slots exceeded their capacity");
   if (stats) {
-    std::vector<int64_t> Dn(N), Un(N);
-    HIPCHK(hipMemcpy(Dn.data(), P.Dn, sizeof(int64_t) * N, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(Un.data(), P.Un, sizeof(int64_t) * N, hipMemcpyDeviceToHost));
+    if ((s = pass_times()) != NQS_OK) return s;
+    const double* hs = mail->sums.v;
     std::memset(stats, 0, sizeof *stats);
     stats->n_samples = N;
     stats->n_conn = inst->H.n_conn;
     stats->n_rows = R;
-    for (int64_t n = 0; n < N; ++n) { stats->n_det_rows += Dn[n]; stats->n_draw_rows += Un[n]; }
+    stats->n_det_rows = mail->sums.det_rows;
+    stats->n_draw_rows = mail->sums.draw_rows;
     stats->sum_c = hs[0];
     stats->B = hs[4];
     stats->E = hs[3];
