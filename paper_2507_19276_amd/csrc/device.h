@@ -41,6 +41,43 @@ __device__ inline bool allowed(int a_prev, int b_prev, int s, int rest, int na, 
 // mask of the n lowest bits (n <= 0: none, n >= 64: all)
 __device__ inline uint64_t low_bits(int n) { return n <= 0 ? 0ull : (n >= 64 ? ~0ull : ((1ull << n) - 1ull)); }
 
+// Site of the n-th set bit of a mask with one bit per site (at 2 x site), -1 for
+// n = 0, 64 when there are fewer.
+__device__ inline int nth_site(uint64_t lo, uint64_t hi, int n) {
+  int c = __popcll(lo) + __popcll(hi);
+  if (c < n) return 64;
+  for (; c > n; --c) {   // in-sector rows: never; a node's ONV differs by at most two electrons
+    if (hi) hi &= ~(1ull << (63 - __clzll(hi)));
+    else lo &= ~(1ull << (63 - __clzll(lo)));
+  }
+  if (!(lo | hi)) return -1;
+  return (hi ? 127 - __clzll(hi) : 63 - __clzll(lo)) >> 1;
+}
+
+// The particle-number / S_z mask of a known row.  State s is allowed at site i when
+// fewer than na (nb) electrons, and fewer than K - na (K - nb) holes, of each spin
+// lie before it: up to the site of the na-th electron a further one is allowed,
+// up to that of the (K - na)-th hole a further hole.  Four compares a site, where
+// running counts take two dozen operations.  In psi_tri.h, before and now: chain
+// K = 20 chi = 16 13.9 -> 13.7 ms, complex chain 9.00 -> 8.87, 3x3x2 lattice chi = 64
+// 76.8 -> 76.1, NN+NNN K = 50 (2048 samples) 84.9 -> 84.2.  Not in psi.hip and
+// psi_bf16.hip, whose code came out no faster (FP32 chain 6.99 -> 7.12 ms, BF16 19.67
+// -> 19.81).
+struct SpinEnds {
+  int ae, ah, be, bh;   // last site at which an electron (e) or a hole (h) of the spin is allowed
+  bool bad;             // the row itself lies outside the sector
+  __device__ SpinEnds(uint64_t lo, uint64_t hi, int K, int na, int nb) {
+    const uint64_t A = 0x5555555555555555ull, ml = A & low_bits(2 * K), mh = A & low_bits(2 * K - 64);
+    const uint64_t al = lo & ml, ah_ = hi & mh, bl = (lo >> 1) & ml, bh_ = (hi >> 1) & mh;
+    ae = nth_site(al, ah_, na);
+    ah = nth_site(~al & ml, ~ah_ & mh, K - na);
+    be = nth_site(bl, bh_, nb);
+    bh = nth_site(~bl & ml, ~bh_ & mh, K - nb);
+    bad = __popcll(al) + __popcll(ah_) != na || __popcll(bl) + __popcll(bh_) != nb;
+  }
+  __device__ bool allowed(int i, int s) const { return i <= ((s & 1) ? ae : ah) && i <= ((s & 2) ? be : bh); }
+};
+
 __device__ inline double tlog(double x) { return log(x); }
 __device__ inline float tlog(float x) { return logf(x); }
 

@@ -126,8 +126,8 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
     if (t == own) orow = rowt[t];
   T prod = T(1), prod2 = T(1);   // prod2 (QUAD, STORE 1): with Z summed over the candidates, as psi.hip
   T zr = T(1), zi = T(0);
-  int pexp = 0, pexp2 = 0, sgn = 1, ca = 0, cb = 0;
-  uint64_t badm = 0;   // lanes whose own row took a state its mask forbids
+  int pexp = 0, pexp2 = 0, sgn = 1;
+  const SpinEnds ends(olo, ohi, P.K, P.na, P.nb);
   if (X.perm && i0 > 0) {
     // the states live at i0 and the log-product state before it, from the
     // row's node at the sites the node covers, else from its sample (psi.hip)
@@ -180,9 +180,6 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
         zi = X.pz[2 * so + 1];
       }
     }
-    const uint64_t below = low_bits(2 * i0), belowh = low_bits(2 * i0 - 64);
-    ca = __popcll(olo & below & 0x5555555555555555ull) + __popcll(ohi & belowh & 0x5555555555555555ull);
-    cb = __popcll(olo & below & 0xAAAAAAAAAAAAAAAAull) + __popcll(ohi & belowh & 0xAAAAAAAAAAAAAAAAull);
   }
   int sc1 = 0, se1 = -1;
   int64_t soff = 0;
@@ -245,18 +242,16 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
     uint64_t full, a0, a1, b0, b1;   // state s = a + 2 b is allowed where a's and b's masks have the lane
     uint32_t pt, own;                // own: bit s = s is some row's state
   };
-  auto masks = [&](int i, int a, int b, int s) {
+  auto masks = [&](int i, int s) {
     Masks M;
-    const int rest = P.K - 1 - i;
-    M.a0 = __ballot(a <= P.na && a + rest >= P.na);
-    M.a1 = __ballot(a < P.na && a + 1 + rest >= P.na);
-    M.b0 = __ballot(b <= P.nb && b + rest >= P.nb);
-    M.b1 = __ballot(b < P.nb && b + 1 + rest >= P.nb);
-    const uint64_t sl = __ballot(s & 1), sh = __ballot(s & 2);
+    M.a0 = __builtin_amdgcn_ballot_w64(i <= ends.ah);
+    M.a1 = __builtin_amdgcn_ballot_w64(i <= ends.ae);
+    M.b0 = __builtin_amdgcn_ballot_w64(i <= ends.bh);
+    M.b1 = __builtin_amdgcn_ballot_w64(i <= ends.be);
+    const uint64_t sl = __builtin_amdgcn_ballot_w64((s & 1) != 0), sh = __builtin_amdgcn_ballot_w64(s >= 2);
     M.full = M.a0 & M.a1 & M.b0 & M.b1;
     M.pt = M.full ? 1u : 0u;
     M.own = 0u;
-    uint64_t ok = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const uint64_t st = ((k & 1) ? sl : ~sl) & ((k & 2) ? sh : ~sh);
@@ -264,9 +259,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
       const uint64_t need = QUAD && STORE == 1 ? ~0ull : (st | (QUAD ? al & ~M.full : al));
       M.pt |= need ? 2u << k : 0u;
       M.own |= st ? 1u << k : 0u;
-      ok |= st & al;
     }
-    badm |= ~ok;
     return M;
   };
   // Operands and vectors come through one buffer resource: the lane's part of
@@ -303,7 +296,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
   };
   if (i0 < iend) {
     if (QUAD) fetch_rb(i0);
-    M = masks(i0, ca, cb, site_state(olo, ohi, i0));
+    M = masks(i0, site_state(olo, ohi, i0));
     const int p = QUAD ? first_part(i0, M.pt) : qoff[i0];
 #pragma unroll
     for (int q = 0; q < PW; ++q) an[q] = ld(p + q);
@@ -338,10 +331,8 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
     Masks Mn{};
     int pn = 0;
     auto look_ahead = [&]() {
-      ca += osi & 1;
-      cb += osi >> 1;
       if (i + 1 < iend) {
-        Mn = masks(i + 1, ca, cb, site_state(olo, ohi, i + 1));
+        Mn = masks(i + 1, site_state(olo, ohi, i + 1));
         if (QUAD) pn = first_part(i + 1, Mn.pt);
       }
     };
@@ -634,7 +625,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
   }
   store_pre(iend);
   if (writer && olive) {
-    const bool bad = (badm >> lane) & 1u;
+    const bool bad = ends.bad;
     const T pf = QUAD && STORE == 1 ? prod2 : prod;
     lphi[orow] = bad ? -INFINITY
                      : 0.5 * (log(double(pf)) + double(QUAD && STORE == 1 ? pexp2 : pexp) * 0.69314718055994530942);
