@@ -59,8 +59,10 @@ template <typename T> constexpr int prefetch_ksteps(int CH, bool lean) {
   return pq;
 }
 
+// (FP32 tensor term at chip 16: kept to the registers of two wavefronts per SIMD;
+// two tiles of rows in place of four, three wavefronts: 7.2 against 6.3 ms)
 template <typename T, int CH, int NTL, bool FOLD, int STORE, bool SEED, bool SAMPLE, bool CPLX, bool TN, bool D1>
-__global__ __launch_bounds__(256) void k_psi_mt(PsiParams<T> P, const uint64_t* __restrict__ m, int64_t R,
+__global__ __launch_bounds__(256, TN && sizeof(T) == 4 && CH == 16 ? 2 : 1) void k_psi_mt(PsiParams<T> P, const uint64_t* __restrict__ m, int64_t R,
                                                 double* __restrict__ lphi, int8_t* __restrict__ sphi, int wpb,
                                                 PsiStates<T> X, SampleArgs SA, double* __restrict__ phs) {
   // every floating-point operation below is written out (explicit fma where
@@ -406,38 +408,56 @@ __global__ __launch_bounds__(256) void k_psi_mt(PsiParams<T> P, const uint64_t* 
         const int d = e1 - e0s;
         const T* Ac = P.TA + toC + lane;
         const T* Ak = P.TA + toK + lane;
+        // all tiles of rows together: each operand feeds NTL MFMA pairs, the
+        // operands of the next k-step are in flight meanwhile (past the core's
+        // last: K0's first), and there are 2 NTL independent chains.  Tile after
+        // tile instead, each waiting for its own copies of the operands with two
+        // chains: tensor-RNN K = 20 chi = 16 FP32 row kernel 7.35 ms (MFMA busy
+        // 56%), now 6.30; FP64 16.3 -> 16.0.
+        V q0[NTL], q1[NTL];
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) {
-          const V plast = d == 3 ? pr2[t] : pr1[t];
-          V q0 = V{0, 0, 0, 0}, q1 = V{0, 0, 0, 0};
-          int kk = 0;
+        for (int t = 0; t < NTL; ++t) q0[t] = q1[t] = V{0, 0, 0, 0};
+        int kk = 0;
+        T c0 = Ac[0], c1 = Ac[64];
 #pragma unroll
-          for (int a1 = 0; a1 < 8; ++a1) {
-            if (a1 >= tQ) break;
-            // p_1[a1] from the lane of the row that holds it (a = 2 g + v)
-            const T b0 = __shfl(pr0[t][a1 & 1], j + 16 * (a1 >> 1));
+        for (int a1 = 0; a1 < 8; ++a1) {
+          if (a1 >= tQ) break;
+          // p_1[a1] from the lane of the row that holds it (a = 2 g + v)
+          T b0[NTL];
 #pragma unroll
-            for (int a2 = 0; a2 < 8; ++a2) {
-              if (a2 >= (d == 3 ? tQ : 1)) break;
-              const T f = d == 3 ? b0 * __shfl(pr1[t][a2 & 1], j + 16 * (a2 >> 1)) : b0;
+          for (int t = 0; t < NTL; ++t) b0[t] = __shfl(pr0[t][a1 & 1], j + 16 * (a1 >> 1));
 #pragma unroll
-              for (int v = 0; v < 2; ++v) {
-                const T bv = f * plast[v];
-                q0 = mfma(Ac[(size_t(kk) * 2 + 0) * 64], bv, q0);
-                q1 = mfma(Ac[(size_t(kk) * 2 + 1) * 64], bv, q1);
-                ++kk;
+          for (int a2 = 0; a2 < 8; ++a2) {
+            if (a2 >= (d == 3 ? tQ : 1)) break;
+            T f[NTL];
+#pragma unroll
+            for (int t = 0; t < NTL; ++t) f[t] = d == 3 ? b0[t] * __shfl(pr1[t][a2 & 1], j + 16 * (a2 >> 1)) : b0[t];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+              ++kk;
+              const T n0 = Ac[(size_t(kk) * 2 + 0) * 64], n1 = Ac[(size_t(kk) * 2 + 1) * 64];
+#pragma unroll
+              for (int t = 0; t < NTL; ++t) {
+                const T bv = f[t] * (d == 3 ? pr2[t] : pr1[t])[v];
+                q0[t] = mfma(c0, bv, q0[t]);
+                q1[t] = mfma(c1, bv, q1[t]);
               }
+              c0 = n0;
+              c1 = n1;
             }
           }
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int tt = 0; tt < TPC; ++tt)
-#pragma unroll
-              for (int v = 0; v < 4; ++v)
-                acc[t][s * TPC + tt] =
-                    mfma(Ak[((s * TPC + tt) * 4 + v) * 64], s < 2 ? q0[v] : q1[v], acc[t][s * TPC + tt]);
         }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const T a = Ak[((s * TPC + tt) * 4 + v) * 64];
+#pragma unroll
+              for (int t = 0; t < NTL; ++t)
+                acc[t][s * TPC + tt] = mfma(a, s < 2 ? q0[t][v] : q1[t][v], acc[t][s * TPC + tt]);
+            }
       }
     }
     __builtin_amdgcn_s_setprio(0);
