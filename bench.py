@@ -314,7 +314,7 @@ def run_eloc_bench(args):
                      "frac": achieved / peak,
                      "traffic": args.traffic_bytes if args.traffic_bytes else measured_traffic(head_name, head_prec),
                      "kernel": "row amplitude kernel (bond contractions and conditionals): k_psi_tri in FP64, "
-                               "k_psi_mt in FP32, k_psi_b16 in BF16",
+                               "(and FP32 but for the chip 16 chain: k_psi_mt), k_psi_b16 in BF16",
                      "flops_per_launch": row_flops(hs, wh, head_prec), "ms_per_launch": hs["ms_psi"],
                      "kernel_sha16": kernel_sha16()},
     }
