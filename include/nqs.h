@@ -357,8 +357,9 @@ nqs_status nqs_eloc_workspace_bytes(const nqs_instance* inst, const nqs_ansatz* 
  * capture, serving loops that must not allocate, harnesses that forbid it.
  * The same computation, arguments and results as nqs_eloc (bit for bit),
  * without the stats pointer, with every workspace block taken from the static
- * array above instead of the context's pool: no hipMalloc, hipFree or other
- * allocating call is made.  NQS_ENOMEM with a message when the call needs more
+ * array above instead of the context's pool, and a pinned host block made with
+ * the context: no hipMalloc, hipHostMalloc, hipFree or other allocating call is
+ * made.  NQS_ENOMEM with a message when the call needs more
  * than NQS_STATIC_WORKSPACE_BYTES; with opts->max_rows_per_pass > 0 a call
  * whose nqs_eloc_workspace_bytes is at most that size always fits.  Every
  * call on a GPU shares that GPU's array, which keeps the last call's contents
@@ -494,6 +495,10 @@ nqs_status nqs_ctx_fail_alloc_at(nqs_ctx* ctx, int64_t k);
  * whole samples past a capacity get no nodes and their rows resume at their
  * first changed site, with the same results.  For tests of that path. */
 nqs_status nqs_ctx_set_node_capacity(nqs_ctx* ctx, double scale);
+/* Number of pinned host blocks (through which calls report counts and sums)
+ * that the context has allocated: two when it is created (one of them kept for
+ * nqs_eloc_noalloc), one more for each further call that runs at the same time. */
+nqs_status nqs_ctx_mailboxes(const nqs_ctx* ctx, int64_t* n);
 /* Bytes currently held by the context's workspace pool (in use, cached). */
 nqs_status nqs_ctx_pool_bytes(const nqs_ctx* ctx, size_t* in_use, size_t* cached);
 /* High-water mark of the pool's in-use bytes; reset != 0 restarts it at the

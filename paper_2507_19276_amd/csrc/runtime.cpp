@@ -88,6 +88,8 @@ struct nqs_ctx {
   // in use until the event recorded after that work has completed
   std::vector<std::pair<hipEvent_t, std::vector<void*>>> pending;
   std::vector<void*> mail;                    // idle mailboxes (struct Mail), one made with the context
+  void* mail_noalloc = nullptr;               // the mailbox of nqs_eloc_noalloc, made with the context
+  std::atomic<int64_t> n_mail{0};             // mailboxes made
 
   void free_block_locked(void* p) {
     auto it = sizes.find(p);
@@ -208,6 +210,7 @@ struct nqs_ctx {
     }
     for (auto& kv : sizes) (void)hipFree(kv.first);
     for (void* p : mail) (void)hipHostFree(p);
+    if (mail_noalloc) (void)hipHostFree(mail_noalloc);
   }
 };
 
@@ -226,13 +229,30 @@ struct Mail {
   int64_t rowptr[kMailRows + 1];
 };
 
-// A context's mailbox for one call on one stream.
+void* new_mailbox(nqs_ctx* ctx) {
+  void* p = nullptr;
+  if (hipHostMalloc(&p, sizeof(Mail), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  ++ctx->n_mail;
+  return p;
+}
+
+// A context's mailbox for one call on one stream; a call uses one for all its
+// results.  noalloc: the one kept for nqs_eloc_noalloc, whose calls do not overlap:
+// the idle ones may all be with other calls, and making one more would allocate.
 struct MailSlot {
   nqs_ctx* ctx;
   hipStream_t st;
+  bool noalloc;
   Mail* m = nullptr;
   bool idle = true;   // no queued work writes to it (else the stream is waited for)
-  MailSlot(nqs_ctx* c, hipStream_t s) : ctx(c), st(s) {
+  MailSlot(nqs_ctx* c, hipStream_t s, bool na = false) : ctx(c), st(s), noalloc(na) {
+    if (noalloc) {
+      m = static_cast<Mail*>(ctx->mail_noalloc);
+      return;
+    }
     {
       std::lock_guard<std::mutex> lk(ctx->mu);
       if (!ctx->mail.empty()) {
@@ -240,15 +260,14 @@ struct MailSlot {
         ctx->mail.pop_back();
       }
     }
-    void* p = nullptr;
-    if (!m && hipHostMalloc(&p, sizeof(Mail), hipHostMallocDefault) == hipSuccess) m = static_cast<Mail*>(p);
-    if (!m) (void)hipGetLastError();
+    if (!m) m = static_cast<Mail*>(new_mailbox(ctx));
   }
   MailSlot(const MailSlot&) = delete;
   MailSlot& operator=(const MailSlot&) = delete;
   ~MailSlot() {
     if (!m) return;
     if (!idle) (void)hipStreamSynchronize(st);
+    if (noalloc) return;
     std::lock_guard<std::mutex> lk(ctx->mu);
     ctx->mail.push_back(m);
   }
@@ -727,6 +746,7 @@ nqs_status nqs_ctx_create(int device, nqs_ctx** out) {
   c->arena_err = static_workspace_setup(device);
   if (c->arena_err == hipSuccess) c->arena = static_workspace(device);
   { MailSlot first(c, nullptr); }
+  c->mail_noalloc = new_mailbox(c);
   *out = c;
   return NQS_OK;
 }
@@ -751,6 +771,12 @@ nqs_status nqs_ctx_fail_alloc_at(nqs_ctx* ctx, int64_t k) {
 nqs_status nqs_ctx_set_node_capacity(nqs_ctx* ctx, double scale) {
   if (!ctx || !(scale > 0.0 && scale <= 1.0)) return fail(NQS_EINVAL, "scale must be in (0, 1]");
   ctx->node_cap_scale.store(scale);
+  return NQS_OK;
+}
+
+nqs_status nqs_ctx_mailboxes(const nqs_ctx* ctx, int64_t* n) {
+  if (!ctx || !n) return fail(NQS_EINVAL, "bad arguments");
+  *n = ctx->n_mail.load();
   return NQS_OK;
 }
 
@@ -1249,10 +1275,9 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
 
 namespace {
 
-nqs_status check_samples(nqs_ctx* ctx, const uint64_t* samples, int64_t N, int K, int na, int nb,
+nqs_status check_samples(MailSlot& ms, const uint64_t* samples, int64_t N, int K, int na, int nb,
                          hipStream_t st) {
   if (N == 0) return NQS_OK;
-  MailSlot ms(ctx, st);
   if (!ms.m) return fail(NQS_ENOMEM, "workspace allocation failed");
   volatile int32_t* bad = &ms.m->bad;
   *bad = 0;
@@ -1262,6 +1287,12 @@ nqs_status check_samples(nqs_ctx* ctx, const uint64_t* samples, int64_t N, int K
   ms.idle = true;
   if (*bad) return fail(NQS_EINVAL, "a sample lies outside the (%d,%d) sector of K=%d", na, nb, K);
   return NQS_OK;
+}
+
+nqs_status check_samples(nqs_ctx* ctx, const uint64_t* samples, int64_t N, int K, int na, int nb,
+                         hipStream_t st) {
+  MailSlot ms(ctx, st);
+  return check_samples(ms, samples, N, K, na, nb, st);
 }
 
 // Device state of resumed amplitude rows (FP64/FP32): the samples' carried
@@ -1480,7 +1511,7 @@ int64_t pass_rows_bound(const HamDev& H, const nqs_eloc_opts& o, int64_t total_r
 
 // enumerate + screen + draw + row pointer (host copy); no rows yet
 nqs_status count_and_draw(Scratch& S, const nqs_instance* inst, const uint64_t* samples, int64_t N,
-                          const nqs_eloc_opts& o, Pipeline& P, hipStream_t st, hipEvent_t* ev) {
+                          const nqs_eloc_opts& o, Pipeline& P, MailSlot& ms, hipStream_t st, hipEvent_t* ev) {
   const HamDev& H = inst->H;
   P.G = make_geom(H.n_conn, N);
   int e2 = 0;
@@ -1517,7 +1548,6 @@ nqs_status count_and_draw(Scratch& S, const nqs_instance* inst, const uint64_t* 
   HIPCHK(launch_diag(H, samples, N, P.hdiag, st));
   if (ev) HIPCHK(hipEventRecord(ev[2], st));
   P.rowptr_host.resize(N + 1);
-  MailSlot ms(S.ctx, st);
   const bool pinned = ms.m && N <= kMailRows;   // larger: the copy through the runtime's own staging buffers
   int64_t* to = pinned ? ms.m->rowptr : P.rowptr_host.data();
   ms.idle = false;
@@ -1795,14 +1825,13 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
   if (N > (int64_t(1) << 31) - 1) return fail(NQS_EUNSUPPORTED, "N too large");
   if ((s = check_supported(ans, opts->precision)) != NQS_OK) return s;
   DeviceGuard g(ctx->device);
-  if ((s = check_samples(ctx, samples, N, inst->K, inst->na, inst->nb, stream)) != NQS_OK) return s;
+  MailSlot ms(ctx, stream, arena != nullptr);
+  if ((s = check_samples(ms, samples, N, inst->K, inst->na, inst->nb, stream)) != NQS_OK) return s;
   if (N == 0) {
     if (stats) { std::memset(stats, 0, sizeof *stats); stats->n_conn = inst->H.n_conn; }
     return NQS_OK;
   }
   Scratch S(ctx, stream, arena);
-  MailSlot ms(ctx, stream);
-  if (!ms.m) return fail(NQS_ENOMEM, "workspace allocation failed");
   Mail* const mail = ms.m;
   mail->overflow = 0;
   hipEvent_t ev[3] = {}, pe[4] = {};
@@ -1820,7 +1849,7 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
     }
   } evg{ev, pe, timing};
   Pipeline P{};
-  if ((s = count_and_draw(S, inst, samples, N, *opts, P, stream, timing ? ev : nullptr)) != NQS_OK) return s;
+  if ((s = count_and_draw(S, inst, samples, N, *opts, P, ms, stream, timing ? ev : nullptr)) != NQS_OK) return s;
   const int64_t R = P.R;
   const int64_t cap = std::min<int64_t>(R, pass_rows_bound(inst->H, *opts, R));
   auto passes = plan_passes(P.rowptr_host, cap);
@@ -2330,8 +2359,9 @@ nqs_status nqs_rows(nqs_ctx* ctx, const nqs_instance* inst, const uint64_t* samp
   if ((s = check_samples(ctx, samples, N, inst->K, inst->na, inst->nb, stream)) != NQS_OK) return s;
   if (N == 0) { if (n_rows) *n_rows = 0; return NQS_OK; }
   Scratch S(ctx, stream);
+  MailSlot ms(ctx, stream);
   Pipeline P{};
-  if ((s = count_and_draw(S, inst, samples, N, *opts, P, stream, nullptr)) != NQS_OK) return s;
+  if ((s = count_and_draw(S, inst, samples, N, *opts, P, ms, stream, nullptr)) != NQS_OK) return s;
   const int64_t R = P.R, w = std::min(R, cap);
   if (w > 0) {
     if ((s = alloc_rows(S, P, R, true)) != NQS_OK) return s;

@@ -88,6 +88,7 @@ def lib():
     L.nqs_ctx_destroy.argtypes = [_p]
     L.nqs_ctx_fail_alloc_at.argtypes = [_p, C.c_int64]
     L.nqs_ctx_set_node_capacity.argtypes = [_p, C.c_double]
+    L.nqs_ctx_mailboxes.argtypes = [_p, C.POINTER(C.c_int64)]
     L.nqs_ctx_pool_bytes.argtypes = [_p, C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
     L.nqs_ctx_pool_peak.argtypes = [_p, C.POINTER(C.c_size_t), C.c_int]
     L.nqs_ctx_set_pool_limit.argtypes = [_p, C.c_size_t]
@@ -167,6 +168,11 @@ class Context:
 
     def set_node_capacity(self, scale: float):
         check(lib().nqs_ctx_set_node_capacity(self.h, float(scale)))
+
+    def mailboxes(self) -> int:
+        n = C.c_int64()
+        check(lib().nqs_ctx_mailboxes(self.h, C.byref(n)))
+        return n.value
 
     def pool_bytes(self):
         a, b = C.c_size_t(), C.c_size_t()
