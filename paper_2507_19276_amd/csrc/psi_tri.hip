@@ -19,6 +19,12 @@ __device__ inline double wave_sum(double x) {
   return x;
 }
 
+__device__ inline double wave_max(double x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
+  return x;
+}
+
 __global__ __launch_bounds__(kQrThreads) void k_tri_qr(TriBuild B) {
 #pragma clang fp contract(off)
   __shared__ double v[256];
@@ -46,17 +52,29 @@ __global__ __launch_bounds__(kQrThreads) void k_tri_qr(TriBuild B) {
   for (int k = 0; k < steps; ++k) {
     if (wv == 0) {
       double* a = G + int64_t(k) * rows;
+      // the column times a power of two that brings its largest entry to [1/2, 1):
+      // the squares of entries beyond 1e+-154 would leave the range of a double
+      // (the reflection does not depend on v's length, so no other bit moves)
+      double big = 0.0;
+      for (int r = k + lane; r < rows; r += 64) big = fmax(big, fabs(a[r]));
+      big = wave_max(big);
+      int ex;
+      (void)frexp(big, &ex);
       double ss = 0.0;
-      for (int r = k + lane; r < rows; r += 64) ss = tfma(a[r], a[r], ss);
+      for (int r = k + lane; r < rows; r += 64) {
+        const double x = ldexp(a[r], -ex);
+        v[r] = x;
+        ss = tfma(x, x, ss);
+      }
       ss = wave_sum(ss);
-      const double a0 = a[k], nrm = sqrt(ss);
+      const double a0 = ldexp(a[k], -ex), nrm = sqrt(ss);
       // v = a -+ |a| e_k, H = 1 - tau v v^T with tau = 2 / v^T v
       const double beta = a0 < 0.0 ? nrm : -nrm;
-      for (int r = k + lane; r < rows; r += 64) v[r] = r == k ? a0 - beta : a[r];
       const double vv = 2.0 * (ss - a0 * beta);
       if (lane == 0) {
+        v[k] = a0 - beta;
         s_tau = vv > 0.0 ? 2.0 / vv : 0.0;
-        a[k] = vv > 0.0 ? beta : a0;
+        if (vv > 0.0) a[k] = ldexp(beta, ex);
       }
     }
     __syncthreads();
