@@ -2,6 +2,7 @@
 // libnqs.  Nothing here is part of the C ABI (include/nqs.h).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 
 #include "nqs.h"
@@ -533,11 +534,26 @@ inline int64_t order_blocks(int64_t R) { return (R + kOrderChunk - 1) / kOrderCh
 // (device); perm: [R] rows in (t0, row) order; t0s: [R] t0 of each position.
 hipError_t launch_order_t0(const uint8_t* t0, int64_t R, int K, int32_t* cnt, int64_t* tot, int32_t* perm,
                            uint8_t* t0s, hipStream_t st);
-// Rows of the samples n0 .. n1-1 by (resume site, sample, state there, next
-// changed site); cnt: [n1 - n0][K+1] int32 scratch, tot, perm, t0s as above.
+// How launch_order_rows splits the samples' rows over workgroups: n parts of at
+// most `rows` rows each, for a pass whose largest sample has max_rows rows, within
+// `ints` of count scratch (n = 0: not even one part per sample fits).  A part of
+// kRowPart rows takes about 50 us.
+constexpr int64_t kRowPart = 16384;
+struct RowParts {
+  int64_t n, rows;
+};
+inline RowParts row_parts(int64_t ns, int64_t max_rows, int K, size_t ints) {
+  const int64_t most = int64_t(ints / (size_t(ns) * (K + 1)));
+  RowParts p;
+  p.n = std::min((max_rows + kRowPart - 1) / kRowPart, std::min<int64_t>(most, 65535));
+  p.rows = p.n > 0 ? (max_rows + p.n - 1) / p.n : 0;
+  return p;
+}
+// Rows of the samples n0 .. n1-1 by (resume site, sample, part, state there, next
+// changed site); cnt: [n1 - n0][parts.n][K+1] int32 scratch, tot, perm, t0s as above.
 hipError_t launch_order_rows(const uint8_t* site, const uint64_t* m, const uint64_t* samples, const int64_t* rowptr,
-                             int64_t n0, int64_t n1, int64_t row_base, int64_t R, int K, int32_t* cnt, int64_t* tot,
-                             int32_t* perm, uint8_t* t0s, hipStream_t st);
+                             int64_t n0, int64_t n1, int64_t row_base, int64_t R, const RowParts& parts, int K,
+                             int32_t* cnt, int64_t* tot, int32_t* perm, uint8_t* t0s, hipStream_t st);
 // The node units of ns samples (nbase[s] < 0: none; nn in all) in the order
 // described in order.hip; cnt: [ns] int32 scratch, tot: [1].
 hipError_t launch_order_nodes(const uint8_t* c1, const uint8_t* e1, const int64_t* nbase, const int32_t* ncnt,

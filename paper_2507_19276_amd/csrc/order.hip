@@ -126,24 +126,38 @@ __global__ __launch_bounds__(256) void k_t0_scatter(const uint8_t* __restrict__ 
 // Order of the FP64 rows (psi_tri.h): by resume site, then sample, then the
 // row's state at the resume site and its next changed site after it, so that the
 // rows of a wavefront agree on nearly every site they evaluate.  The rows of
-// a sample are contiguous, so one workgroup per sample counts its rows per
-// resume site (launch 1), the columns are scanned over the samples (k_t0_scan),
-// and the workgroup places its rows with LDS counters over (resume site, state,
-// next change).  Rows with equal keys take their places in any order (LDS
-// atomics): which rows share a wavefront does not change a bit of any.
+// a sample are contiguous, so one workgroup per sample (per kRowPart of its rows
+// where it has more: one workgroup alone took 2 ms over the 572 k rows of an exact
+// K = 50 sample, a fifth of the call) counts its rows per resume site (launch 1),
+// the columns are scanned over the workgroups (k_t0_scan), and the workgroup places
+// its rows with LDS counters over (resume site, state, next change).  Rows with
+// equal keys take their places in any order (LDS atomics): which rows share a
+// wavefront does not change a bit of any.
 constexpr int kRowOrderThreads = 512;
+
+// the rows of part blockIdx.y of sample n0 + blockIdx.x, counted from row_base; the
+// parts of all samples are numbered sample by sample
+__device__ inline int64_t row_part(const int64_t* rowptr, int64_t n0, int64_t row_base, int64_t part_rows,
+                                   int64_t& r0, int64_t& r1) {
+  const int64_t n = n0 + blockIdx.x, end = rowptr[n + 1] - row_base;
+  r0 = rowptr[n] - row_base + int64_t(blockIdx.y) * part_rows;
+  r1 = r0 + part_rows < end ? r0 + part_rows : end;
+  return int64_t(blockIdx.x) * gridDim.y + blockIdx.y;
+}
 
 __global__ __launch_bounds__(kRowOrderThreads) void k_row_count(const uint8_t* __restrict__ site,
                                                                 const int64_t* __restrict__ rowptr, int64_t n0,
-                                                                int64_t row_base, int K, int32_t* __restrict__ cnt) {
+                                                                int64_t row_base, int64_t part_rows, int K,
+                                                                int32_t* __restrict__ cnt) {
   __shared__ int h[65];
   const int tid = threadIdx.x;
   if (tid <= K) h[tid] = 0;
   __syncthreads();
-  const int64_t r1 = rowptr[n0 + blockIdx.x + 1] - row_base;
-  for (int64_t r = rowptr[n0 + blockIdx.x] - row_base + tid; r < r1; r += kRowOrderThreads) atomicAdd(&h[site[r]], 1);
+  int64_t r0, r1;
+  const int64_t part = row_part(rowptr, n0, row_base, part_rows, r0, r1);
+  for (int64_t r = r0 + tid; r < r1; r += kRowOrderThreads) atomicAdd(&h[site[r]], 1);
   __syncthreads();
-  if (tid <= K) cnt[int64_t(blockIdx.x) * (K + 1) + tid] = h[tid];
+  if (tid <= K) cnt[part * (K + 1) + tid] = h[tid];
 }
 
 // LDS bin of a row: (resume site, state there, next changed site)
@@ -166,25 +180,27 @@ __device__ inline int row_bin(int t, uint64_t lo, uint64_t hi, uint64_t nlo, uin
 
 __global__ __launch_bounds__(kRowOrderThreads) void k_row_place(
     const uint8_t* __restrict__ site, const uint64_t* __restrict__ m, const uint64_t* __restrict__ samples,
-    const int64_t* __restrict__ rowptr, int64_t n0, int64_t row_base, int K, const int32_t* __restrict__ off,
-    const int64_t* __restrict__ tot, int32_t* __restrict__ perm, uint8_t* __restrict__ t0s) {
+    const int64_t* __restrict__ rowptr, int64_t n0, int64_t row_base, int64_t part_rows, int K,
+    const int32_t* __restrict__ off, const int64_t* __restrict__ tot, int32_t* __restrict__ perm, uint8_t* __restrict__ t0s) {
   extern __shared__ int bins[];   // [K + 1][4][K + 1], the last site's one bin
   __shared__ int start[65];
   const int tid = threadIdx.x, per = 4 * (K + 1), nbin = K * per + 1;
   const int64_t n = n0 + blockIdx.x;
-  const int64_t r0 = rowptr[n] - row_base, r1 = rowptr[n + 1] - row_base;
+  int64_t r0, r1;
+  const int64_t part = row_part(rowptr, n0, row_base, part_rows, r0, r1);
+  if (r0 >= r1) return;
   const uint64_t nlo = samples[2 * n], nhi = samples[2 * n + 1];
   for (int k = tid; k < nbin; k += kRowOrderThreads) bins[k] = 0;
   if (tid < 64) {
-    // first position of each site: the lower sites' totals and the lower samples' rows
+    // first position of each site: the lower sites' totals and the lower parts' rows
     int64_t a = tid <= K ? tot[tid] : 0;
     const int64_t own = a;
     for (int o = 1; o < 64; o <<= 1) {
       const int64_t x = __shfl_up(a, o);
       if (tid >= o) a += x;
     }
-    if (tid <= K) start[tid] = int(a - own) + off[int64_t(blockIdx.x) * (K + 1) + tid];
-    if (tid == 63 && K == 64) start[64] = int(a) + off[int64_t(blockIdx.x) * 65 + 64];
+    if (tid <= K) start[tid] = int(a - own) + off[part * (K + 1) + tid];
+    if (tid == 63 && K == 64) start[64] = int(a) + off[part * 65 + 64];
   }
   __syncthreads();
   for (int64_t r = r0 + tid; r < r1; r += kRowOrderThreads)
@@ -301,17 +317,17 @@ hipError_t launch_order_t0(const uint8_t* t0, int64_t R, int K, int32_t* cnt, in
 }
 
 hipError_t launch_order_rows(const uint8_t* site, const uint64_t* m, const uint64_t* samples, const int64_t* rowptr,
-                             int64_t n0, int64_t n1, int64_t row_base, int64_t R, int K, int32_t* cnt, int64_t* tot,
-                             int32_t* perm, uint8_t* t0s, hipStream_t st) {
+                             int64_t n0, int64_t n1, int64_t row_base, int64_t R, const RowParts& parts, int K,
+                             int32_t* cnt, int64_t* tot, int32_t* perm, uint8_t* t0s, hipStream_t st) {
   if (R <= 0) return hipSuccess;
-  if (K < 1 || K > 64 || R >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  if (K < 1 || K > 64 || R >= (int64_t(1) << 31) || parts.n < 1 || parts.n > 65535) return hipErrorInvalidValue;
   const int64_t ns = n1 - n0;
-  hipLaunchKernelGGL(k_row_count, dim3(unsigned(ns)), dim3(kRowOrderThreads), 0, st, site, rowptr, n0, row_base, K,
-                     cnt);
-  hipLaunchKernelGGL(k_t0_scan, dim3(unsigned(K + 1)), dim3(256), 0, st, cnt, ns, K, tot);
+  const dim3 grid(unsigned(ns), unsigned(parts.n));
+  hipLaunchKernelGGL(k_row_count, grid, dim3(kRowOrderThreads), 0, st, site, rowptr, n0, row_base, parts.rows, K, cnt);
+  hipLaunchKernelGGL(k_t0_scan, dim3(unsigned(K + 1)), dim3(256), 0, st, cnt, ns * parts.n, K, tot);
   const size_t lds = size_t(K * 4 * (K + 1) + 1) * sizeof(int);
-  hipLaunchKernelGGL(k_row_place, dim3(unsigned(ns)), dim3(kRowOrderThreads), lds, st, site, m, samples, rowptr, n0,
-                     row_base, K, cnt, tot, perm, t0s);
+  hipLaunchKernelGGL(k_row_place, grid, dim3(kRowOrderThreads), lds, st, site, m, samples, rowptr, n0, row_base,
+                     parts.rows, K, cnt, tot, perm, t0s);
   return hipGetLastError();
 }
 

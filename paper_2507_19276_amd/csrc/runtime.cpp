@@ -2031,10 +2031,13 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
                                   ebase, nl, row_node, row_site, stream));
         const int64_t nn = tot2[0];
         // the rows' order first: it fixes which node states the row pass reads.
-        // Its per-sample counts live in the node states' storage, written later.
+        // Its counts live in the node states' storage, written later.
         const size_t nhs_ints = size_t(scap) * ans->chip * (state_bytes(opts->precision) / sizeof(int32_t));
-        if (ans->tri_rows(opts->precision) && size_t(ns) * (K + 1) <= nhs_ints)
-          HIPCHK(launch_order_rows(row_site, P.rows.m, samples, P.rowptr, n0, n1, row_base, Rp, K,
+        int64_t most = 0;
+        for (int64_t n = n0; n < n1; ++n) most = std::max(most, P.rowptr_host[n + 1] - P.rowptr_host[n]);
+        const RowParts parts = row_parts(ns, most, K, nhs_ints);
+        if (ans->tri_rows(opts->precision) && parts.n > 0)
+          HIPCHK(launch_order_rows(row_site, P.rows.m, samples, P.rowptr, n0, n1, row_base, Rp, parts, K,
                                    static_cast<int32_t*>(rs.nhs), rs.tot, rs.perm, rs.t0, stream));
         else
           HIPCHK(launch_order_t0(row_site, Rp, K, rs.cnt, rs.tot, rs.perm, rs.t0, stream));
