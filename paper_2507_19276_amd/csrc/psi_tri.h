@@ -634,10 +634,9 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
   }
 }
 
-template <typename T, int CH, int DM, int STORE, bool CPLX>
+template <typename T, int CH, int NTL, int DM, int STORE, bool CPLX>
 hipError_t run_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
                    const PsiStates<T>& X, double* phs) {
-  constexpr int NTL = sizeof(T) == 8 ? tri_tiles(CH, DM) : tri_tiles32(CH);
   static_assert(NTL <= 4, "the node-need marks assume at most 64 rows per wavefront");
   const size_t per_wave = size_t(P.W) * 16 * NTL * CH * sizeof(T);
   if (per_wave > 160 * 1024) return hipErrorInvalidValue;
@@ -648,24 +647,46 @@ hipError_t run_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lph
   return hipGetLastError();
 }
 
+// FP64: one tile of rows per wavefront in launches of at most kTriOneTileRows rows
+// (one wavefront of one tile per SIMD, 256 CUs x 4): such a launch lasts as long as
+// one wavefront's chain of matrix instructions, which a second tile doubles.  The
+// samples' own pass (STORE 1) evaluates all four candidates besides the triangular
+// factor and is that small up to 16384 samples, so it has this form alone.  One
+// sample at K = 36, NN+NNN, chi = 64, us in psi.hip / with two tiles / with one: own
+// pass 635 / 1340 / 711, its 8 k rows 721 / 654 / 342, its nodes 709 / 801 / 390.
+constexpr int64_t kTriOneTileRows = 16 * 256 * 4;
+template <typename T, int CH, int DM, int STORE, bool CPLX>
+hipError_t run_tri_tiles(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
+                         const PsiStates<T>& X, double* phs) {
+  constexpr int NTL = sizeof(T) == 8 ? tri_tiles(CH, DM) : tri_tiles32(CH);
+  constexpr bool one = sizeof(T) == 8 && NTL > 1;
+  if constexpr (one && STORE == 1) {
+    return run_tri<T, CH, 1, DM, STORE, CPLX>(P, m, R, lphi, sphi, st, X, phs);
+  } else {
+    if constexpr (one)
+      if (R <= kTriOneTileRows) return run_tri<T, CH, 1, DM, STORE, CPLX>(P, m, R, lphi, sphi, st, X, phs);
+    return run_tri<T, CH, NTL, DM, STORE, CPLX>(P, m, R, lphi, sphi, st, X, phs);
+  }
+}
+
 template <typename T, int CH, int DM>
 hipError_t run_tri_modes(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
                          const PsiStates<T>& X, int mode, double* phs) {
   const int store = mode == PSI_STORE ? 1 : (mode == PSI_NODE ? 2 : 0);
   if (phs) {
     switch (store) {
-      case 0: return run_tri<T, CH, DM, 0, true>(P, m, R, lphi, sphi, st, X, phs);
-      case 1: return run_tri<T, CH, DM, 1, true>(P, m, R, lphi, sphi, st, X, phs);
-      default: return run_tri<T, CH, DM, 2, true>(P, m, R, lphi, sphi, st, X, phs);
+      case 0: return run_tri_tiles<T, CH, DM, 0, true>(P, m, R, lphi, sphi, st, X, phs);
+      case 1: return run_tri_tiles<T, CH, DM, 1, true>(P, m, R, lphi, sphi, st, X, phs);
+      default: return run_tri_tiles<T, CH, DM, 2, true>(P, m, R, lphi, sphi, st, X, phs);
     }
   }
   if constexpr (sizeof(T) == 4 && CH == 16 && DM == 1) {
     return hipErrorInvalidValue;   // psi.hip's (tri32 in runtime.cpp)
   } else {
     switch (store) {
-      case 0: return run_tri<T, CH, DM, 0, false>(P, m, R, lphi, sphi, st, X, phs);
-      case 1: return run_tri<T, CH, DM, 1, false>(P, m, R, lphi, sphi, st, X, phs);
-      default: return run_tri<T, CH, DM, 2, false>(P, m, R, lphi, sphi, st, X, phs);
+      case 0: return run_tri_tiles<T, CH, DM, 0, false>(P, m, R, lphi, sphi, st, X, phs);
+      case 1: return run_tri_tiles<T, CH, DM, 1, false>(P, m, R, lphi, sphi, st, X, phs);
+      default: return run_tri_tiles<T, CH, DM, 2, false>(P, m, R, lphi, sphi, st, X, phs);
     }
   }
 }
