@@ -315,7 +315,8 @@ struct PsiStates {
   int64_t ns = 0;                // sample stride
   const int32_t* perm = nullptr; // SEED: [R] row of each position
   const uint8_t* t0 = nullptr;   // SEED: [R] first changed site of each position (ascending)
-  const int32_t* owner = nullptr;// SEED: [rows] sample of each row
+  const int32_t* owner = nullptr;// SEED, ROWS: [rows] sample of each row
+  const uint64_t* samples = nullptr;   // ROWS: [samples][2]
   // one level of shared prefixes (nodes.hip), per node u with record
   // nrec[u]: entry off + k holds the log-product state before site c1 + k
   // (k <= e1 - c1); the carried state after site s (c1 <= s < e1) is in slot

@@ -124,7 +124,15 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
 #pragma unroll
   for (int t = 1; t < NTL; ++t)
     if (t == own) orow = rowt[t];
-  T prod = T(1), prod2 = T(1);   // prod2 (QUAD, STORE 1): with Z summed over the candidates, as psi.hip
+  // QUAD: the samples' own amplitudes have Z summed over the candidates, as psi.hip;
+  // STORE 1: all rows are samples, STORE 3: those that equal their sample
+  bool self = STORE == 1;
+  if constexpr (STORE == 3) {
+    const int64_t o = X.owner[orow];
+    self = olo == X.samples[2 * o] && ohi == X.samples[2 * o + 1];
+  }
+  const bool sums = QUAD && (STORE == 1 || (STORE == 3 && __builtin_amdgcn_ballot_w64(self) != 0));
+  T prod = T(1), prod2 = T(1);   // prod2: with that sum, kept where the wavefront has such a row
   T zr = T(1), zi = T(0);
   int pexp = 0, pexp2 = 0, sgn = 1;
   const SpinEnds ends(olo, ohi, P.K, P.na, P.nb);
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
     for (int k = 0; k < 4; ++k) {
       const uint64_t st = ((k & 1) ? sl : ~sl) & ((k & 2) ? sh : ~sh);
       const uint64_t al = ((k & 1) ? M.a1 : M.a0) & ((k & 2) ? M.b1 : M.b0);
-      const uint64_t need = QUAD && STORE == 1 ? ~0ull : (st | (QUAD ? al & ~M.full : al));
+      const uint64_t need = sums ? ~0ull : (st | (QUAD ? al & ~M.full : al));
       M.pt |= need ? 2u << k : 0u;
       M.own |= st ? 1u << k : 0u;
     }
@@ -605,7 +613,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
     int ex;
     prod = tfrexp(prod * (pc / (QUAD && ((M.full >> lane) & 1u) ? Z : Zs)), &ex);
     pexp += ex;
-    if (QUAD && STORE == 1) {
+    if (sums) {
       prod2 = tfrexp(prod2 * (pc / Zs), &ex);
       pexp2 += ex;
     }
@@ -626,9 +634,9 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
   store_pre(iend);
   if (writer && olive) {
     const bool bad = ends.bad;
-    const T pf = QUAD && STORE == 1 ? prod2 : prod;
-    lphi[orow] = bad ? -INFINITY
-                     : 0.5 * (log(double(pf)) + double(QUAD && STORE == 1 ? pexp2 : pexp) * 0.69314718055994530942);
+    const bool two = QUAD && self;
+    const T pf = two ? prod2 : prod;
+    lphi[orow] = bad ? -INFINITY : 0.5 * (log(double(pf)) + double(two ? pexp2 : pexp) * 0.69314718055994530942);
     sphi[orow] = int8_t(bad ? 0 : sgn);
     if (CPLX) phs[orow] = bad ? 0.0 : atan2(double(zi), double(zr));
   }
@@ -672,12 +680,16 @@ hipError_t run_tri_tiles(const TriParams& P, const uint64_t* m, int64_t R, doubl
 template <typename T, int CH, int DM>
 hipError_t run_tri_modes(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
                          const PsiStates<T>& X, int mode, double* phs) {
-  const int store = mode == PSI_STORE ? 1 : (mode == PSI_NODE ? 2 : 0);
+  // (FP32 rows have one form of Z)
+  const int store = mode == PSI_STORE ? 1 : (mode == PSI_NODE ? 2 : (mode == PSI_ROWS && sizeof(T) == 8 ? 3 : 0));
   if (phs) {
     switch (store) {
       case 0: return run_tri_tiles<T, CH, DM, 0, true>(P, m, R, lphi, sphi, st, X, phs);
       case 1: return run_tri_tiles<T, CH, DM, 1, true>(P, m, R, lphi, sphi, st, X, phs);
-      default: return run_tri_tiles<T, CH, DM, 2, true>(P, m, R, lphi, sphi, st, X, phs);
+      case 2: return run_tri_tiles<T, CH, DM, 2, true>(P, m, R, lphi, sphi, st, X, phs);
+      default:
+        if constexpr (sizeof(T) == 8) return run_tri_tiles<T, CH, DM, 3, true>(P, m, R, lphi, sphi, st, X, phs);
+        return hipErrorInvalidValue;
     }
   }
   if constexpr (sizeof(T) == 4 && CH == 16 && DM == 1) {
@@ -686,7 +698,10 @@ hipError_t run_tri_modes(const TriParams& P, const uint64_t* m, int64_t R, doubl
     switch (store) {
       case 0: return run_tri_tiles<T, CH, DM, 0, false>(P, m, R, lphi, sphi, st, X, phs);
       case 1: return run_tri_tiles<T, CH, DM, 1, false>(P, m, R, lphi, sphi, st, X, phs);
-      default: return run_tri_tiles<T, CH, DM, 2, false>(P, m, R, lphi, sphi, st, X, phs);
+      case 2: return run_tri_tiles<T, CH, DM, 2, false>(P, m, R, lphi, sphi, st, X, phs);
+      default:
+        if constexpr (sizeof(T) == 8) return run_tri_tiles<T, CH, DM, 3, false>(P, m, R, lphi, sphi, st, X, phs);
+        return hipErrorInvalidValue;
     }
   }
 }

@@ -183,6 +183,7 @@ hipError_t dispatch_tri(const TriParams& P, const uint64_t* m, int64_t R, double
   if (mode == PSI_STORE || mode == PSI_ROWS) X.perm = nullptr;   // the kernel takes a null order as rows from site 0
   const bool resumed = mode == PSI_SEED || mode == PSI_NODE;
   if ((mode == PSI_STORE && !X.pm) || (resumed && !X.perm)) return hipErrorInvalidValue;
+  if (mode == PSI_ROWS && sizeof(T) == 8 && (!X.owner || !X.samples)) return hipErrorInvalidValue;
   if (phs && (!P.c2 || ((resumed || mode == PSI_STORE) && !X.pz) ||
               (((resumed && X.unode) || mode == PSI_NODE) && !X.npz)))
     return hipErrorInvalidValue;

@@ -1311,6 +1311,7 @@ struct Resume {
   int32_t* cnt = nullptr;   // [order blocks][K+1]
   int64_t* tot = nullptr;   // [K+1]
   const int32_t* owner = nullptr;
+  const uint64_t* samples = nullptr;   // rows from site 0: [samples][2]
   // one node level (FP64/FP32): node storage and the rows' nodes
   void* nhs = nullptr;      // [entries][chip] T
   void* nlp = nullptr;      // [entries] LogProd<T> (16 bytes)
@@ -1331,6 +1332,7 @@ PsiStates<T> states(const Resume& r) {
   X.perm = r.perm;
   X.t0 = r.t0;
   X.owner = r.owner;
+  X.samples = r.samples;
   X.nhs = static_cast<T*>(r.nhs);
   X.nlp = static_cast<LogProd<T>*>(r.nlp);
   X.npz = static_cast<T*>(r.npz);
@@ -1363,7 +1365,8 @@ size_t state_bytes(int precision) { return precision == NQS_F64 ? 8 : (precision
 size_t mantissa_bytes(int precision) { return precision == NQS_F64 ? 8 : 4; }
 
 // amplitudes of R rows into (lphi, sphi).  mode PSI_STORE (samples, with rs)
-// or PSI_SEED (rows of a pass, with rs and its order).  The rows of a local
+// or PSI_SEED (rows of a pass, with rs and its order) or PSI_ROWS (rows of a pass from
+// site 0, with their samples in rs).  The rows of a local
 // energy (every mode but PLAIN) take the triangular normaliser in FP64 where
 // there is one; the amplitudes that PLAIN and STORE return for samples are those
 // of the four-candidate sum, as the sampler's.
@@ -1371,7 +1374,7 @@ size_t mantissa_bytes(int precision) { return precision == NQS_F64 ? 8 : 4; }
 nqs_status run_amplitudes(const nqs_ansatz* a, int precision, const uint64_t* m, int64_t R, double* lphi,
                           int8_t* sphi, hipStream_t st, const Resume* rs = nullptr, int mode = PSI_PLAIN,
                           double* phs = nullptr) {
-  if (mode != PSI_PLAIN && mode != PSI_ROWS && !rs) return fail(NQS_EINVAL, "resume state missing");
+  if (mode != PSI_PLAIN && !rs) return fail(NQS_EINVAL, "resume state missing");
   if (a->cplx && !phs) return fail(NQS_EINVAL, "complex amplitudes need their phases");
   if (precision == NQS_F64 && a->tri && mode != PSI_PLAIN) {
     HIPCHK(launch_psi_tri(a->tri_params(), m, R, lphi, sphi, st, rs ? states<double>(*rs) : PsiStates<double>(), mode,
@@ -1383,7 +1386,10 @@ nqs_status run_amplitudes(const nqs_ansatz* a, int precision, const uint64_t* m,
                           a->cplx ? phs : nullptr));
     return NQS_OK;
   }
-  if (mode == PSI_ROWS) mode = PSI_PLAIN;
+  if (mode == PSI_ROWS) {
+    mode = PSI_PLAIN;
+    rs = nullptr;
+  }
   if (a->cplx) {
     if (precision == NQS_F64) {
       HIPCHK(launch_psi_f64(a->params(a->fwd64()), m, R, lphi, sphi, st,
@@ -1980,16 +1986,6 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
       ms_amp += t;
     }
   }
-  if (tri && !resume) {
-    // the samples' own amplitudes (run_amplitudes), kept in outputs that the
-    // reduction writes after it has read them
-    lphi_s = f2;
-    sphi_s = reinterpret_cast<int8_t*>(et) + 7 * N;   // above what earlier passes' reductions write
-    phs_s = ans->cplx ? el : nullptr;
-    if ((s = run_amplitudes(ans, opts->precision, samples, N, lphi_s, sphi_s, stream, nullptr, PSI_PLAIN, phs_s)) !=
-        NQS_OK)
-      return s;
-  }
   // times and row counts of the pass queued last, whose events the next one takes
   bool queued = false;
   auto pass_times = [&]() -> nqs_status {
@@ -2086,15 +2082,16 @@ nqs_status eloc_run(nqs_ctx* ctx, const nqs_instance* inst, const nqs_ansatz* an
         HIPCHK(hipMemcpyAsync(mail->tot, rs.tot, sizeof(int64_t) * (K + 1), hipMemcpyDeviceToHost, stream));
     } else {
       if (timing) HIPCHK(hipEventRecord(kq[0], stream));
-      if ((s = run_amplitudes(ans, opts->precision, P.rows.m, Rp, lphi, sphi, stream, nullptr, PSI_ROWS, phs)) !=
-          NQS_OK)
+      rs.owner = P.rows.owner;
+      rs.samples = samples;
+      if ((s = run_amplitudes(ans, opts->precision, P.rows.m, Rp, lphi, sphi, stream, &rs, PSI_ROWS, phs)) != NQS_OK)
         return s;
       if (timing) HIPCHK(hipEventRecord(kq[1], stream));
       site_rows += Rp * K;
       psi_flops += double(Rp) * tail_flops[0];
     }
     if (timing) HIPCHK(hipEventRecord(pe[2], stream));
-    if (tri)
+    if (tri && resume)
       HIPCHK(launch_own_rows(n0, n1, P.rowptr, P.rowptr_host[n0], lphi_s, sphi_s, phs_s, lphi, sphi, phs, stream));
     if (ans->nh)
       HIPCHK(launch_corr_rows(ans->corr(), P.rows.m, P.rows.owner, samples, theta, Etab, Rp, opts->precision, lf,
