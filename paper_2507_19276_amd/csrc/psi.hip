@@ -262,11 +262,12 @@ __global__ __launch_bounds__(256, TN && sizeof(T) == 4 && CH == 16 ? 2 : 1) void
     }
     iend = __builtin_amdgcn_readfirstlane(em < P.K ? em : P.K);
   }
-  // Resumed rows at chip 16 (a candidate is one output tile): the candidates that
-  // the particle-number mask forbids to every row of the wavefront are left out.
-  // (K = 20, chi = 16, FP32: tensor-RNN 10.30 -> 10.09 ms, chain 7.00 -> 6.95, an
-  // optimisation step with the Ising-RBM 6.07 -> 6.01.)
-  constexpr bool SKIP = TPC == 1 && SEED && !SAMPLE && PQ == KS;
+  // Resumed rows of the tensor term at chip 16 in FP32 (a candidate is one output
+  // tile): the candidates that the particle-number mask forbids to every row of the
+  // wavefront are left out.  (Row kernel, K = 20 NN+NNN chi = 16: FP32 6.78 -> 6.61
+  // ms.  Elsewhere the branches cost more than they save: FP64 16.58 -> 16.94 ms, the
+  // FP32 chain without the term 4.48 -> 4.57.)
+  constexpr bool SKIP = TN && sizeof(T) == 4 && TPC == 1 && SEED && !SAMPLE && PQ == KS;
   for (int i = i0; i < iend; ++i) {
     store_pre(i);
     const int wslot = wsl[i];
