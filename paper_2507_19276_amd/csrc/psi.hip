@@ -409,56 +409,75 @@ __global__ __launch_bounds__(256, TN && sizeof(T) == 4 && CH == 16 ? 2 : 1) void
         const int d = e1 - e0s;
         const T* Ac = P.TA + toC + lane;
         const T* Ak = P.TA + toK + lane;
-        // all tiles of rows together: each operand feeds NTL MFMA pairs, the
-        // operands of the next k-step are in flight meanwhile (past the core's
-        // last: K0's first), and there are 2 NTL independent chains.  Tile after
-        // tile instead, each waiting for its own copies of the operands with two
-        // chains: tensor-RNN K = 20 chi = 16 FP32 row kernel 7.35 ms (MFMA busy
-        // 56%), now 6.30; FP64 16.3 -> 16.0.
-        V q0[NTL], q1[NTL];
+        // The tiles go G at a time.  All together, each operand feeds NTL MFMA pairs,
+        // the operands of the next k-step are in flight meanwhile (past the core's
+        // last: K0's first), and there are 2 NTL independent chains; but FP64 sites
+        // with two parents, whose cores are short, go tile after tile, each loading
+        // its operands where it uses them.  (Row kernels, tile after tile and together:
+        // K = 20 NN+NNN chi = 16 FP32 7.87 and 6.61 ms, FP64 15.1 and 16.5; 3x3x2 lattice
+        // chi = 16, most sites with three parents, FP32 3.40 and 2.55, FP64 6.36 and
+        // 4.88.)
+        auto core = [&](auto gc) {
+          constexpr int G = decltype(gc)::value;
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) q0[t] = q1[t] = V{0, 0, 0, 0};
-        int kk = 0;
-        T c0 = Ac[0], c1 = Ac[64];
+          for (int t0 = 0; t0 < NTL; t0 += G) {
+            V q0[G], q1[G];
 #pragma unroll
-        for (int a1 = 0; a1 < 8; ++a1) {
-          if (a1 >= tQ) break;
-          // p_1[a1] from the lane of the row that holds it (a = 2 g + v)
-          T b0[NTL];
+            for (int t = 0; t < G; ++t) q0[t] = q1[t] = V{0, 0, 0, 0};
+            int kk = 0;
+            T c0 = Ac[0], c1 = Ac[64];
 #pragma unroll
-          for (int t = 0; t < NTL; ++t) b0[t] = __shfl(pr0[t][a1 & 1], j + 16 * (a1 >> 1));
+            for (int a1 = 0; a1 < 8; ++a1) {
+              if (a1 >= tQ) break;
+              // p_1[a1] from the lane of the row that holds it (a = 2 g + v)
+              T b0[G];
 #pragma unroll
-          for (int a2 = 0; a2 < 8; ++a2) {
-            if (a2 >= (d == 3 ? tQ : 1)) break;
-            T f[NTL];
+              for (int t = 0; t < G; ++t) b0[t] = __shfl(pr0[t0 + t][a1 & 1], j + 16 * (a1 >> 1));
 #pragma unroll
-            for (int t = 0; t < NTL; ++t) f[t] = d == 3 ? b0[t] * __shfl(pr1[t][a2 & 1], j + 16 * (a2 >> 1)) : b0[t];
+              for (int a2 = 0; a2 < 8; ++a2) {
+                if (a2 >= (d == 3 ? tQ : 1)) break;
+                T f[G];
 #pragma unroll
-            for (int v = 0; v < 2; ++v) {
-              ++kk;
-              const T n0 = Ac[(size_t(kk) * 2 + 0) * 64], n1 = Ac[(size_t(kk) * 2 + 1) * 64];
+                for (int t = 0; t < G; ++t)
+                  f[t] = d == 3 ? b0[t] * __shfl(pr1[t0 + t][a2 & 1], j + 16 * (a2 >> 1)) : b0[t];
 #pragma unroll
-              for (int t = 0; t < NTL; ++t) {
-                const T bv = f[t] * (d == 3 ? pr2[t] : pr1[t])[v];
-                q0[t] = mfma(c0, bv, q0[t]);
-                q1[t] = mfma(c1, bv, q1[t]);
+                for (int v = 0; v < 2; ++v) {
+                  if (G == 1) {
+                    c0 = Ac[(size_t(kk) * 2 + 0) * 64];
+                    c1 = Ac[(size_t(kk) * 2 + 1) * 64];
+                  }
+                  ++kk;
+                  T n0 = c0, n1 = c1;
+                  if (G > 1) {
+                    n0 = Ac[(size_t(kk) * 2 + 0) * 64];
+                    n1 = Ac[(size_t(kk) * 2 + 1) * 64];
+                  }
+#pragma unroll
+                  for (int t = 0; t < G; ++t) {
+                    const T bv = f[t] * (d == 3 ? pr2[t0 + t] : pr1[t0 + t])[v];
+                    q0[t] = mfma(c0, bv, q0[t]);
+                    q1[t] = mfma(c1, bv, q1[t]);
+                  }
+                  c0 = n0;
+                  c1 = n1;
+                }
               }
-              c0 = n0;
-              c1 = n1;
             }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+              for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                  const T a = Ak[((s * TPC + tt) * 4 + v) * 64];
+#pragma unroll
+                  for (int t = 0; t < G; ++t)
+                    acc[t0 + t][s * TPC + tt] = mfma(a, s < 2 ? q0[t][v] : q1[t][v], acc[t0 + t][s * TPC + tt]);
+                }
           }
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int tt = 0; tt < TPC; ++tt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const T a = Ak[((s * TPC + tt) * 4 + v) * 64];
-#pragma unroll
-              for (int t = 0; t < NTL; ++t)
-                acc[t][s * TPC + tt] = mfma(a, s < 2 ? q0[t][v] : q1[t][v], acc[t][s * TPC + tt]);
-            }
+        };
+        if (sizeof(T) == 8 && d != 3) core(std::integral_constant<int, 1>{});
+        else core(std::integral_constant<int, NTL>{});
       }
     }
     __builtin_amdgcn_s_setprio(0);
