@@ -225,8 +225,9 @@ int64_t nqs_ansatz_n_params(const nqs_ansatz* ans);
  * doubles) into the library's kernel layouts for every precision.  The caller's
  * buffer may be freed or changed afterwards; call again after an update.
  * EINVAL if some eta < 0 or NaN (nothing changes then).  A failure after the
- * old layouts were released (device memory) leaves the ansatz unbound: every
- * call refuses it with EINVAL until a bind succeeds. */
+ * old layouts were given up (device memory) leaves the ansatz unbound: every
+ * call refuses it with EINVAL until a bind succeeds.  Work queued before a
+ * failure has completed when the call returns. */
 nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStream_t stream);
 
 /* log|Psi(n)| (device double[N]) and sign Psi(n) (device int8[N]) of N samples.
@@ -487,8 +488,9 @@ nqs_status nqs_serve_info(nqs_server* srv, nqs_serve_status* out);
 
 /* ---- test hooks --------------------------------------------------------- */
 
-/* Make the k-th subsequent workspace allocation of this context fail with
- * NQS_ENOMEM (k >= 1; 0 disables).  For failure-handling tests. */
+/* Make the k-th subsequent device allocation of this context fail with
+ * NQS_ENOMEM (k >= 1; 0 disables): workspace blocks, and the layouts that the
+ * first bind of an ansatz allocates.  For failure-handling tests. */
 nqs_status nqs_ctx_fail_alloc_at(nqs_ctx* ctx, int64_t k);
 /* Scale the node storage capacities of this context's later local-energy
  * calls by scale (0 < scale <= 1; 1 restores them; NQS_EINVAL otherwise):

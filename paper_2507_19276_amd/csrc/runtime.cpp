@@ -124,10 +124,16 @@ struct nqs_ctx {
     free_blocks.clear();
     cached = 0;
   }
+  // the test hook: whether this allocation is the one to fail
+  bool fail_now_locked() { return fail_at > 0 && --fail_at == 0; }
+  bool fail_now() {
+    std::lock_guard<std::mutex> lk(mu);
+    return fail_now_locked();
+  }
   void* acquire(size_t bytes) {
     bytes = size_class(bytes);
     std::lock_guard<std::mutex> lk(mu);
-    if (fail_at > 0 && --fail_at == 0) return nullptr;
+    if (fail_now_locked()) return nullptr;
     if (!pending.empty()) reclaim_locked(false);
     auto it = free_blocks.find(bytes);
     if (it != free_blocks.end()) {
@@ -624,9 +630,12 @@ nqs_status build_ta(nqs_ansatz* a, const std::vector<double>& prm, PsiLayout<T>&
   return upload(&L.TA, TA);
 }
 
+// a layout's buffer, allocated by the first bind that needs it
 template <typename T>
-nqs_status ensure(T** p, int64_t n) {
-  if (!*p) HIPCHK(hipMalloc((void**)p, size_t(std::max<int64_t>(n, 1)) * sizeof(T)));
+nqs_status ensure(nqs_ctx* ctx, T** p, int64_t n) {
+  if (*p) return NQS_OK;
+  if (ctx->fail_now()) return fail(NQS_ENOMEM, "parameter layout allocation failed");
+  HIPCHK(hipMalloc((void**)p, size_t(std::max<int64_t>(n, 1)) * sizeof(T)));
   return NQS_OK;
 }
 
@@ -640,16 +649,16 @@ nqs_status pack_layout(nqs_ansatz* a, PackParams P, PsiLayout<T>& L, bool fold, 
   const int64_t ES = int64_t(a->chip / 4) * (a->chip / 4) * 64, ne = a->pptr[a->K], K = a->K, CH = a->chip;
   nqs_status s;
   L.folded = fold;
-  if ((s = ensure(&L.A, (P.n_fwd + 1) * ES)) != NQS_OK) return s;
-  if ((s = ensure(&L.v, K * 4 * CH)) != NQS_OK) return s;
-  if ((s = ensure(&L.eta, K * CH)) != NQS_OK) return s;
-  if ((s = ensure(&L.w, K * CH)) != NQS_OK) return s;
-  if ((s = ensure(&L.c, K)) != NQS_OK) return s;
-  if (a->cplx && (s = ensure(&L.w2, K * CH)) != NQS_OK) return s;
-  if (a->cplx && (s = ensure(&L.c2, K)) != NQS_OK) return s;
+  if ((s = ensure(a->ctx, &L.A, (P.n_fwd + 1) * ES)) != NQS_OK) return s;
+  if ((s = ensure(a->ctx, &L.v, K * 4 * CH)) != NQS_OK) return s;
+  if ((s = ensure(a->ctx, &L.eta, K * CH)) != NQS_OK) return s;
+  if ((s = ensure(a->ctx, &L.w, K * CH)) != NQS_OK) return s;
+  if ((s = ensure(a->ctx, &L.c, K)) != NQS_OK) return s;
+  if (a->cplx && (s = ensure(a->ctx, &L.w2, K * CH)) != NQS_OK) return s;
+  if (a->cplx && (s = ensure(a->ctx, &L.c2, K)) != NQS_OK) return s;
   if (!fold) {
-    if ((s = ensure(&L.AF, ne * ES)) != NQS_OK) return s;
-    if ((s = ensure(&L.BT, ne * ES)) != NQS_OK) return s;
+    if ((s = ensure(a->ctx, &L.AF, ne * ES)) != NQS_OK) return s;
+    if ((s = ensure(a->ctx, &L.BT, ne * ES)) != NQS_OK) return s;
     if (!L.afoff) {
       std::vector<int64_t> off(K);
       for (int i = 0; i < a->K; ++i) off[i] = a->pptr[i] * ES;
@@ -1180,11 +1189,12 @@ nqs_status nqs_ansatz_destroy(nqs_ansatz* ans) {
 
 int64_t nqs_ansatz_n_params(const nqs_ansatz* ans) { return ans ? ans->n_params : -1; }
 
-nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStream_t stream) {
-  if (!ans || !params) return fail(NQS_EINVAL, "NULL argument");
-  DeviceGuard g(ans->ctx->device);
+}  // extern "C"
+
+namespace {
+nqs_status bind_layouts(nqs_ansatz* ans, const double* params, hipStream_t stream) {
   nqs_status st;
-  if ((st = ensure(&ans->d_flags, 3)) != NQS_OK) return st;
+  if ((st = ensure(ans->ctx, &ans->d_flags, 3)) != NQS_OK) return st;
   // eta of the caller's vector: cx_offEta for complex parameters (chi_c units)
   const int64_t* off_eta = ans->cplx ? ans->d_cx + 5 * ans->K : ans->d_offEta;
   HIPCHK(launch_check_params(ans->K, ans->chi_c, off_eta, params, ans->n_params, ans->d_flags, stream));
@@ -1204,7 +1214,7 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
   ans->bound = false;
   const double* prm = params;
   if (ans->cplx) {
-    if ((st = ensure(&ans->d_real, ans->nr_params)) != NQS_OK) return st;
+    if ((st = ensure(ans->ctx, &ans->d_real, ans->nr_params)) != NQS_OK) return st;
     HIPCHK(launch_realify(ans->cxmap(), ans->K, params, ans->d_real, stream));
     prm = ans->d_real;
   }
@@ -1237,17 +1247,17 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
   if (!ans->cplx) {
     P.fold = ans->has_fold;
     const int64_t n = bf16_edge_values(ans->chip) * (ans->n_fwd + 1);
-    if ((st = ensure(&ans->bfA, n)) != NQS_OK) return st;
-    if ((st = ensure(&ans->bfAlo, n)) != NQS_OK) return st;
+    if ((st = ensure(ans->ctx, &ans->bfA, n)) != NQS_OK) return st;
+    if ((st = ensure(ans->ctx, &ans->bfAlo, n)) != NQS_OK) return st;
     HIPCHK(launch_pack_bf16(P, ans->bfA, ans->bfAlo, stream));
   }
   if (ans->nh) {
     const int64_t nh = ans->nh, nv = 2 * ans->K;
-    if ((st = ensure(&ans->d_cb, nh)) != NQS_OK) return st;
-    if ((st = ensure(&ans->d_cW, nh * nv)) != NQS_OK) return st;
-    if ((st = ensure(&ans->d_cW1t, nh * nv)) != NQS_OK) return st;
-    if (ans->ising && (st = ensure(&ans->d_cS, nv * nv * nh)) != NQS_OK) return st;
-    if (ans->ising && (st = ensure(&ans->d_cS32, nv * nv * nh)) != NQS_OK) return st;
+    if ((st = ensure(ans->ctx, &ans->d_cb, nh)) != NQS_OK) return st;
+    if ((st = ensure(ans->ctx, &ans->d_cW, nh * nv)) != NQS_OK) return st;
+    if ((st = ensure(ans->ctx, &ans->d_cW1t, nh * nv)) != NQS_OK) return st;
+    if (ans->ising && (st = ensure(ans->ctx, &ans->d_cS, nv * nv * nh)) != NQS_OK) return st;
+    if (ans->ising && (st = ensure(ans->ctx, &ans->d_cS32, nv * nv * nh)) != NQS_OK) return st;
     HIPCHK(hipMemcpyAsync(ans->d_cb, prm + ans->offB, size_t(nh) * sizeof(double), hipMemcpyDeviceToDevice, stream));
     HIPCHK(hipMemcpyAsync(ans->d_cW, prm + ans->offWc, size_t(nh * nv) * sizeof(double), hipMemcpyDeviceToDevice,
                           stream));
@@ -1270,8 +1280,20 @@ nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStre
   ans->bound = true;
   return NQS_OK;
 }
+}  // namespace
 
-}  // extern "C"
+extern "C" nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStream_t stream) {
+  if (!ans || !params) return fail(NQS_EINVAL, "NULL argument");
+  DeviceGuard g(ans->ctx->device);
+  const nqs_status st = bind_layouts(ans, params, stream);
+  if (st != NQS_OK) {
+    // kernels queued before the failure read the caller's vector and write the
+    // layouts, which a later bind on another stream writes in place
+    (void)hipStreamSynchronize(stream);
+    (void)hipGetLastError();
+  }
+  return st;
+}
 
 namespace {
 
