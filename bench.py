@@ -70,15 +70,34 @@ def kernel_sha16():
     return h.hexdigest()[:16]
 
 
-def row_flops(st, w, prec):
-    """Flops of the row kernel: st["psi_flops"] counts four candidates per site
-    (8 chi^2 d); FP64 rows need their own candidate and the triangular factor
-    of the four (2 chi^2 d + (chi d)^2) where every site has at most three
-    parents and there is no tensor term."""
-    d = [int(b - a) for a, b in zip(w.parent_ptr[:-1], w.parent_ptr[1:])]
-    if prec != "f64" or w.tensor or max(d) > 3:
-        return st["psi_flops"]
-    return st["psi_flops"] * sum(2 * x + x * x for x in d) / sum(8 * x for x in d)
+def row_roofline(st, w, ans, prec):
+    """Roofline of the row kernel's launches.  st["psi_flops"] counts four
+    candidates per site (8 chi^2 d at d parents).  k_psi_tri<double> needs of them
+    the own candidate and the triangular factor (2 chi^2 d + (chi d)^2, (2 + d) / 8
+    of it): exact where the sites from the third on, at which rows resume, have
+    equally many parents, else with the fewest: a lower bound.  k_psi_tri<float>
+    leaves out the candidates forbidden to a whole wavefront, whose number is not
+    known here: its rate in four-candidate flops is given and no fraction."""
+    kernel = ans.row_kernel(prec)
+    fl = st["psi_flops"]
+    r = {"bound": "mfma", "peak": PEAKS[prec], "unit": "TFLOP/s", "kernel": kernel, "ms_per_launch": st["ms_psi"],
+         "four_candidate_tflops": fl / (st["ms_psi"] * 1e-3) / 1e12}
+    if kernel == "k_psi_tri<float>":
+        return {**r, "achieved": None, "frac": None, "flops_per_launch": None,
+                "note": "candidates forbidden to a whole wavefront are left out"}
+    if kernel == "k_psi_tri<double>":
+        d = [int(b - a) for a, b in zip(w.parent_ptr[:-1], w.parent_ptr[1:])][2:]
+        fl *= (2 + min(d)) / 8
+        if min(d) != max(d):
+            r["note"] = "lower bound (sites of different in-degree)"
+    achieved = fl / (st["ms_psi"] * 1e-3) / 1e12
+    return {**r, "achieved": achieved, "frac": achieved / PEAKS[prec], "flops_per_launch": fl}
+
+
+def rate(r):
+    """Text of a row kernel's rate."""
+    return (f"{r['achieved']:.1f} TFLOP/s" if r["achieved"] is not None
+            else f"{r['four_candidate_tflops']:.1f} TFLOP/s of four candidates")
 
 
 def measured_traffic(workload, prec):
@@ -280,8 +299,7 @@ def run_eloc_bench(args):
     head = results[head_prec]
     hs = head["stats"]
     wh = Wh["w"]
-    achieved = row_flops(hs, wh, head_prec) / (hs["ms_psi"] * 1e-3) / 1e12
-    peak = PEAKS[head_prec]
+    roof = {p: row_roofline(r["stats"], wh, Wh["ans"], p) for p, r in results.items()}
     line = {
         "metric": "local energies/sec at fixed bond dim D",
         "value": head["value"],
@@ -301,21 +319,17 @@ def run_eloc_bench(args):
         "rows_per_step": hs["n_rows"],
         "site_rows_per_step": hs["n_site_rows"],
         "by_precision": {p: {"value": r["value"], "ms_per_step": r["ms_per_step"],
-                             "row_kernel_ms": r["stats"]["ms_psi"],
-                             "row_kernel_tflops": row_flops(r["stats"], wh, p) / r["stats"]["ms_psi"] / 1e9,
-                             "row_kernel_frac_of_peak": row_flops(r["stats"], wh, p) / r["stats"]["ms_psi"] / 1e9
-                             / PEAKS[p],
+                             "row_kernel": roof[p]["kernel"], "row_kernel_ms": r["stats"]["ms_psi"],
+                             "row_kernel_tflops": roof[p]["achieved"],
+                             "row_kernel_four_candidate_tflops": roof[p]["four_candidate_tflops"],
+                             "row_kernel_frac_of_peak": roof[p]["frac"],
                              "stages_ms": {k: r["stats"][k] for k in ("ms_enumerate", "ms_draw", "ms_rows",
                                                                        "ms_amplitude", "ms_reduce")},
                              "H_elements_per_s_enumerate": N * int(Wh["inst"].n_conn)
                              / (r["stats"]["ms_enumerate"] * 1e-3),
                              "batch_energy": r["E"]} for p, r in results.items()},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                     "frac": achieved / peak,
+        "roofline": {**roof[head_prec],
                      "traffic": args.traffic_bytes if args.traffic_bytes else measured_traffic(head_name, head_prec),
-                     "kernel": "row amplitude kernel (bond contractions and conditionals): k_psi_tri in FP64, "
-                               "(and FP32 but for the chip 16 chain: k_psi_mt), k_psi_b16 in BF16",
-                     "flops_per_launch": row_flops(hs, wh, head_prec), "ms_per_launch": hs["ms_psi"],
                      "kernel_sha16": kernel_sha16()},
     }
     if not args.headline_only:
@@ -324,8 +338,8 @@ def run_eloc_bench(args):
         line[other] = {"workload": WORKLOAD_TEXT[other],
                        "by_precision": {p: {"value": r["value"], "ms_per_step": r["ms_per_step"],
                                             "row_kernel_ms": r["stats"]["ms_psi"],
-                                            "row_kernel_frac_of_peak": row_flops(r["stats"], Wo["w"], p)
-                                            / r["stats"]["ms_psi"] / 1e9 / PEAKS[p]}
+                                            "row_kernel_frac_of_peak": row_roofline(r["stats"], Wo["w"], Wo["ans"],
+                                                                                    p)["frac"]}
                                         for p, r in ro.items()}}
         eq = {}
         for Wx, n_sub in ((Wh, 256 if head_name == "c3" else Wh["w"].n_samples),
@@ -525,14 +539,12 @@ def run_next_bench(args):
     for prec in ("f32", "f64"):
         kw = dict(eps=w.eps, n_eps=w.n_eps, precision=prec, stream_id=0)
         dt, (o, st) = timed(lambda: nqs.eloc_complex(ctx, inst, ans, s, seed=w.seed, **kw), 3)
-        fl = row_flops(st, w, prec) / (st["ms_psi"] * 1e-3) / 1e12
+        roof = row_roofline(st, w, ans, prec)
         cx[prec] = {"local_energies_per_s": w.n_samples / dt, "ms_per_step": dt * 1e3,
                     "row_kernel_ms": st["ms_psi"], "site_rows": st["n_site_rows"], "E_im": st["E_im"],
-                    "roofline": {"bound": "mfma", "achieved": fl, "peak": PEAKS[prec], "unit": "TFLOP/s",
-                                 "frac": fl / PEAKS[prec], "flops_per_launch": row_flops(st, w, prec),
-                                 "kernel": "k_psi_mt<float,32,...,CPLX>" if prec == "f32" else "k_psi_tri<32,...,CPLX>"}}
+                    "roofline": roof}
         print(f"# complex {prec}: {w.n_samples / dt:.0f} E_loc/s, row kernel {st['ms_psi']:.2f} ms, "
-              f"{fl:.2f} TFLOP/s", file=sys.stderr, flush=True)
+              f"{rate(roof)}", file=sys.stderr, flush=True)
     p = torch.from_numpy(w.params.copy()).cuda()
     m, v = torch.zeros_like(p), torch.zeros_like(p)
     steps = []
@@ -618,16 +630,14 @@ def run_configs_bench(args):
             se = float(np.sqrt((wf ** 2 * (el[ok] - E) ** 2).sum()) / wf.sum())
             ess = float(wf.sum() ** 2 / (wf ** 2).sum())
             energies[prec] = (E, se)
-            fl = row_flops(st, w, prec) / (st["ms_psi"] * 1e-3) / 1e12
+            roof = row_roofline(st, w, ans, prec)
             res[prec] = {"local_energies_per_s": w.n_samples / dt, "ms_per_step": dt * 1e3, "rows": st["n_rows"],
                          "site_rows": st["n_site_rows"], "E": E, "sampling_se": se, "effective_samples": ess,
                          "stage_ms": {k: st[k] for k in ("ms_enumerate", "ms_draw", "ms_rows", "ms_amplitude",
                                                           "ms_reduce", "ms_psi")},
-                         "roofline": {"bound": "mfma", "achieved": fl, "peak": PEAKS[prec], "unit": "TFLOP/s",
-                                      "frac": fl / PEAKS[prec], "flops_per_launch": row_flops(st, w, prec),
-                                      "kernel": "row amplitude kernel"}}
+                         "roofline": roof}
             print(f"# {name} {prec}: {w.n_samples / dt:.0f} E_loc/s, {st['n_rows']} rows, row kernel "
-                  f"{st['ms_psi']:.1f} ms at {fl:.1f} TFLOP/s", file=sys.stderr, flush=True)
+                  f"{st['ms_psi']:.1f} ms at {rate(roof)}", file=sys.stderr, flush=True)
         E64, se64 = energies["f64"]
         for prec in precs:
             res[prec]["energy_error_in_se_vs_f64_gpu"] = abs(energies[prec][0] - E64) / se64

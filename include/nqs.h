@@ -229,6 +229,10 @@ int64_t nqs_ansatz_n_params(const nqs_ansatz* ans);
  * call refuses it with EINVAL until a bind succeeds.  Work queued before a
  * failure has completed when the call returns. */
 nqs_status nqs_ansatz_bind_params(nqs_ansatz* ans, const double* params, hipStream_t stream);
+/* Name of the kernel that evaluates the amplitude rows of local energies of this
+ * precision (nqs_precision) with the bound parameters, e.g. "k_psi_tri<double>";
+ * NULL when unbound or when the precision does not run with this ansatz. */
+const char* nqs_ansatz_row_kernel(const nqs_ansatz* ans, int32_t precision);
 
 /* log|Psi(n)| (device double[N]) and sign Psi(n) (device int8[N]) of N samples.
  * A sample outside the sector is EINVAL; Psi(n) = 0 gives -inf and sign 0. */

@@ -1647,6 +1647,16 @@ nqs_status check_supported(const nqs_ansatz* a, int precision) {
 
 extern "C" {
 
+const char* nqs_ansatz_row_kernel(const nqs_ansatz* ans, int32_t precision) {
+  if (!ans || !ans->bound || precision < 0 || precision > 3) return nullptr;
+  if (is_bf16(precision)) return ans->cplx || ans->tensor ? nullptr : "k_psi_b16";
+  const bool f64 = precision == NQS_F64;
+  if (f64 && ans->tensor && !ans->tn_mfma && !ans->tn_f64_ok) return nullptr;
+  if (ans->tri_rows(precision)) return f64 ? "k_psi_tri<double>" : "k_psi_tri<float>";
+  if (ans->tensor && !ans->tn_mfma) return f64 ? "k_psi_tn<double>" : "k_psi_tn<float>";
+  return f64 ? "k_psi_mt<double>" : "k_psi_mt<float>";
+}
+
 nqs_status nqs_connected(nqs_ctx* ctx, const nqs_instance* inst, const uint64_t* samples, int64_t N,
                          uint64_t* m_out, double* h_out, double* hdiag_out, hipStream_t stream) {
   if (!ctx || !inst || (!samples && N > 0) || N < 0) return fail(NQS_EINVAL, "bad arguments");

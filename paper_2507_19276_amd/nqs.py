@@ -103,6 +103,8 @@ def lib():
     L.nqs_ansatz_n_params.argtypes = [_p]
     L.nqs_ansatz_n_params.restype = C.c_int64
     L.nqs_ansatz_bind_params.argtypes = [_p, _p, _p]
+    L.nqs_ansatz_row_kernel.argtypes = [_p, C.c_int32]
+    L.nqs_ansatz_row_kernel.restype = C.c_char_p
     L.nqs_logpsi.argtypes = [_p, _p, _p, C.c_int64, C.c_int32, _p, _p, _p]
     L.nqs_logpsi_vjp.argtypes = [_p, _p, _p, C.c_int64, _p, C.c_int32, _p, _p]
     L.nqs_logpsi_phase.argtypes = [_p, _p, _p, C.c_int64, C.c_int32, _p, _p, _p]
@@ -273,6 +275,12 @@ class Ansatz:
         check(lib().nqs_ansatz_bind_params(self.h, _ptr(p), _p(_stream())))
         self._bound = p.clone() if p.data_ptr() == params.data_ptr() else p
         return self
+
+    def row_kernel(self, precision="f64") -> Optional[str]:
+        """Name of the kernel that evaluates the amplitude rows of local energies."""
+        pr = PRECISIONS[precision] if isinstance(precision, str) else int(precision)
+        k = lib().nqs_ansatz_row_kernel(self.h, pr)
+        return None if k is None else k.decode()
 
     def logpsi(self, samples, precision="f64"):
         s = _samples(samples)
