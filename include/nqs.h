@@ -45,8 +45,9 @@
  *   3. once per amplitude pass in FP64 / FP32 with resumed rows, to read the
  *      number of shared-prefix nodes of the pass (it sizes the node pass),
  *   4. at the end;
- * with a stats pointer also before each further pass, for the stage timers and
- * the per-site row totals of the one before.  nqs_ansatz_bind_params lays the
+ * with a stats pointer also after the samples' own pass (rows that resume) and
+ * before each further pass, for the stage timers and the per-site row totals of
+ * the one before.  nqs_ansatz_bind_params lays the
  * parameters out on the device and waits for their checks (infinities, zero and
  * negative eta decide its result and the kernels used).  Workspace blocks go
  * back to the context's pool behind the work queued on the call's stream

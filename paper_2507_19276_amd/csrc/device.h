@@ -75,7 +75,6 @@ struct SpinEnds {
     bh = nth_site(~bl & ml, ~bh_ & mh, K - nb);
     bad = __popcll(al) + __popcll(ah_) != na || __popcll(bl) + __popcll(bh_) != nb;
   }
-  __device__ bool allowed(int i, int s) const { return i <= ((s & 1) ? ae : ah) && i <= ((s & 2) ? be : bh); }
 };
 
 __device__ inline double tlog(double x) { return log(x); }

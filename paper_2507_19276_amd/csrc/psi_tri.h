@@ -78,7 +78,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
   constexpr bool LATE = NTL == 1;
   const int lane = threadIdx.x;
   const int j = lane & 15, g = lane >> 4;
-  const int own = NTL == 4 ? g : (NTL == 2 ? (g >> 1) : 0);
+  const int own = NTL == 2 ? (g >> 1) : 0;
   const int64_t base = int64_t(blockIdx.x) * RW;
   V* ring = reinterpret_cast<V*>(smem) + lane;
   const CInt* fptr = (const CInt*)(P.pptr);
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
     toff[t] = q.coff;
     tneed[t] = q.need;
   }
-  const bool writer = NTL == 4 || (NTL == 2 ? (g & 1) == 0 : g == 0);
+  const bool writer = NTL == 2 ? (g & 1) == 0 : g == 0;
   auto store_pre = [&](int i) {
     if (STORE == 1 && writer && olive && orow < X.ns) {
       const size_t so = size_t(i) * X.ns + orow;
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
 template <typename T, int CH, int NTL, int DM, int STORE, bool CPLX>
 hipError_t run_tri(const TriParams& P, const uint64_t* m, int64_t R, double* lphi, int8_t* sphi, hipStream_t st,
                    const PsiStates<T>& X, double* phs) {
-  static_assert(NTL <= 4, "the node-need marks assume at most 64 rows per wavefront");
+  static_assert(NTL <= 2, "a lane group owns the rows of one of at most two tiles");
   const size_t per_wave = size_t(P.W) * 16 * NTL * CH * sizeof(T);
   if (per_wave > 160 * 1024) return hipErrorInvalidValue;
   // one wavefront per workgroup: its LDS goes to the next as soon as it ends

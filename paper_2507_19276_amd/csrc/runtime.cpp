@@ -1081,7 +1081,6 @@ nqs_status nqs_ansatz_create(nqs_ctx* ctx, int K, int n_alpha, int n_beta, int c
       qoff[i] = int(nblk);
       nblk += tri_site_blocks(a->chip, fptr[i + 1] - fptr[i]);
     }
-    nblk += 2;   // the window's fetches past the last part
     a->tri_gstride = int64_t(4) * chi * (int64_t(chi) * a->dmax + 1);
     if ((st = upload(&a->d_qoff, qoff)) != NQS_OK) return st;
     a->tri_vofs = int(nblk * 2048);
@@ -1092,7 +1091,7 @@ nqs_status nqs_ansatz_create(nqs_ctx* ctx, int K, int n_alpha, int n_beta, int c
       qoff[i] = int(nblk32);
       nblk32 += 4 * tri_lc32(a->chip, fptr[i + 1] - fptr[i]);
     }
-    nblk32 += kTriWindow32;
+    nblk32 += kTriWindow32;   // the window's fetches past the last site (FP64: of the first blocks again)
     if ((st = upload(&a->d_qoff32, qoff)) != NQS_OK) return st;
     a->tri_vofs32 = int(nblk32 * 1024);
     a->tri_bytes32 = a->tri_vofs32 + K * 6 * a->chip * int(sizeof(float));
@@ -2449,12 +2448,12 @@ nqs_status nqs_eloc_workspace_bytes(const nqs_instance* inst, const nqs_ansatz* 
       const NodeCaps c = node_caps(rows, K, ans->W, pair_nodes(K, tn), tn);
       const int64_t nslots = node_slots(c, K, tn);
       const size_t esz = state_bytes(opts->precision);
-      b += al(size_t(N) * 4) + 4 * al(size_t(N) * 8) + al(24);
+      b += al(size_t(N) * 4) + 4 * al(size_t(N) * 8) + al(8);
       b += al(size_t(c.nodes) * 16) + al(size_t(c.nodes) * 4) + 2 * al(size_t(c.nodes)) + al(size_t(c.nodes) * 8);
       b += al(size_t(c.nodes) * 4) + al(size_t(c.nodes)) + al(size_t(c.nodes) * 8);
       b += al(size_t(c.nodes) * 8) + al(size_t(c.nodes) * 2);
       b += al(size_t(c.nodes) * sizeof(NodeRec));
-      if (!tn) b += al(size_t(slot_blocks(c.nodes)) * 8) + al(4);
+      if (!tn) b += al(size_t(slot_blocks(c.nodes)) * 8);
       b += al(size_t(c.nodes) * 8) + al(size_t(c.nodes));
       b += al(size_t(nslots) * ans->chip * esz) + al(size_t(c.entries) * sizeof(LogProd<double>));
       if (ans->cplx)
@@ -2463,8 +2462,7 @@ nqs_status nqs_eloc_workspace_bytes(const nqs_instance* inst, const nqs_ansatz* 
       b += al(size_t(order_blocks(rows)) * (K + 1) * 4) + al(size_t(K + 1) * 8);
     }
   }
-  b += 3 * al(size_t(N) * 8) + al(64);     // outputs the caller did not provide, batch sums
-  b += al(4);                              // sample validation flag
+  b += 3 * al(size_t(N) * 8);     // outputs the caller did not provide
   *bytes = b;
   return NQS_OK;
 }
