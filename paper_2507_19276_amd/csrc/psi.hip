@@ -262,12 +262,14 @@ __global__ __launch_bounds__(256, TN && sizeof(T) == 4 && CH == 16 ? 2 : 1) void
     }
     iend = __builtin_amdgcn_readfirstlane(em < P.K ? em : P.K);
   }
-  // Resumed rows of the tensor term at chip 16 in FP32 (a candidate is one output
-  // tile): the candidates that the particle-number mask forbids to every row of the
-  // wavefront are left out.  (Row kernel, K = 20 NN+NNN chi = 16: FP32 6.78 -> 6.61
-  // ms.  Elsewhere the branches cost more than they save: FP64 16.58 -> 16.94 ms, the
-  // FP32 chain without the term 4.48 -> 4.57.)
-  constexpr bool SKIP = TN && sizeof(T) == 4 && TPC == 1 && SEED && !SAMPLE && PQ == KS;
+  // Resumed FP32 rows at chip 16 (a candidate is one output tile): the candidates
+  // that the particle-number mask forbids to every row of the wavefront are left out.
+  // Row kernels without and with it: chain chi = 16 on samples drawn from Phi^2, K = 20
+  // 4.32 and 4.17 ms, K = 50 2.25 and 2.10; on uniform random samples, which leave
+  // less out, chain K = 20 4.48 and 4.57, tensor-RNN K = 20 6.78 and 6.61.  FP64, whose
+  // rows here are mostly the tensor term's, pays more for the branches: lattice 4.83
+  // and 5.09 (drawn samples).
+  constexpr bool SKIP = sizeof(T) == 4 && TPC == 1 && SEED && !SAMPLE && PQ == KS;
   for (int i = i0; i < iend; ++i) {
     store_pre(i);
     const int wslot = wsl[i];
