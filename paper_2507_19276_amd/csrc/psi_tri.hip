@@ -52,21 +52,28 @@ __global__ __launch_bounds__(kQrThreads) void k_tri_qr(TriBuild B) {
   for (int k = 0; k < steps; ++k) {
     if (wv == 0) {
       double* a = G + int64_t(k) * rows;
-      // the column times a power of two that brings its largest entry to [1/2, 1):
-      // the squares of entries beyond 1e+-154 would leave the range of a double
-      // (the reflection does not depend on v's length, so no other bit moves)
-      double big = 0.0;
-      for (int r = k + lane; r < rows; r += 64) big = fmax(big, fabs(a[r]));
-      big = wave_max(big);
-      int ex;
-      (void)frexp(big, &ex);
       double ss = 0.0;
       for (int r = k + lane; r < rows; r += 64) {
-        const double x = ldexp(a[r], -ex);
-        v[r] = x;
-        ss = tfma(x, x, ss);
+        v[r] = a[r];
+        ss = tfma(a[r], a[r], ss);
       }
       ss = wave_sum(ss);
+      // the squares of entries beyond 1e+-154, and the products of v with other columns
+      // long before, leave the range of a double: a column far from 1 is taken times a
+      // power of two that brings its largest entry to [1/2, 1) (the reflection does not
+      // depend on v's length)
+      int ex = 0;
+      if (!(ss > 1e-40 && ss < 1e40)) {
+        double big = 0.0;
+        for (int r = k + lane; r < rows; r += 64) big = fmax(big, fabs(a[r]));
+        (void)frexp(wave_max(big), &ex);
+        ss = 0.0;
+        for (int r = k + lane; r < rows; r += 64) {
+          v[r] = ldexp(a[r], -ex);
+          ss = tfma(v[r], v[r], ss);
+        }
+        ss = wave_sum(ss);
+      }
       const double a0 = ldexp(a[k], -ex), nrm = sqrt(ss);
       // v = a -+ |a| e_k, H = 1 - tau v v^T with tau = 2 / v^T v
       const double beta = a0 < 0.0 ? nrm : -nrm;
