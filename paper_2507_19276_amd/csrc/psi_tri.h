@@ -22,7 +22,8 @@
 // What bounds it: FP64 MFMA and VALU instructions share the SIMD's FP64 units
 // (they never overlap, measured), so its time is its matrix instructions plus its
 // epilogue plus what the resident wavefronts do not hide.  Hence two tiles of rows
-// per wavefront (each operand block feeds two MFMA chains) at registers for two
+// per wavefront (each operand block feeds two MFMA chains; one tile in launches too
+// small to fill the chip, see kTriOneTileRows) at registers for two
 // or three wavefronts per SIMD: at chi = 32 four tiles at one wavefront ran
 // 160 against 119 ms.  Row kernels before (psi.hip) and now: NN+NNN K = 50, chi = 32,
 // 4096 samples 202 -> 119 ms (MFMA busy 84%); 3x3x2 lattice chi = 64, 1024 samples
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(64, tri_occ<T>(CH, DM)) void k_psi_tri(TriParams P,
   // all four allowed, own state; and the wavefront's parts there: bit 0 = some
   // row has all four states allowed (Z from R), bit 1 + s = candidate s is some
   // row's state, or an allowed state of a row whose mask forbids another (not
-  // QUAD: of any row).
+  // QUAD: of any row; all four where `sums`).
   struct Masks {
     uint64_t full, a0, a1, b0, b1;   // state s = a + 2 b is allowed where a's and b's masks have the lane
     uint32_t pt, own;                // own: bit s = s is some row's state

@@ -1385,12 +1385,12 @@ bool is_bf16(int precision) { return precision == NQS_BF16 || precision == NQS_B
 size_t state_bytes(int precision) { return precision == NQS_F64 ? 8 : (precision == NQS_F32 ? 4 : 2); }
 size_t mantissa_bytes(int precision) { return precision == NQS_F64 ? 8 : 4; }
 
-// amplitudes of R rows into (lphi, sphi).  mode PSI_STORE (samples, with rs)
-// or PSI_SEED (rows of a pass, with rs and its order) or PSI_ROWS (rows of a pass from
-// site 0, with their samples in rs).  The rows of a local
-// energy (every mode but PLAIN) take the triangular normaliser in FP64 where
-// there is one; the amplitudes that PLAIN and STORE return for samples are those
-// of the four-candidate sum, as the sampler's.
+// amplitudes of R rows into (lphi, sphi).  mode PSI_STORE (samples, with rs),
+// PSI_SEED (rows of a pass, with rs and its order) or PSI_ROWS (rows of a pass from
+// site 0, with their samples in rs).  The rows of a local energy (every mode but
+// PLAIN) take the triangular normaliser in FP64 where there is one; the amplitudes
+// of the samples themselves (PLAIN, STORE, the samples among ROWS) are those of the
+// four-candidate sum, as the sampler's.
 // phs: complex parameters, the phase of each row
 nqs_status run_amplitudes(const nqs_ansatz* a, int precision, const uint64_t* m, int64_t R, double* lphi,
                           int8_t* sphi, hipStream_t st, const Resume* rs = nullptr, int mode = PSI_PLAIN,
